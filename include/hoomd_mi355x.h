@@ -122,14 +122,15 @@ typedef struct {
                               latches HOOMD_E_DANGEROUS_BUILD: a particle may
                               have passed r_buff/2 before it was seen
                               (Sec. 4.2, Sec. 6.1)                          */
-    int32_t tpp_nlist;     /* lanes per particle of the neighbour-list build:
-                              0 or the fixed value hoomd_autotune() reports
-                              (anything else is HOOMD_E_ARG)               */
+    int32_t tpp_nlist;     /* neighbour-list build: 64 or 32, the members of a
+                              tile's cells staged at once (1,536 or 768; the
+                              same for mixed-precision DPD either way), 0 =
+                              64 (anything else is HOOMD_E_ARG)            */
     int32_t tpp_force;     /* lanes per particle, forces: 1, 2, 4, 8 or 16
                               (0 = chosen from the system size; hoomd_autotune
                               times the candidates) (Sec. 5.1, 5.2)         */
-    int32_t block_nlist;   /* threads per workgroup of the build: 0 or the
-                              value hoomd_autotune() reports                */
+    int32_t block_nlist;   /* threads per workgroup of the build: 256 or 512,
+                              0 = 256 (512 for mixed-precision DPD)         */
     int32_t block_force;   /* threads per workgroup of the force pass: 0 or
                               64 * tpp_force (one 64-row tile each)         */
     int32_t use_graph;     /* 1: step() replays captured pairs of middle steps
@@ -466,8 +467,8 @@ int hoomd_get_layout(hoomd_ctx *ctx, int32_t sys, hoomd_layout *out);
  * neighbour count to within 4) from a process-wide cache, and scans only
  * when there is none.  Candidates: the force pass with W = 1, 2, 4, 8, 16
  * lanes per particle (64 W threads per workgroup); the framed list build
- * with (lanes per row, threads per workgroup) = (64, 512), (64, 256),
- * (32, 512), (32, 256).  A scan rebuilds the neighbour list afterwards, so
+ * with (tpp_nlist, block_nlist) = (64, 512), (64, 256), (32, 512),
+ * (32, 256).  A scan rebuilds the neighbour list afterwards, so
  * the state is what it was.  Synchronises when tuning.  Fields given
  * explicitly in hoomd_params are kept (not tuned). */
 typedef struct {

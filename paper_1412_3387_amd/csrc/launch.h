@@ -38,6 +38,7 @@ struct LaunchCtx {
     int32_t *cell_size;
     int32_t *cell_idx;
     float4 *cell_xf;               // member position from the cell corner (FP32), row bits in w
+                                   // (cell_xf_slots(cell_cap) per cell)
     uint16_t *nlist;               // halo indices, tile-major rows
     int32_t *nn;
     int nlist_cap;
@@ -56,6 +57,9 @@ struct LaunchCtx {
     bool has_bonds;
     int32_t *slow_list;            // tiles the framed build passes on to the general one
     char *plan;                    // per-tile plans of the framed build (build_plan_bytes)
+    int seg_cap;                   // segments a plan has room for
+    bool sorted;                   // rows are put in Morton order (sort_period > 0)
+    bool line_rows;                // the line-ordered build (mixed-precision DPD)
     int32_t *slow_n;               // their number (cleared by the binning launch)
     int32_t *rare_list;            // tiles the force pass handles in its second launch
     int32_t *rare_n;               // their number (cleared by the binning launch)
@@ -129,12 +133,19 @@ void launch_disp_check(const LaunchCtx &L, const double4 *pos, int32_t *flag, in
 size_t force_lds_bytes(int pair, int halo_cap, int nlist_cap);
 int force_row_over_read();
 int force_halo_entry_bytes(int pair);
-size_t fast_build_lds_bytes(int nlist_cap);
-int nlist_lanes_per_row();  // lanes that scan one row in the framed build (default)
-int nlist_block();          // threads per workgroup of the framed build (default)
-bool nlist_shape_ok(int lanes_per_row, int block);  // a shape launch_nlist runs
-size_t build_plan_bytes(int64_t tiles);
+int nlist_chunk();  // chunk (64 or 32) of the framed build (default)
+int nlist_block(bool line_rows);  // threads per workgroup of the framed build (default)
+bool nlist_shape_ok(int chunk, int block);  // a shape launch_nlist runs
+int build_seg_cap(double cell_mean);  // segments of a tile's plan, from the mean members of a cell
+size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows);
+int cell_xf_slots(int cell_cap);      // cell_xf entries per cell
 hipError_t prepare_nlist(int nlist_cap);
+// The line-ordered build (nlist_lines.hip), behind launch_cell_sort and
+// launch_nlist.
+size_t line_plan_bytes(int64_t tiles);
+hipError_t prepare_lines(int nlist_cap);
+void launch_cells_and_lines(const LaunchCtx &L, const double4 *pos, int n_sort, int n_plan);
+void launch_build_lines(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int block);
 // Raises the dynamic-LDS limit of the rare-tile force kernels (init time).
 hipError_t prepare_force();
 

@@ -31,7 +31,12 @@
 // Tile header halo_n[tile]: bits 0-15 halo size, bits 16-30 the longest row
 // of the tile, bit 31 set when the tile is too wide for one periodic image
 // per halo entry.
-#include "launch.h"
+#include <algorithm>
+#include <cmath>
+#include <cstddef>
+#include <type_traits>
+
+#include "nlist_dev.h"
 
 namespace md {
 
@@ -39,8 +44,6 @@ constexpr int kBuildThreads = 512;   // 64 rows x 8 lanes
 constexpr int kBuildW = 8;
 constexpr int kChunk = 2048;         // members staged at once
 constexpr int kSlotMax = 16384;      // members of a tile's stencil cells
-constexpr int kRebuildGrid = 2048;   // blocks of the grid-stride rebuild kernels
-constexpr int kPlanGrid = 8192;      // one-wave workgroups of the plan kernel
 constexpr int kKeys = 2048;          // 64 rows x 27 stencil cells, padded
 constexpr int kKpt = kKeys / kBuildThreads;  // stencil keys per thread
 static_assert(kKeys % kBuildThreads == 0 && kKeys <= 8 * kBuildThreads, "key split");
@@ -125,100 +128,9 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
     }
 }
 
-// System owning a cell: largest s with cprefix[s] <= c (cprefix holds each
-// system's first cell; a compact array, so the search stays in the scalar
-// cache).
-__device__ __forceinline__ int find_sys_cell(const int64_t *__restrict__ cprefix, int n_sys, int64_t c)
-{
-    int lo = 0, hi = n_sys;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (cprefix[mid] <= c) lo = mid;
-        else hi = mid;
-    }
-    return lo;
-}
-
-// One wave per cell (wave w of W takes cells w, w + W, ...): members ranked
-// by their FP32 x coordinate relative to the cell's corner, ties by row index
-// (a total order on (bits, row), so the ranks are a permutation whatever the
-// values), sizes published.  Next to each member's row the list keeps its
-// position relative to the cell's lower corner in FP32 (row bits in w), so
-// that the framed build stages a cell with one coalesced read.  The counts
-// are left for the plan of the framed build, which runs beside this, and
-// cleared by the framed scan.  cell_cap <= 64 * CPL.
-template <int CPL>
-__device__ __forceinline__ void cell_sort_waves(int64_t wfirst, int64_t wstep, const SysDev *__restrict__ sys,
-                                                const int64_t *__restrict__ cprefix, int n_sys, const double4 *__restrict__ pos, int64_t n_cells,
-                                                const int32_t *__restrict__ cell_count,
-                                                int32_t *__restrict__ cell_size, int32_t *__restrict__ cell_idx,
-                                                float4 *__restrict__ cell_xf, int cell_cap,
-                                                const int32_t *__restrict__ sflag)
-{
-    const int lane = lane_id();
-    for (int64_t c = wfirst; c < n_cells; c += wstep) {
-        const int s = find_sys_cell(cprefix, n_sys, c);
-        if (!sflag[s]) continue;  // this system keeps its list
-        int m = cell_count[c];
-        m = m < cell_cap ? m : cell_cap;
-        const SysDev &S = sys[s];
-        const int64_t key = c - S.cell0;
-        const int cx = (int)(key % S.bins[0]), cy = (int)((key / S.bins[0]) % S.bins[1]),
-                  cz = (int)(key / ((int64_t)S.bins[0] * S.bins[1]));
-        const double ox = S.lo[0] + (double)cx * (S.L[0] / S.bins[0]);
-        const double oy = S.lo[1] + (double)cy * (S.L[1] / S.bins[1]);
-        const double oz = S.lo[2] + (double)cz * (S.L[2] / S.bins[2]);
-        int32_t v[CPL];
-        float4 f[CPL];
-        int64_t ord[CPL];  // (x bits made order-preserving as a signed integer, row)
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-            const int k = q * kWave + lane;
-            v[q] = k < m ? cell_idx[c * cell_cap + k] : INT32_MAX;
-            f[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-            ord[q] = INT64_MAX;
-            if (k < m) {
-                const double4 x = pos[v[q]];
-                f[q] = make_float4((float)(x.x - ox), (float)(x.y - oy), (float)(x.z - oz), __int_as_float(v[q]));
-                const int32_t b = __float_as_int(f[q].x);
-                ord[q] = ((int64_t)(b ^ ((b >> 31) & 0x7FFFFFFF)) << 32) | (uint32_t)v[q];
-            }
-        }
-        int rank[CPL];
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) rank[q] = 0;
-#pragma unroll
-        for (int q2 = 0; q2 < CPL; ++q2) {
-            const int tmax = m - q2 * kWave < kWave ? m - q2 * kWave : kWave;
-            for (int t = 0; t < tmax; ++t) {
-                const int64_t other = __shfl(ord[q2], t, kWave);
-#pragma unroll
-                for (int q = 0; q < CPL; ++q) rank[q] += other < ord[q] ? 1 : 0;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < CPL; ++q) {
-            const int k = q * kWave + lane;
-            if (k < m) {
-                cell_idx[c * cell_cap + rank[q]] = v[q];
-                cell_xf[c * cell_cap + rank[q]] = f[q];
-            }
-        }
-        if (lane == 0) cell_size[c] = m;
-    }
-}
-
 // ---------------------------------------------------------------------------
 // tile-halo neighbour list
 // ---------------------------------------------------------------------------
-
-// Wrap a cell coordinate difference into [-bins/2, bins - bins/2).
-__device__ __forceinline__ int wrap_rel(int d, int bins)
-{
-    const int h = bins / 2;
-    d = ((d + h) % bins + bins) % bins - h;
-    return d;
-}
 
 struct BuildShared {
     double cx[kChunk], cy[kChunk], cz[kChunk];
@@ -269,65 +181,9 @@ __device__ __forceinline__ int block_scan(int32_t *a, int n, int32_t *scan)
     return total;
 }
 
-// The same with wave-level shuffles: two barriers instead of 2 log2(NT).
-// The barriers order LDS accesses only (the caller's global accesses may stay
-// in flight).
-template <int NT>
-__device__ __forceinline__ int block_scan_w(int32_t *a, int n, int32_t *wsum)
-{
-    constexpr int NW = NT / kWave;
-    const int tid = threadIdx.x;
-    const int lane = lane_id();
-    const int w = tid >> 6;
-    const int b = 8 * tid;
-    int v[8];
-    int sum = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        v[k] = b + k < n ? a[b + k] : 0;
-        sum += v[k];
-    }
-    int inc = sum;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int y = __shfl_up(inc, off, kWave);
-        if (lane >= off) inc += y;
-    }
-    if (lane == kWave - 1) wsum[w] = inc;
-    lds_barrier();
-    int before = 0, total = 0;
-#pragma unroll
-    for (int q = 0; q < NW; ++q) {
-        const int x = wsum[q];
-        before += q < w ? x : 0;
-        total += x;
-    }
-    int run = before + inc - sum;
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        if (b + k < n) {
-            a[b + k] = run;
-            run += v[k];
-        }
-    lds_barrier();
-    return total;
-}
-
 __device__ __forceinline__ int block_scan8(int32_t *a, int n, int32_t *scan)
 {
     return block_scan<kBuildThreads>(a, n, scan);
-}
-
-// Index of the largest entry <= x in the ascending array a[0..n).
-__device__ __forceinline__ int upper_idx(const int32_t *a, int n, int x)
-{
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] <= x) lo = mid;
-        else hi = mid;
-    }
-    return lo;
 }
 
 template <bool EXCL>
@@ -677,200 +533,122 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
 // framed tile build
 // ---------------------------------------------------------------------------
 //
-// The common case of the build above, reorganised so that the work per
-// candidate is a handful of FP32 operations:
+// The common case of the build above, with the distances of a whole tile
+// taken on the matrix cores:
 //   * The tile's cells are placed in one frame: cell coordinates relative to
-//     the first row's cell, unwrapped across periodic faces.  The stencil
-//     cells of all rows are marked in a bitmap over the frame's box (home
-//     cells +-1), so the distinct cells come out in box order and the three
-//     x-adjacent cells of a row's stencil line are three consecutive distinct
-//     cells: a row's candidates are nine contiguous slot ranges ("runs").
-//   * Members are staged as FP32 positions in the frame, relative to the
-//     first row: the cell list keeps each member's position from its cell's
-//     corner in FP32, and staging adds the corner's frame position (one
-//     coalesced read per member).  One wave takes one row at a time; its 64
-//     lanes split the
-//     nine runs in proportion to their lengths (at least one lane each), so
-//     a row takes about (members / 55) + 1 passes.  A candidate whose FP32
-//     distance lies clearly inside or outside r_list is decided there; one
-//     within a relative band of 2^-10 of r_list^2 is decided by the exact
-//     FP64 test (difference of the stored positions, then the periodic
-//     shift), so the list is exactly the FP64 one.  Three roundings of
-//     magnitude at most F (the frame extent) per coordinate bound the FP32
-//     error of r^2 by about 6 sqrt(3) F 2^-24 / r_list relative; tiles with
-//     F > 512 r_list are passed on.
-//   * Rows are assembled in LDS and written out coalesced after the halo
-//     numbering, without a read-back.
+//     the first row's cell, unwrapped across periodic faces, positions
+//     relative to the centre of the rows' bounding box.  The stencil cells of
+//     all rows are marked in a bitmap over the frame's box; those farther
+//     than r_list from the bounding box are dropped.
+//   * Members are staged as FP32 positions in the frame: the cell list keeps
+//     each member's position from its cell's corner in FP32, and staging adds
+//     the corner's frame position (one coalesced read per member, a segment
+//     of up to 8 members of a cell per 8 lanes).  Members farther than
+//     r_list from the bounding box are dropped, the others packed in order.
+//   * |x_j - x_i|^2 - r_list^2 of 16 members x 16 rows is one
+//     v_mfma_f32_16x16x4_f32: (x_j, |x_j|^2) against (-2 x_i, 1), accumulated
+//     onto |x_i|^2 - r_list^2.  A wave takes 16 members at a time against all
+//     64 rows; the sign bits of the results, shifted into one mask word per
+//     lane and row, are the hits.  A result within the tile's band of zero
+//     (a bound on its FP32 error) is decided by the exact FP64 test
+//     (difference of the stored positions, then the periodic shift), so the
+//     list is exactly the FP64 one.
+//   * Two register swaps turn the masks so that lane t holds row t's words;
+//     the members that some row uses (an OR over the rows) are numbered, that
+//     is the tile's halo, and every row's hits are expanded into halo indices
+//     in LDS and written out coalesced.
 // Tiles that do not fit (a frame wider than a periodic box, fewer than three
 // cells on a periodic axis, too many distinct cells or members) are appended
 // to a device list and built by k_build_tile.
 
-constexpr int kFastThreads = 512;           // threads per workgroup by default (8 waves)
-constexpr int kFastWavesMax = 8;            // waves per workgroup at most
-constexpr int kFastChunk = 2560;     // members staged at once (float4 each)
-constexpr int kBoxMax = 8192;        // cells of the frame box
-constexpr int kBoxWords = kBoxMax / 32;
-constexpr int kUMax = 256;           // distinct cells of a framed tile
-constexpr int kFastSlotMax = 8192;   // members of a framed tile's stencil cells
-constexpr int kRuns = 9;
-static_assert(kUMax <= 256, "slot map holds distinct cells as bytes");
+constexpr int kFastThreads = 256;    // threads per workgroup by default (4 waves)
+constexpr int kBoxDense = 160;       // cells of a frame box looked at without marking the stencils first
+constexpr int kSegMin = 256;         // segments of a tile's plan there is always room for
 
-// DPP lane move within rows of 16 lanes (every lane of the wave active).
-template <int CTRL>
-__device__ __forceinline__ int dpp_mov(int v)
-{
-    return __builtin_amdgcn_update_dpp(v, v, CTRL, 0xF, 0xF, false);
-}
+// Per-tile plan of the framed build, written by k_cells_and_plan and read by
+// k_build_fast: the header, the rows' frame positions and the segments of up
+// to 8 members of its cells.
+struct PlanTile {
+    int32_t nu, nseg, pp;                // distinct cells (-1: passed on), segments, per-pair image flag
+    float band;                          // accumulated values nearer zero do not decide
+    float half[3], keep2;                // half widths of the rows' bounding box, bound on its distance^2
+    int32_t row, nrows;                  // first row, rows
+    float lo, hi;                        // FP32 differences squared below are inside, above outside
+    double ref[3], pad;                  // the frame's origin
+    float4 xrow[kTile];                  // row position in the frame, |x|^2 - r_list^2
+    float4 seg[1];                       // corner of the cell in the frame, first member / 8 (bits) in w
+};                                       // (as many as the context has room for)
+constexpr int kPlanHead = 80 + 16 * kTile;
+static_assert(offsetof(PlanTile, seg) == kPlanHead, "one packed block");
 
-// Minimum / maximum over the 64 lanes of a fully active wave: swaps within
-// quads, half rows and rows, then the four row results.
-__device__ __forceinline__ int wave_min_full(int v)
-{
-    v = min(v, dpp_mov<0xB1>(v));   // quad_perm [1,0,3,2]
-    v = min(v, dpp_mov<0x4E>(v));   // quad_perm [2,3,0,1]
-    v = min(v, dpp_mov<0x141>(v));  // row_half_mirror
-    v = min(v, dpp_mov<0x140>(v));  // row_mirror
-    return min(min(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               min(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
+// Bytes of a plan block with room for seg_cap segments.
+__host__ __device__ inline int64_t plan_stride(int seg_cap) { return kPlanHead + (int64_t)sizeof(float4) * seg_cap; }
 
-// Values that are the same in every lane (read from LDS or computed from
-// such values), moved to scalar registers.
-__device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ float uni(float v) { return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v))); }
-__device__ __forceinline__ double uni(double v)
-{
-    const int64_t b = __double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-    return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
-}
+// Members staged at once, each wave's in its own part: eight of a wave's
+// blocks of 16 fill a mask word of 32 bits per row and result group.  LPR 64
+// holds the kept members of most tiles of a liquid in one pass (an LJ liquid
+// at 0.8442 keeps 1,140 on average), whose rows are put together in the LDS
+// of the staged positions, and leaves room for four workgroups of 256 threads
+// per CU; with LPR 32 most tiles take two passes.  (The passes decide the
+// order of a row's entries, so they are the same with and without bonds.)
+constexpr int build_chunk(int lpr) { return 24 * lpr; }
+constexpr int kExSlots = 512;        // slots of a tile's partner-tag table (64 rows x 4 partners)
 
-__device__ __forceinline__ int wave_max_full(int v)
-{
-    v = max(v, dpp_mov<0xB1>(v));
-    v = max(v, dpp_mov<0x4E>(v));
-    v = max(v, dpp_mov<0x141>(v));
-    v = max(v, dpp_mov<0x140>(v));
-    return max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
-               max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48)));
-}
-
+template <int NT, int LPR>
 struct FastShared {
-    float4 cp[kFastChunk];               // member position in the frame (FP32), row in w
-    int32_t ucell[kUMax];                // cell index of each distinct cell
-    float4 uoff[kUMax];                  // frame position of each distinct cell's corner (FP32)
-    int32_t ustart[kUMax + 1];           // first slot of each distinct cell
-    uint32_t used[kFastSlotMax / 32];
-    int32_t wpre[kFastSlotMax / 32 + 1];
-    uint32_t run[kTile][kRuns];          // slot range of each row line: lo | hi << 16
-    uint32_t runc[kTile][kRuns];         // the same cut to the chunk and to the line's x-window
-    float hw[kTile][kRuns];              // half width in x of each row line
-    float4 xrow[kTile];                  // row position in the frame (FP32)
-    int32_t rown[kTile];                 // hits of each row so far
-    uint64_t lmask[kTile];               // per row: bit of the last lane of each (non-empty) line but the last
-    uint8_t lb[kTile][kRuns + 1];        // per row: first lane of each (non-empty) line, then the lanes used
-    uint8_t ln[kTile][kRuns];            // 32 lanes per row: the non-empty lines in order
-    uint8_t nk[kTile];                   // 32 lanes per row: non-empty lines in this chunk
-    int32_t scan[kFastWavesMax];         // per-wave totals of the block scans
-    uint8_t smap[kFastChunk];            // distinct cell of each slot of the chunk
-    double xref[3];                      // first row's position: the frame reference
-    int32_t info[5];                     // distinct cells, per-pair image flag, longest row, slots,
-                                         // FP32 decision band (float bits)
+    static constexpr int kC = build_chunk(LPR);
+    static constexpr int kWaves = NT / kWave;
+    static constexpr int kCw = kC / kWaves;              // members of a wave
+    static constexpr int kWords = (kCw / 16 + 7) / 8;
+    static_assert(kCw % 16 == 0 && kCw >= kWave && kCw <= 384, "whole blocks, at least a round");
+    int32_t cj[kC];                      // particle rows of the staged members
+    uint32_t used[kWords * kWaves * 4];  // hits of any row, per wave and result group
+    uint16_t cnt[kWaves][kTile];         // hits of each row in each wave's members
+    uint16_t selfq[kWaves][kTile];       // the row's own staged place, 0xFFFF: not this wave's
+    int32_t left[kWaves];                // the wave has members left for another pass
     int32_t grab[2];                     // tile indices taken from the die's counter
 };
 
-// Per-tile plan of the framed build, written by k_cells_and_plan and read by
-// k_build_fast: a header {distinct cells (-1: passed on), slots, per-pair
-// image flag, 0}, then per distinct cell {cell, first slot} and its corner
-// in the frame, per row its frame position, and per row line its slot range
-// and the half width in x that its y-z distance leaves.
-struct PlanPtrs {
-    int4 *hdr;
-    int2 *cell;
-    float4 *off;
-    float4 *xrow;
-    uint32_t *run;
-    float *hw;
+// Exclusions of a tile of bonded rows: the rows' partner tags in an open-
+// addressed table, and per wave the staged places found for them.
+template <int NT>
+struct ExShared {
+    int32_t tag[kExSlots];
+    uint8_t row[kExSlots];
+    int32_t n[NT / kWave][kTile];
+    uint16_t q[NT / kWave][kTile][2 * kMaxBondCap];
 };
 
-__host__ __device__ inline PlanPtrs plan_ptrs(char *base, int64_t tiles)
-{
-    PlanPtrs P;
-    size_t off = 0;
-    auto carve = [&](size_t bytes) {
-        char *p = base + off;
-        off += (bytes + 255) / 256 * 256;
-        return p;
-    };
-    P.hdr = reinterpret_cast<int4 *>(carve(sizeof(int4) * tiles));
-    P.cell = reinterpret_cast<int2 *>(carve(sizeof(int2) * tiles * kUMax));
-    P.off = reinterpret_cast<float4 *>(carve(sizeof(float4) * tiles * kUMax));
-    P.xrow = reinterpret_cast<float4 *>(carve(sizeof(float4) * tiles * kTile));
-    P.run = reinterpret_cast<uint32_t *>(carve(sizeof(uint32_t) * tiles * kTile * kRuns));
-    P.hw = reinterpret_cast<float *>(carve(sizeof(float) * tiles * kTile * kRuns));
-    return P;
-}
-
-// Exclusive scan in place of a[0..n), n <= 4 * 64, by one fully active
-// wave; returns the total.
-__device__ __forceinline__ int wave_scan_excl(int32_t *a, int n)
-{
-    const int lane = lane_id();
-    int v[4];
-    int sum = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int i = lane * 4 + k;
-        v[k] = i < n ? a[i] : 0;
-        sum += v[k];
-    }
-    int inc = sum;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int y = __shfl_up(inc, off, kWave);
-        if (lane >= off) inc += y;
-    }
-    const int total = __shfl(inc, kWave - 1, kWave);
-    int run = inc - sum;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const int i = lane * 4 + k;
-        if (i < n) a[i] = run;
-        run += v[k];
-    }
-    return total;
-}
-static_assert(kBoxWords <= 4 * kWave && kUMax <= 4 * kWave, "one-wave scans of the plan");
+// x, y, z and |x|^2 of the staged members: the four components' rows start
+// 16 banks apart, so that one read of 16 members' four components meets every
+// bank once.
+constexpr int build_astride(int kc) { return kc + 16 + (64 - kc % 64) % 64; }
 
 // The plan of one tile per wave (workgroups of one wave: no block barriers
 // wait on other waves, so many tiles are in flight per CU).  Lane t takes
 // row t: its home cell in the frame (cell coordinates relative to the first
 // row's cell, unwrapped across periodic faces with the cut opposite the first
-// row or through it, whichever gives the shorter extent), its nine x-lines of
-// three cells marked in a bitmap over the frame's box, the distinct cells in
-// box order with their sizes and first slots, and every line cut to the cells
-// within r_list.  The rows' build positions are written here.  Tiles that do
-// not fit (a frame wider than a periodic box, fewer than three cells on a
-// periodic axis, too many distinct cells or members) go to the general build.
-struct PlanShared {
-    uint32_t box[kBoxWords];
-    int32_t bpre[kBoxWords + 1];
-    int32_t ucell[kUMax];
-    int32_t ustart[kUMax + 1];
-};
-
+// row or, where that does not fit, through it).  Then a lane takes a cell of
+// the frame's box (home cells +-1) at a time: those within r_list of the
+// bounding box of some 16 rows are the tile's cells, their members its
+// segments, in box order.  A large box (rows that jump, where the Morton curve
+// leaves a region) holds many cells that no row's stencil meets: there the
+// stencils are marked in a bitmap first.  The rows' build positions are
+// written here.  Tiles that do not fit (a frame wider than a periodic box,
+// fewer than three cells on a periodic axis, too many cells or members) go to
+// the general build.
+// Vector instructions bound it: with the cells of every tile found from the
+// bitmap and a division per coordinate it took 2,250 of them per tile, and
+// the launch 222 us for 2,000,000 LJ rows; now
+// 174 us.
 __device__ __forceinline__ void plan_tiles(
-    PlanShared &ps, int pb, int npb, const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix,
-    int n_sys, int tiles, const double4 *__restrict__ pos, const int32_t *__restrict__ cell_count, int cell_cap,
-    double4 *__restrict__ xbuild, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n, PlanPtrs plan,
-    const int32_t *__restrict__ sflag, int32_t *__restrict__ halo_n, int halo_lds,
-    int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
+    int pb, int npb, const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
+    const double4 *__restrict__ pos, const int32_t *__restrict__ cell_count, int cell_cap,
+    double4 *__restrict__ xbuild, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
+    char *__restrict__ plan, int64_t stride, const int32_t *__restrict__ sflag,
+    int32_t *__restrict__ halo_n, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
 {
-    uint32_t *box = ps.box;
-    int32_t *bpre = ps.bpre;
-    int32_t *ucell = ps.ucell;
-    int32_t *ustart = ps.ustart;
+    __shared__ uint32_t box[kBoxMax / 32];
     const int lane = lane_id();
     int64_t tfirst, tend;
     int tstep;
@@ -892,24 +670,32 @@ __device__ __forceinline__ void plan_tiles(
         const int bins[3] = {S.bins[0], S.bins[1], S.bins[2]};
         const int per[3] = {S.per[0], S.per[1], S.per[2]};
         const int64_t row0 = S.row0, cell0 = S.cell0;
-        const int n_local = S.n_local;
+        // (each system's own room, whatever the other systems of the context
+        // have: it decides which build a tile gets)
+        const int n_local = S.n_local, seg_cap = S.seg_cap;
         const double rl2 = S.rl2;
         const int r0 = (tile - S.tile0) * kTile;
-        if (r0 >= n_local) {
-            // a tile past the local rows (room for particles that may
-            // arrive): an empty list and halo, nothing to build
+        PlanTile *pt = reinterpret_cast<PlanTile *>(plan + tile * stride);
+        // an empty plan: nu = 0 for a tile past the local rows (room for
+        // particles that may arrive), -1 for one passed on
+        auto empty = [&](int nu) {
             if (lane == 0) {
-                plan.hdr[tile] = make_int4(0, 0, 0, 0);
-                halo_n[tile] = 0;
+                pt->nu = nu;
+                pt->nseg = 0;
+                pt->pp = 0;
+                pt->nrows = 0;
             }
+        };
+        if (r0 >= n_local) {
+            empty(0);
+            if (lane == 0) halo_n[tile] = 0;
             continue;
         }
-        const float cw[3] = {(float)(Ls[0] / bins[0]), (float)(Ls[1] / bins[1]), (float)(Ls[2] / bins[2])};
+        const double wide[3] = {Ls[0] / bins[0], Ls[1] / bins[1], Ls[2] / bins[2]};
+        const float cw[3] = {(float)wide[0], (float)wide[1], (float)wide[2]};
         auto pass_on = [&]() {
-            if (lane == 0) {
-                slow_list[atomicAdd(slow_n, 1)] = tile;
-                plan.hdr[tile] = make_int4(-1, 0, 0, 0);
-            }
+            if (lane == 0) slow_list[atomicAdd(slow_n, 1)] = tile;
+            empty(-1);
         };
 
         // ---- rows: home cell in the frame, frame position, build position ----
@@ -919,44 +705,33 @@ __device__ __forceinline__ void plan_tiles(
         if (act) xbuild[row0 + r] = make_double4(xi.x, xi.y, xi.z, 0.0);
         const double xr[3] = {uni(xi.x), uni(xi.y), uni(xi.z)};  // row 0 of the tile
         const double xa[3] = {xi.x, xi.y, xi.z};
-        int c0[3], h[3], elo[3], ehi[3];
-        float xf[3], frel[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            c0[a] = uni(cell_coord(xr[a], S.lo[a], S.scale[a], bins[a]));
-            const int ci = cell_coord(xa[a], S.lo[a], S.scale[a], bins[a]);
-            const int d = ci - c0[a];
-            const int sft = bins[a] / 2;
-            const int hc[2] = {per[a] ? wrap_rel(d, bins[a]) : d, per[a] ? sft + wrap_rel(d - sft, bins[a]) : d};
-            int mn[2], mx[2];
-#pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                mn[v] = wave_min_full(act ? hc[v] : INT32_MAX);
-                mx[v] = wave_max_full(act ? hc[v] : INT32_MIN);
-            }
-            const int pick = mx[1] - mn[1] < mx[0] - mn[0] ? 1 : 0;
-            h[a] = hc[pick];
-            elo[a] = pick ? mn[1] : mn[0];
-            ehi[a] = pick ? mx[1] : mx[0];
-            // image of the row in the frame: the home cell at c0 + h
-            const int kimg = per[a] ? (c0[a] + h[a] - ci) / bins[a] : 0;
-            xf[a] = (float)((xa[a] + (double)kimg * Ls[a]) - xr[a]);
-            frel[a] = (float)(xa[a] - S.lo[a]) - (float)ci * cw[a];
-        }
-        plan.xrow[(int64_t)tile * kTile + lane] = make_float4(xf[0], xf[1], xf[2], 0.f);
-        // spread of the rows around row 0 per axis (xf is relative to it;
-        // non-negative floats order as their bit patterns)
-        float spread[3];
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-            spread[a] = __int_as_float(wave_max_full(act ? __float_as_int(fabsf(xf[a])) : 0));
-
-        // ---- frame box and the stencil-cell bitmap ----------------------------
-        int blo[3], X[3];
+        int c0[3], h[3], blo[3], X[3];
+        double xd[3];
+        float xf[3];
         bool pass = false;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
-            int lo_ = elo[a] - 1, hi_ = ehi[a] + 1;
+            const int ci = cell_coord(xa[a], S.lo[a], S.scale[a], bins[a]);
+            c0[a] = uni(ci);
+            const int hd = ci - c0[a];
+            // image of the row in the frame: the home cell at c0 + h
+            int kimg = 0;
+            if (per[a]) {
+                const int sft = bins[a] / 2;
+                kimg = hd >= bins[a] - sft ? -1 : (hd < -sft ? 1 : 0);
+            }
+            int elo = wave_min_full(act ? hd + kimg * bins[a] : INT32_MAX);
+            int ehi = wave_max_full(act ? hd + kimg * bins[a] : INT32_MIN);
+            if (per[a] && ehi - elo + 3 > bins[a]) {
+                kimg = hd < 0 ? 1 : 0;
+                elo = wave_min_full(act ? hd + kimg * bins[a] : INT32_MAX);
+                ehi = wave_max_full(act ? hd + kimg * bins[a] : INT32_MIN);
+            }
+            h[a] = hd + kimg * bins[a];
+            xd[a] = (xa[a] + (double)kimg * Ls[a]) - xr[a];
+            xf[a] = (float)xd[a];
+            // the frame's box
+            int lo_ = elo - 1, hi_ = ehi + 1;
             if (!per[a]) {
                 lo_ = lo_ > -c0[a] ? lo_ : -c0[a];
                 hi_ = hi_ < bins[a] - 1 - c0[a] ? hi_ : bins[a] - 1 - c0[a];
@@ -965,142 +740,156 @@ __device__ __forceinline__ void plan_tiles(
             }
             blo[a] = lo_;
             X[a] = hi_ - lo_ + 1;
-            if ((double)X[a] * (double)cw[a] > 512.0 * sqrt(rl2)) pass = true;
+            pass = pass || (double)X[a] * wide[a] > 512.0 * sqrt(rl2);
+        }
+        if (pass || X[0] * X[1] * X[2] > kBoxMax) {
+            pass_on();
+            continue;
         }
         const int vol = X[0] * X[1] * X[2];
-        if (pass || vol > kBoxMax) {
-            pass_on();
-            continue;
-        }
-        const int nbw = (vol + 31) >> 5;
-        __syncthreads();  // LDS of the previous tile no longer read
-        for (int q = lane; q < nbw; q += kWave) box[q] = 0u;
-        __syncthreads();
-        // a row's stencil as nine x-lines of (up to) three adjacent cells:
-        // consecutive bits of one box row
-        if (act) {
-            for (int rr = 0; rr < kRuns; ++rr) {
-                const int fy = h[1] + rr % 3 - 1, fz = h[2] + rr / 3 - 1;
-                if (!per[1] && (c0[1] + fy < 0 || c0[1] + fy >= bins[1])) continue;
-                if (!per[2] && (c0[2] + fz < 0 || c0[2] + fz >= bins[2])) continue;
-                int xa_ = h[0] - 1, xb_ = h[0] + 1;
-                if (!per[0]) {
-                    xa_ = c0[0] + xa_ >= 0 ? xa_ : -c0[0];
-                    xb_ = c0[0] + xb_ < bins[0] ? xb_ : bins[0] - 1 - c0[0];
-                }
-                const int b = ((fz - blo[2]) * X[1] + (fy - blo[1])) * X[0] + (xa_ - blo[0]);
-                const uint64_t bits = ((1ull << (xb_ - xa_ + 1)) - 1ull) << (b & 31);
-                atomicOr(&box[b >> 5], (uint32_t)bits);
-                if (bits >> 32) atomicOr(&box[(b >> 5) + 1], (uint32_t)(bits >> 32));
-            }
-        }
-        __syncthreads();
 
-        // ---- distinct cells (box order), sizes, first slots ----------------------
-        for (int q = lane; q < nbw; q += kWave) bpre[q] = __popc(box[q]);
-        __syncthreads();
-        const int nu = uni(wave_scan_excl(bpre, nbw));
-        __syncthreads();
-        if (nu > kUMax || nu < 1) {
-            pass_on();
-            continue;
-        }
-        for (int b = lane; b < vol; b += kWave) {
-            const uint32_t word = box[b >> 5];
-            if ((word >> (b & 31)) & 1u) ucell[bpre[b >> 5] + __popc(word & ((1u << (b & 31)) - 1u))] = b;
-        }
-        __syncthreads();
-        // four distinct cells per lane; every lane reads a valid cell (the
-        // last one again past the end) so that the reads are in flight together
-        int cells[4];
-        float4 offs[4];
-        int sizes[4];
+        // the frame's origin: the centre of the rows' bounding box (inactive
+        // rows, and rows that are no numbers, find nothing); and the bounding
+        // boxes of each 16 rows
+        const bool found = act && fabsf(xf[0]) < 1e15f && fabsf(xf[1]) < 1e15f && fabsf(xf[2]) < 1e15f;
+        const bool any = __ballot(found) != 0ull;
+        float half[3], spread[3], xc[3], gmid[4][3], ghalf[4][3];
+        double ref[3];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int u = lane + k * kWave;
-            const int b = ucell[u < nu ? u : nu - 1];
-            const int f[3] = {b % X[0] + blo[0], (b / X[0]) % X[1] + blo[1], b / (X[0] * X[1]) + blo[2]};
+        for (int a = 0; a < 3; ++a) {
+            const int o = float_order(xf[a]);
+            const int mnr = row_min_full(found ? o : INT32_MAX), mxr = row_max_full(found ? o : INT32_MIN);
+            int mn[4], mx[4];
+#pragma unroll
+            for (int R = 0; R < 4; ++R) {
+                mn[R] = __builtin_amdgcn_readlane(mnr, 16 * R);
+                mx[R] = __builtin_amdgcn_readlane(mxr, 16 * R);
+            }
+            const float lo_ = any ? float_unorder(min(min(mn[0], mn[1]), min(mn[2], mn[3]))) : 0.f;
+            const float hi_ = any ? float_unorder(max(max(mx[0], mx[1]), max(mx[2], mx[3]))) : 0.f;
+            const float ctr = 0.5f * (lo_ + hi_);
+            // (xf and its differences round: a little more than half the extent)
+            half[a] = 0.5000005f * (hi_ - lo_) + 0x1p-22f * fmaxf(fabsf(lo_), fabsf(hi_));
+            // spread of the rows around row 0 (xf is relative to it)
+            spread[a] = fmaxf(fabsf(lo_), fabsf(hi_));
+#pragma unroll
+            for (int R = 0; R < 4; ++R) {
+                const bool none = mn[R] > mx[R];
+                const float l = float_unorder(mn[R]), h2 = float_unorder(mx[R]);
+                gmid[R][a] = none ? 0.f : 0.5f * (l + h2) - ctr;
+                ghalf[R][a] = none ? -1e30f : 0.5f * (h2 - l);
+            }
+            ref[a] = xr[a] + (double)ctr;
+            xc[a] = (float)(xd[a] - (double)ctr);
+        }
+        const double n2 = (double)xc[0] * xc[0] + (double)xc[1] * xc[1] + (double)xc[2] * xc[2];
+        pt->xrow[lane] = found ? make_float4(xc[0], xc[1], xc[2], (float)(n2 - rl2)) : make_float4(0.f, 0.f, 0.f, 1e30f);
+        // Band around zero inside which the FP32 value of |x_j - x_i|^2 -
+        // r_list^2 cannot decide the test, with u = 2^-24 and the candidate
+        // within about r_list of a row (farther ones come out far above it):
+        // each separation is off by at most eta = 4 u (largest coordinate +
+        // r_list + cell: the cell-relative position, the corner, their sum
+        // and the row's position round once each), which moves r^2 by
+        // 2 sqrt(3) r_list eta + 3 eta^2; |x_j|^2, the accumulator's start and
+        // the four products and sums round to at most 12 u of the sum of the
+        // magnitudes, (|x_i| + |x_j|)^2 + r_list^2.  Doubled.
+        const float rmax = sqrtf(__int_as_float(wave_max_full(found ? __float_as_int((float)n2) : 0)));
+        const float amax = fmaxf(half[0], fmaxf(half[1], half[2]));
+        float band, keep2, near_lo, near_hi;
+        const double rl = sqrt(rl2);
+        {
+            const double u = 0x1p-24;
+            const double eta = 4.0 * u * ((double)amax + 1.02 * rl + (double)fmaxf(cw[0], fmaxf(cw[1], cw[2])));
+            const double mag = 2.0 * rmax * 1.0001 + 1.02 * rl;
+            const double moved = 2.0 * sqrt(3.0) * 1.02 * rl * eta + 3.0 * eta * eta;
+            const double dr2 = moved + 12.0 * u * (mag * mag + rl2);
+            band = (float)(2.0 * dr2);
+            // the differences themselves, squared in FP32: moved, and five
+            // more roundings of about r_list^2
+            const double dd = 2.0 * (moved + 6.0 * u * rl2);
+            near_lo = (float)(rl2 - dd);
+            near_hi = (float)(rl2 + dd);
+            // bound on the squared distance from the bounding box of anything
+            // within r_list of a row
+            keep2 = (float)(rl2 * 1.0001 + 1e-3 + 2.0 * dr2);
+        }
+
+        // ---- the cells within r_list of some 16 rows, their segments ----------
+        // (a quotient of cell numbers by high product: exact while the product
+        // of dividend and divisor stays below 2^32; kBoxMax^2 does)
+        const bool marked = vol > kBoxDense;
+        if (marked) {
+            // a row's stencil as nine x-lines of (up to) three adjacent cells:
+            // consecutive bits of one box row
+            __syncthreads();  // (an earlier tile's marks are read)
+            for (int q = lane; q < (vol + 31) / 32; q += kWave) box[q] = 0u;
+            __syncthreads();
+            if (found)
+                for (int rr = 0; rr < 9; ++rr) {
+                    const int fy = h[1] + rr % 3 - 1 - blo[1], fz = h[2] + rr / 3 - 1 - blo[2];
+                    if (fy < 0 || fy >= X[1] || fz < 0 || fz >= X[2]) continue;  // beyond an open face
+                    const int xa_ = h[0] - 1 > blo[0] ? h[0] - 1 : blo[0];
+                    const int xb_ = h[0] + 1 < blo[0] + X[0] - 1 ? h[0] + 1 : blo[0] + X[0] - 1;
+                    const int b = (fz * X[1] + fy) * X[0] + (xa_ - blo[0]);
+                    const uint64_t bits = ((1ull << (xb_ - xa_ + 1)) - 1ull) << (b & 31);
+                    atomicOr(&box[b >> 5], (uint32_t)bits);
+                    if (bits >> 32) atomicOr(&box[(b >> 5) + 1], (uint32_t)(bits >> 32));
+                }
+            __syncthreads();
+        }
+        const uint32_t inv0 = 0xFFFFFFFFu / (uint32_t)X[0] + 1u, inv01 = 0xFFFFFFFFu / (uint32_t)(X[0] * X[1]) + 1u;
+        const bool flat0 = X[0] == 1, flat01 = X[0] * X[1] == 1;
+        const int xs = cell_xf_stride(cell_cap) / kSeg;
+        int nu = 0, nseg = 0;
+        for (int b0 = 0; b0 < vol; b0 += kWave) {
+            const int b = b0 + lane < vol ? b0 + lane : vol - 1;
+            const int fz = flat01 ? b : (int)__umulhi((uint32_t)b, inv01);
+            const int t = b - fz * (X[0] * X[1]);
+            const int fy = flat0 ? t : (int)__umulhi((uint32_t)t, inv0);
+            const int f[3] = {t - fy * X[0] + blo[0], fy + blo[1], fz + blo[2]};
             int pc[3];
-            float off[3];
+            float off[3], mid[3], wid[3];
 #pragma unroll
             for (int a = 0; a < 3; ++a) {
                 pc[a] = c0[a] + f[a];
                 const int ki = pc[a] >= bins[a] ? 1 : (pc[a] < 0 ? -1 : 0);
                 pc[a] -= ki * bins[a];
-                // the cell's lower corner in the frame, relative to the reference
-                off[a] = (float)((S.lo[a] + (double)pc[a] * (Ls[a] / bins[a]) + (double)ki * Ls[a]) - xr[a]);
+                // the cell's lower corner in the frame
+                off[a] = (float)((S.lo[a] + (double)pc[a] * wide[a] + (double)ki * Ls[a]) - ref[a]);
+                // its middle and half width; an open axis's outermost cells
+                // hold whatever lies beyond them
+                mid[a] = off[a] + 0.5f * cw[a];
+                wid[a] = !per[a] && (pc[a] == 0 || pc[a] == bins[a] - 1) ? 1e30f : 0.501f * cw[a];
             }
-            cells[k] = (int32_t)(cell0 + ((int64_t)pc[2] * bins[1] + pc[1]) * bins[0] + pc[0]);
-            offs[k] = make_float4(off[0], off[1], off[2], 0.f);
-            sizes[k] = cell_count[cells[k]];
-        }
-        __syncthreads();  // ucell no longer read
+            bool near = false;
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int u = lane + k * kWave;
-            if (u < nu) ustart[u] = sizes[k] < cell_cap ? sizes[k] : cell_cap;
+            for (int R = 0; R < 4; ++R) {
+                float d2 = 0.f;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float gap = fmaxf(fabsf(mid[a] - gmid[R][a]) - (ghalf[R][a] + wid[a]), 0.f);
+                    d2 += gap * gap;
+                }
+                near = near || d2 <= keep2;
+            }
+            near = near && b0 + lane < vol && (!marked || ((box[b >> 5] >> (b & 31)) & 1u));
+            const int64_t cell = cell0 + ((int64_t)pc[2] * bins[1] + pc[1]) * bins[0] + pc[0];
+            int size = near ? cell_count[cell] : 0;
+            size = size < cell_cap ? size : cell_cap;
+            const int own = (size + kSeg - 1) / kSeg;
+            const int incl = wave_scan_incl(own);
+            const int s0 = nseg + incl - own;
+            for (int q = 0; q < own; ++q)
+                if (s0 + q < seg_cap)
+                    pt->seg[s0 + q] = make_float4(off[0], off[1], off[2], __int_as_float((int)cell * xs + q));
+            nseg += __builtin_amdgcn_readlane(incl, kWave - 1);
+            nu += __popcll(__ballot(size > 0));
         }
-        __syncthreads();
-        const int nslot = uni(wave_scan_excl(ustart, nu));
-        if (lane == 0) ustart[nu] = nslot;
-        __syncthreads();
-        if (nslot > kFastSlotMax) {
+        if (nseg > seg_cap) {
             pass_on();
             continue;
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int u = lane + k * kWave;
-            if (u < nu) {
-                plan.cell[(int64_t)tile * kUMax + u] = make_int2(cells[k], ustart[u]);
-                plan.off[(int64_t)tile * kUMax + u] = offs[k];
-            }
-        }
 
-        // ---- every row line cut to the cells within r_list; x half widths -----
-        const float rl2f = (float)rl2 * 1.0001f + 1e-3f;
-        float fext = 0.f;
-#pragma unroll
-        for (int a = 0; a < 3; ++a) fext = fmaxf(fext, (float)X[a] * cw[a]);
-        // bound on the FP32 error of a frame x difference, with room to spare
-        const float xmargin = 1e-3f + fext * 0x1p-18f;
-        const int64_t pr = ((int64_t)tile * kTile + lane) * kRuns;
-        for (int rr = 0; rr < kRuns; ++rr) {
-            uint32_t v = 0u;
-            float hwv = 0.f;
-            if (act) {
-                const int dy = rr % 3 - 1, dz = rr / 3 - 1;
-                const int hx = h[0], hy = h[1] + dy, hz = h[2] + dz;
-                bool in = (per[1] || (c0[1] + hy >= 0 && c0[1] + hy < bins[1])) &&
-                          (per[2] || (c0[2] + hz >= 0 && c0[2] + hz < bins[2]));
-                // squared distance in y and z from the row to the line's cells
-                // (a lower bound for every member of the line)
-                float gyz = 0.f;
-                if (dy != 0) {
-                    const float gg = dy < 0 ? frel[1] : cw[1] - frel[1];
-                    gyz += gg > 0.f ? gg * gg : 0.f;
-                }
-                if (dz != 0) {
-                    const float gg = dz < 0 ? frel[2] : cw[2] - frel[2];
-                    gyz += gg > 0.f ? gg * gg : 0.f;
-                }
-                in = in && gyz <= rl2f;
-                if (in) {
-                    const float fx = frel[0];
-                    const float gl = fx > 0.f ? fx : 0.f, gr = cw[0] - fx > 0.f ? cw[0] - fx : 0.f;
-                    const bool left = (per[0] || c0[0] + hx - 1 >= 0) && gl * gl + gyz <= rl2f;
-                    const bool right = (per[0] || c0[0] + hx + 1 < bins[0]) && gr * gr + gyz <= rl2f;
-                    const int xa_ = hx + (left ? -1 : 0), xb_ = hx + (right ? 1 : 0);
-                    const int b = ((hz - blo[2]) * X[1] + (hy - blo[1])) * X[0] + (xa_ - blo[0]);
-                    const int u0 = bpre[b >> 5] + __popc(box[b >> 5] & ((1u << (b & 31)) - 1u));
-                    const int u1 = u0 + (xb_ - xa_);
-                    v = (uint32_t)ustart[u0] | ((uint32_t)ustart[u1 + 1] << 16);
-                    hwv = sqrtf(fmaxf(rl2f - gyz, 0.f)) + xmargin;
-                }
-            }
-            plan.run[pr + rr] = v;
-            plan.hw[pr + rr] = hwv;
-        }
         // One image per halo entry (the one nearest row 0, taken by the force
         // pass at every step) is every row's minimum image while, per
         // periodic axis, spread + r_list + 2 r_buff < L/2: until the next
@@ -1109,23 +898,27 @@ __device__ __forceinline__ void plan_tiles(
         // and the partner image nearest the row is within L/2 of row 0 (the
         // rows' FP32 offsets get a margin of 1e-5 L).  Otherwise the force
         // pass takes the minimum image per pair.
+        const double rbuff = 2.0 * sqrt(S.disp2);
         int pp = 0;
-        {
-            const double rlist = sqrt(rl2), rbuff = 2.0 * sqrt(S.disp2);
-            for (int a = 0; a < 3; ++a)
-                if (per[a] && (double)spread[a] + rlist + 2.0 * rbuff + 1e-5 * Ls[a] >= 0.5 * Ls[a]) pp = 1;
+#pragma unroll
+        for (int a = 0; a < 3; ++a)
+            if (per[a] && (double)spread[a] + rl + 2.0 * rbuff + 1e-5 * Ls[a] >= 0.5 * Ls[a]) pp = 1;
+        if (lane == 0) {
+            pt->nu = nu;
+            pt->nseg = nseg;
+            pt->pp = pp;
+            pt->band = band;
+            pt->lo = near_lo;
+            pt->hi = near_hi;
+            pt->row = (int32_t)(row0 + r0);
+            pt->nrows = n_local - r0 < kTile ? n_local - r0 : kTile;
+            pt->keep2 = keep2;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                pt->half[a] = half[a];
+                pt->ref[a] = ref[a];
+            }
         }
-        // relative band around r_list^2 inside which the FP32 distance of a
-        // candidate cannot decide the test: a bound on the FP32 rounding of
-        // frame coordinates up to E in magnitude (cell-relative position,
-        // cell corner, their sum, the row's position: |error| <= 2^-24 (4E +
-        // |dx|) per separation), propagated through r^2 and doubled
-        const double Ef = (double)fext + (double)fmaxf(cw[0], fmaxf(cw[1], cw[2]));
-        const double rl = sqrt(rl2);
-        const double eta = 0x1p-24 * (4.0 * Ef + 1.01 * rl);
-        const double dr2 = 2.0 * sqrt(3.0) * rl * eta + 3.0 * eta * eta + 3.0 * 0x1p-24 * rl2 * 1.01;
-        const float band = (float)(2.0 * (dr2 / rl2 + 3.0 * 0x1p-24));
-        if (lane == 0) plan.hdr[tile] = make_int4(nu, nslot, pp, __float_as_int(band));
     }
 }
 
@@ -1138,8 +931,8 @@ __global__ __launch_bounds__(kWave) void k_cells_and_plan(
     const int32_t *__restrict__ tprefix, int tiles,
     const double4 *__restrict__ pos, int64_t n_cells, const int32_t *__restrict__ cell_count,
     int32_t *__restrict__ cell_size, int32_t *__restrict__ cell_idx, float4 *__restrict__ cell_xf, int cell_cap,
-    double4 *__restrict__ xbuild, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n, PlanPtrs plan,
-    const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *__restrict__ halo_n,
+    double4 *__restrict__ xbuild, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
+    char *__restrict__ plan, int64_t stride, const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *__restrict__ halo_n,
     int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
 {
     if (*flag == 0) return;
@@ -1147,9 +940,8 @@ __global__ __launch_bounds__(kWave) void k_cells_and_plan(
         cell_sort_waves<CPL>(blockIdx.x, n_sort, sys, cprefix, n_sys, pos, n_cells, cell_count, cell_size, cell_idx,
                              cell_xf, cell_cap, sflag);
     } else {
-        __shared__ PlanShared ps;
-        plan_tiles(ps, (int)blockIdx.x - n_sort, (int)gridDim.x - n_sort, sys, tprefix, n_sys, tiles, pos,
-                   cell_count, cell_cap, xbuild, slow_list, slow_n, plan, sflag, halo_n, halo_lds, rare_list, rare_n);
+        plan_tiles((int)blockIdx.x - n_sort, (int)gridDim.x - n_sort, sys, tprefix, n_sys, tiles, pos,
+                   cell_count, cell_cap, xbuild, slow_list, slow_n, plan, stride, sflag, halo_n, halo_lds, rare_list, rare_n);
     }
 }
 
@@ -1162,41 +954,62 @@ __global__ void k_zero_counts(int32_t *__restrict__ cell_count, int64_t n_cells,
         cell_count[c] = 0;
 }
 
-// One tile index from a die's counter, by one lane.  The pointer gets a zero
-// from a vector register that the compiler cannot see through: taken as
-// divergent, the atomic is issued plainly and its result waited for where it
-// is used (the pass that merges the atomics of a wave into one would wait
-// for it at once).
-__device__ __forceinline__ int take_tile(int32_t *ctr)
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+// The masks of the four row groups (16 rows each), one word per group and
+// lane, turned so that lane t holds row t's words, one per result group:
+// register index and group of 16 lanes change places.
+__device__ __forceinline__ void turn_masks(uint32_t (&m)[4])
 {
-    int zero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
-    return atomicAdd(ctr + zero, 1);
+    auto p = __builtin_amdgcn_permlane32_swap(m[0], m[2], false, false);
+    auto q = __builtin_amdgcn_permlane32_swap(m[1], m[3], false, false);
+    auto r = __builtin_amdgcn_permlane16_swap(p[0], q[0], false, false);
+    auto s = __builtin_amdgcn_permlane16_swap(p[1], q[1], false, false);
+    m[0] = r[0];
+    m[1] = r[1];
+    m[2] = s[0];
+    m[3] = s[1];
 }
 
-// A plan header read through the vector memory path: the index gets a zero
-// from a vector register that the compiler cannot see through, so the read is
-// not made a scalar one (a pending scalar read would be waited for at the
-// next LDS barrier).
-__device__ __forceinline__ int4 next_header(const int4 *hdr, int tile)
+__device__ __forceinline__ uint32_t wave_or(uint32_t v)
 {
-    int zero;
-    asm volatile("v_mov_b32 %0, 0" : "=v"(zero));
-    return hdr[tile + zero];
+    v |= (uint32_t)dpp_mov<0xB1>((int)v);
+    v |= (uint32_t)dpp_mov<0x4E>((int)v);
+    v |= (uint32_t)dpp_mov<0x141>((int)v);
+    v |= (uint32_t)dpp_mov<0x140>((int)v);
+    return (uint32_t)(__builtin_amdgcn_readlane((int)v, 0) | __builtin_amdgcn_readlane((int)v, 16) |
+                      __builtin_amdgcn_readlane((int)v, 32) | __builtin_amdgcn_readlane((int)v, 48));
 }
 
-// NT threads per workgroup (NT / 64 waves share a tile); LPR lanes scan one
-// row: 64 (a wave per row) or 32 (two rows per wave).
+// Slot of a partner tag in a tile's table (kExSlots of them).
+__device__ __forceinline__ uint32_t ex_slot(int32_t t) { return ((uint32_t)t * 2654435761u) >> 23; }
+static_assert(kExSlots == 1 << 9, "ex_slot");
+
+// NT threads per workgroup: its waves share a tile, each with members of its
+// own, which it reads, packs and takes the distances of without waiting for
+// the others; up to 16 LPR / kWaves of them at a time.  The waves meet three
+// times per tile: when the hits are known (halo numbering needs all of them),
+// when the rows are together in LDS, and when they have been read out.
+//
+// Vector instructions bound it: about 10,000 per tile for an LJ liquid (1,140
+// members kept, 628 of them in the halo), a fifth of them the 75 blocks of
+// matrix results (30 each beside four matrix instructions), the others
+// staging (45 per 64 places), the expansion of the masks and the fixed work
+// of each wave; the matrix units are a quarter busy.  Built and sorted LJ
+// liquid of 2,000,000 rows: 1.02 ms (scan of x-cut lines, a wave per row:
+// 1.70 ms; 17,900 instructions per tile).  Four waves a tile and 36 KB leave
+// four tiles per CU; eight waves a tile, two per CU, took 0.5 ms more with
+// the same code, because the fixed work is done twice as often and two tiles
+// hide less of the reads' latency.
 template <bool EXCL, int NT, int LPR>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_build_fast(
     const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
     const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
-    const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx,
-    const float4 *__restrict__ cell_xf, int cell_cap,
+    int bond_stride, const float4 *__restrict__ cell_xf,
     uint16_t *__restrict__ nlist, int32_t *__restrict__ nn, int cap, int rstride,
-    int32_t *__restrict__ halo, int32_t *__restrict__ halo_n, int halo_cap, PlanPtrs plan,
-    int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, int32_t *__restrict__ tile_ctr,
-    int32_t *__restrict__ cell_count, int64_t n_cells,
+    int32_t *__restrict__ halo, int32_t *__restrict__ halo_n, int halo_cap, const char *__restrict__ plan,
+    int64_t plan_stride, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n,
+    int32_t *__restrict__ tile_ctr, int32_t *__restrict__ cell_count, int64_t n_cells,
     const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *build_count, Status *st)
 {
     if (*flag == 0) return;
@@ -1204,604 +1017,417 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // for the next build
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += (int64_t)gridDim.x * blockDim.x)
         cell_count[c] = 0;
-    __shared__ FastShared sh;
-    extern __shared__ uint16_t srows[];  // [kTile][rstride]: staged slot of each hit
-    const int tid = threadIdx.x;
-    const int lane = lane_id();
-    const int wv = tid >> 6;
-    constexpr int kWaves = NT / kWave;
-    static_assert(kWaves >= 2 && kWaves <= kFastWavesMax, "a loader wave and at least one more");
-    static_assert(LPR == 32 || LPR == 64, "a row per wave or per half wave");
+    using Sh = FastShared<NT, LPR>;
+    constexpr int kWaves = Sh::kWaves, kC = Sh::kC, kCw = Sh::kCw, kWords = Sh::kWords, kA = build_astride(kC);
+    constexpr int kRounds = 5;                     // staging reads of a lane in flight
+    constexpr int kSegWave = kWave / kSeg;         // segments a wave stages at once
+    static_assert(kWords * kWaves * 4 <= kWave, "one-wave scan of the marks");
+    __shared__ Sh sh;
+    __shared__ typename std::conditional<EXCL, ExShared<NT>, char>::type ex;
+    // the staged positions, then (all distances taken) the rows' halo indices
+    // [kTile][rstride]
+    extern __shared__ float lds_a[];
+    uint16_t *const srows = reinterpret_cast<uint16_t *>(lds_a);
+    int tid = threadIdx.x;
+    const int wv = uni(tid >> 6);
     if (blockIdx.x == 0 && tid == 0) atomicAdd(build_count, 1);
 
     // Each die's workgroups walk one contiguous run of tiles.  With one
     // system every tile of the run is built, and the tiles are handed out one
     // at a time from the die's counter (cleared by the binning launch): a
     // workgroup that meets costly tiles takes fewer, so the launch ends with
-    // its run.  The loader wave (which makes no global writes, so its wait
-    // for the count waits for no write) takes the tile after next as a tile
-    // starts.  A batch rebuilds only some systems, and a count for every tile
-    // it skips would cost more than it balances: there the workgroups of a
-    // die take every step-th tile of the run, and skip without a barrier.
+    // its run.  One lane takes the tile after next as a tile starts.  A batch
+    // rebuilds only some systems, and a count for every tile it skips would
+    // cost more than it balances: there the workgroups of a die take every
+    // step-th tile of the run that is rebuilt.
     const bool dyn = n_sys == 1;
     const int D = (int)gridDim.x < kDies ? (int)gridDim.x : kDies;
     const int die = (int)blockIdx.x % D;
-    int64_t tfirst, tend;
+    int64_t first_, end_;
     int tstep;
-    die_range(blockIdx.x, gridDim.x, tiles, tfirst, tend, tstep);
-    const int64_t dfirst = (int64_t)tiles * die / D;
+    die_range(blockIdx.x, gridDim.x, tiles, first_, end_, tstep);
+    const int tend = (int)end_;
+    const int dfirst = (int)((int64_t)tiles * die / D);
     int32_t *ctr = tile_ctr + die * kTileCtrStride;
+    auto rebuilt_from = [&](int t) -> int {
+        while (t < tend && !sflag[find_sys(tprefix, n_sys, t)]) t += tstep;
+        return t;
+    };
     int grabbed = 0;
-    int64_t t_next = tfirst;
+    int t_cur, t_next;
     if (dyn) {
         if (tid == kWave) {
             sh.grab[0] = take_tile(ctr);
-            grabbed = take_tile(ctr);
+            sh.grab[1] = take_tile(ctr);
         }
         lds_barrier();
-        t_next = dfirst + sh.grab[0];
+        t_cur = dfirst + uni(sh.grab[0]);
+        t_next = dfirst + uni(sh.grab[1]);
+    } else {
+        t_cur = rebuilt_from((int)first_);
+        t_next = rebuilt_from(t_cur + tstep);
     }
-    int par = 0;
-    // each tile's plan header is read one tile ahead, by every thread, with
-    // no branch, so that the read stays in flight until its use
-    int4 hd_next = next_header(plan.hdr, t_next < tend ? (int)t_next : 0);
-    bool built = false;  // a tile was built since the last barrier (its LDS may still be read)
-    for (;;) {
-        if (dyn) {
-            // the next tile's index, taken during the last tile
-            par ^= 1;
-            if (tid == kWave) sh.grab[par] = grabbed;
-        }
-        if (dyn || built) lds_barrier();  // LDS of the previous tile no longer read; the index published
-        built = false;
-        const int64_t t_cur = t_next;
-        t_next = dyn ? dfirst + sh.grab[par] : t_cur + tstep;
-        if (t_cur >= tend) break;
-        if (dyn && tid == kWave) grabbed = take_tile(ctr);  // the tile after next
-        const int tile = (int)t_cur;
-        const int4 hd_tile = hd_next;
-        hd_next = next_header(plan.hdr, t_next < tend ? (int)t_next : tile);
-        const int s = find_sys(tprefix, n_sys, tile);
-        if (!sflag[s]) continue;  // a system that keeps its list
-        built = true;
-        const SysDev &S = sys[s];
-        const double Ls[3] = {S.L[0], S.L[1], S.L[2]};
-        const double iL[3] = {S.invL[0], S.invL[1], S.invL[2]};
-        const int bins[3] = {S.bins[0], S.bins[1], S.bins[2]};
-        const int per[3] = {S.per[0], S.per[1], S.per[2]};
-        const int64_t row0 = S.row0, nl0 = S.nl0;
-        const int n_local = S.n_local;
-        const double rl2 = S.rl2;
-        const int r0 = (tile - S.tile0) * kTile;
+    if (t_cur >= tend) return;
 
-        // ---- 1. the tile's plan ------------------------------------------------
-        // Wave 1 does this tile's global reads and no global writes: a wave's
-        // wait for a read also waits for all of its earlier writes, and the
-        // other waves still have the previous tile's rows in flight.
-        const bool loader = wv == 1;
-        const int tr = tid - kWave;  // lane of the loader wave
-        if (loader) {
-            const int4 hd = hd_tile;
-            if (tr == 0) {
-                sh.info[0] = hd.x;
-                sh.info[1] = hd.z;
-                sh.info[3] = hd.y;
-                sh.info[4] = hd.w;
+    // a tile's plan: the header's first words, and this lane's segments of
+    // kRounds rounds from r0 on (read whether they are there or not)
+    float4 head[3], sg[kRounds];
+    auto plan_of = [&](int t) { return reinterpret_cast<const PlanTile *>(plan + t * plan_stride); };
+    auto read_segments = [&](int t, int r0) {
+        const float4 *p = plan_of(t)->seg + (r0 * kWaves + wv) * kSegWave + (tid & (kWave - 1)) / kSeg;
+#pragma unroll
+        for (int k = 0; k < kRounds; ++k) sg[k] = p[k * kWaves * kSegWave];
+    };
+    auto read_head = [&](int t) {
+        const float4 *p = reinterpret_cast<const float4 *>(plan_of(t));
+#pragma unroll
+        for (int k = 0; k < 3; ++k) head[k] = p[k];
+    };
+    // the partner tags of a tile's rows into its table (free slots hold -1;
+    // half of the slots at most are ever taken), by one wave
+    auto insert_partners = [&](int t) {
+        if constexpr (EXCL) {
+            if (wv != 0) return;
+            for (int k = tid; k < kExSlots; k += kWave) ex.tag[k] = -1;
+            const PlanTile *P = plan_of(t);
+            if (tid >= P->nrows) return;
+            const int64_t pr = (int64_t)(P->row + tid) * bond_stride;
+            for (int b = 0; b < bond_stride; ++b) {
+                const int32_t v = ptag[pr + b];
+                if (v < 0) continue;
+                uint32_t k = ex_slot(v);
+                while (atomicCAS(&ex.tag[k], -1, v) != -1) k = (k + 1) & (kExSlots - 1);
+                ex.row[k] = (uint8_t)tid;
             }
-            if (hd.x > 0) {
-                const int nu_ = hd.x < kUMax ? hd.x : kUMax;
-                const int64_t pu = (int64_t)tile * kUMax, pr = (int64_t)tile * kTile * kRuns;
-                // every read issued before the first is used: cells past the
-                // end read the last one again
-                int2 cs[kUMax / kWave];
-                float4 os[kUMax / kWave];
-                uint32_t rv[kRuns];
-                float hv[kRuns];
-#pragma unroll
-                for (int k = 0; k < kUMax / kWave; ++k) {
-                    const int u = tr + k * kWave;
-                    cs[k] = plan.cell[pu + (u < nu_ ? u : nu_ - 1)];
-                    os[k] = plan.off[pu + (u < nu_ ? u : nu_ - 1)];
-                }
-#pragma unroll
-                for (int k = 0; k < kRuns; ++k) {
-                    rv[k] = plan.run[pr + tr + k * kWave];
-                    hv[k] = plan.hw[pr + tr + k * kWave];
-                }
-                const float4 xw = plan.xrow[(int64_t)tile * kTile + tr];
-                const double4 x0 = pos[row0 + r0];
-#pragma unroll
-                for (int k = 0; k < kUMax / kWave; ++k) {
-                    const int u = tr + k * kWave;
-                    if (u < nu_) {
-                        sh.ucell[u] = cs[k].x;
-                        sh.ustart[u] = cs[k].y;
-                        sh.uoff[u] = os[k];
-                    }
-                }
-#pragma unroll
-                for (int k = 0; k < kRuns; ++k) {
-                    const int e = tr + k * kWave;
-                    sh.run[e / kRuns][e % kRuns] = rv[k];
-                    sh.hw[e / kRuns][e % kRuns] = hv[k];
-                }
-                sh.xrow[tr] = xw;
-                if (tr == 0) {
-                    sh.ustart[nu_] = hd.y;
-                    sh.xref[0] = x0.x;
-                    sh.xref[1] = x0.y;
-                    sh.xref[2] = x0.z;
-                }
-            }
-        } else if (wv == 0) {
-            sh.rown[tid] = r0 + tid < n_local ? 0 : -1;
         }
+    };
+    read_head(t_cur);
+    read_segments(t_cur, 0);
+    if constexpr (EXCL) {
+        insert_partners(t_cur);
         lds_barrier();
-        const int nu = uni(sh.info[0]);
-        const int nslot = uni(sh.info[3]);
-        if (nu <= 0 || nu > kUMax || nslot > kFastSlotMax) continue;  // built by the general kernel
-        const double xr[3] = {uni(sh.xref[0]), uni(sh.xref[1]), uni(sh.xref[2])};
-        for (int q = tid; q < (nslot + 31) / 32; q += NT) sh.used[q] = 0u;
-        // ---- 5. stage members a chunk at a time, scan every row's lines -------------
-        const bool one_chunk = nslot <= kFastChunk;
-        // FP32 distances below lo_f are hits, above hi_f misses, in between
-        // the exact FP64 test decides (the band comes with the tile's plan)
-        const double band = (double)__int_as_float(uni(sh.info[4]));
-        const float lo_f = (float)(rl2 * (1.0 - band)), hi_f = (float)(rl2 * (1.0 + band));
-        for (int q0 = 0; q0 < nslot; q0 += kFastChunk) {
-            const int q1 = q0 + kFastChunk < nslot ? q0 + kFastChunk : nslot;
-            lds_barrier();
-            // slot -> distinct cell of the chunk: each cell writes its index
-            // over its own slots
-            for (int u = tid; u < nu; u += NT) {
-                int qa = sh.ustart[u], qb = sh.ustart[u + 1];
-                qa = qa > q0 ? qa : q0;
-                qb = qb < q1 ? qb : q1;
-                for (int q = qa; q < qb; ++q) sh.smap[q - q0] = (uint8_t)u;
-            }
-            lds_barrier();
-            // staging: one coalesced read per member (cell-relative FP32
-            // position and row), moved into the frame by its cell's corner;
-            // four reads of a thread in flight at once
-            {
-                constexpr int kB = 4;
-                for (int qb = q0 + tid; qb < q1; qb += kB * NT) {
-                    int us[kB], qs[kB];
-                    float4 cs[kB];
+    }
+
+    for (;;) {
+        // what follows from the thread's number is worked out anew for each
+        // tile: kept across the loop, its many addresses would take the
+        // registers of resident waves
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & (kWave - 1);
+        const int tile = t_cur;
+        const bool more = t_next < tend;
+        if (dyn && tid == kWave) grabbed = take_tile(ctr);  // the tile after next
+        const int nu = uni(__float_as_int(head[0].x)), nseg = uni(__float_as_int(head[0].y)),
+                  pp = uni(__float_as_int(head[0].z));
+        const float band = uni(head[0].w);
+        const float hx = uni(head[1].x), hy = uni(head[1].y), hz = uni(head[1].z), keep2 = uni(head[1].w);
+        const int rbase = uni(__float_as_int(head[2].x)), nrows = uni(__float_as_int(head[2].y));
+        const int rounds = (nseg + kWaves * kSegWave - 1) / (kWaves * kSegWave);
+        const int base = wv * kCw;  // this wave's staged members
+
+        int ntot = 0;   // this lane's row: hits so far (the same in every wave)
+        int hbase = 0;  // halo entries so far
+        bool whole;     // one pass takes all members: the rows are put together in LDS
+        int r = 0;      // rounds staged
+        for (int pass = 0;; ++pass) {
+            // ---- 1. stage: read, keep what is near the rows, pack ---------------
+            sh.selfq[wv][lane] = 0xFFFF;
+            if constexpr (EXCL) ex.n[wv][lane] = 0;
+            int n = 0;
+            bool full = false;
+            while (r < rounds && !full) {
+                if (r > 0) read_segments(tile, r);
+                float4 mem[kRounds];
 #pragma unroll
-                    for (int k = 0; k < kB; ++k) {
-                        const int q = qb + k * NT;
-                        qs[k] = q;
-                        us[k] = q < q1 ? (int)sh.smap[q - q0] : 0;
-                    }
+                for (int k = 0; k < kRounds; ++k) {
+                    const bool in = ((r + k) * kWaves + wv) * kSegWave + lane / kSeg < nseg;
+                    mem[k] = cell_xf[(int64_t)(in ? __float_as_int(sg[k].w) : 0) * kSeg + (lane & (kSeg - 1))];
+                }
+                const int r1 = r;
 #pragma unroll
-                    for (int k = 0; k < kB; ++k)
-                        if (qs[k] < q1) cs[k] = cell_xf[(int64_t)sh.ucell[us[k]] * cell_cap + (qs[k] - sh.ustart[us[k]])];
-#pragma unroll
-                    for (int k = 0; k < kB; ++k) {
-                        const int q = qb + k * NT;
-                        if (q < q1) {
-                            const float4 o = sh.uoff[us[k]];
-                            sh.cp[q - q0] = make_float4(cs[k].x + o.x, cs[k].y + o.y, cs[k].z + o.z, cs[k].w);
-                        }
-                    }
-                }
-            }
-            lds_barrier();
-            // members of a line are ordered by x (cells in x order, each sorted
-            // by x): cut every line, within this chunk, to the slots within the
-            // half width that its y-z distance leaves (|dx|^2 <= r_list^2 - gap^2,
-            // widened by a margin for the FP32 frame coordinates)
-            for (int e = tid; e < kTile * kRuns; e += NT) {
-                const int t = e / kRuns, rr = e - kRuns * (e / kRuns);
-                const uint32_t v = sh.run[t][rr];
-                int a = (int)(v & 0xffffu), b = (int)(v >> 16);
-                a = a > q0 ? a : q0;
-                b = b < q1 ? b : q1;
-                if (b <= a) {
-                    sh.runc[t][rr] = 0u;
-                    continue;
-                }
-                const float hw = sh.hw[t][rr];
-                const float xc = sh.xrow[t].x;
-                const float tlo = xc - hw, thi = xc + hw;
-                // first slot with x >= tlo, first slot with x > thi
-                int pa = a, pb = a;
-                int step = 1;
-                while (2 * step <= b - a) step *= 2;
-                for (; step > 0; step >>= 1) {
-                    if (pa + step <= b && sh.cp[pa + step - 1 - q0].x < tlo) pa += step;
-                    if (pb + step <= b && sh.cp[pb + step - 1 - q0].x <= thi) pb += step;
-                }
-                sh.runc[t][rr] = (uint32_t)pa | ((uint32_t)(pb > pa ? pb : pa) << 16);
-            }
-            lds_barrier();
-            if constexpr (LPR == 64) {
-                // lanes to lines, one thread per row: line r takes lanes [B_r, B_r+1)
-                // with B_r = r + about 55 P_r / T (P_r the members of the row's lines
-                // before line r in this chunk, T all of them), so every line keeps at
-                // least one lane and longer lines get more.  Kept as the first lanes
-                // and a mask with the last lane of every line but the last.
-                if (tid < kTile) {
-                    int lens[kRuns];
-                    int tot = 0;
-    #pragma unroll
-                    for (int r = 0; r < kRuns; ++r) {
-                        const uint32_t rv = sh.runc[tid][r];
-                        const int x0_ = (int)(rv & 0xffffu), x1_ = (int)(rv >> 16);
-                        lens[r] = x1_ > x0_ ? x1_ - x0_ : 0;
-                        tot += lens[r];
-                    }
-                    const uint32_t inv = tot > 0 ? 65536u / (uint32_t)tot : 0u;  // floor(2^16 / T)
-                    uint64_t mask = 0;
-                    int pre = 0, b0 = 0;
-    #pragma unroll
-                    for (int r = 0; r < kRuns; ++r) {
-                        const int pn = pre + lens[r];
-                        const int b1 = r == kRuns - 1 ? kWave : r + 1 + (int)((55u * (uint32_t)pn * inv) >> 16);
-                        sh.lb[tid][r] = (uint8_t)b0;
-                        if (r < kRuns - 1) mask |= 1ull << (b1 - 1);
-                        b0 = b1;
-                        pre = pn;
-                    }
-                    sh.lb[tid][kRuns] = (uint8_t)kWave;
-                    sh.lmask[tid] = tot > 0 ? mask : 0ull;
-                    if (tot == 0 && sh.rown[tid] >= 0) sh.lb[tid][0] = 0xFF;  // nothing to scan in this chunk
-                }
-                lds_barrier();
-                for (int t = wv; t < kTile; t += kWaves) {
-                    int ntot = uni(sh.rown[t]);
-                    if (ntot < 0) continue;  // inactive row
-                    if (uni((int)sh.lb[t][0]) == 0xFF) continue;  // no members in this chunk
-                    // this lane's line: the lines that end before it; its lanes,
-                    // members (cut to the chunk) and stride
-                    const uint64_t lm = sh.lmask[t];
-                    int myline = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(lm >> 32),
-                                                                __builtin_amdgcn_mbcnt_lo((uint32_t)lm, 0u));
-                    myline = myline < kRuns - 1 ? myline : kRuns - 1;
-                    const int blo_ = sh.lb[t][myline], bhi_ = sh.lb[t][myline + 1];
-                    const uint32_t rv = sh.runc[t][myline];
-                    const int x0_ = (int)(rv & 0xffffu), x1_ = (int)(rv >> 16);
-                    const int gsz = bhi_ - blo_ > 1 ? bhi_ - blo_ : 1;
-                    const int base = x0_ + (lane - blo_);
-                    const int end = x1_;
-                    const float4 xt0 = sh.xrow[t];
-                    const float4 xt = make_float4(uni(xt0.x), uni(xt0.y), uni(xt0.z), 0.f);
-                    const int32_t it = (int32_t)(row0 + r0 + t);
-                    int32_t part[kMaxBondCap];
-                    if constexpr (EXCL) {
-                        const int64_t prow = (int64_t)it * S.bond_stride;
-    #pragma unroll
-                        for (int bnd = 0; bnd < kMaxBondCap; ++bnd)
-                            part[bnd] = bnd < S.bond_cap ? ptag[prow + bnd] : -1;
-                    }
-                    uint16_t *myrow = srows + t * rstride;
-                    // exact FP64 decision of a candidate whose FP32 distance is
-                    // within the band around r_list
-                    auto exact = [&](const float4 c) -> bool {
-                        const int32_t j = __float_as_int(c.w);
-                        const double4 xa = pos[it], xb = pos[j];
-                        const double cj[3] = {(double)c.x, (double)c.y, (double)c.z};
-                        const double xt3[3] = {(double)xt.x, (double)xt.y, (double)xt.z};
-                        const double pa[3] = {xa.x, xa.y, xa.z}, pb[3] = {xb.x, xb.y, xb.z};
-                        double d[3];
-    #pragma unroll
-                        for (int ax = 0; ax < 3; ++ax) {
-                            // frame images of both: k = round((frame - stored) / L)
-                            const double kj = rint((cj[ax] + xr[ax] - pb[ax]) * iL[ax]);
-                            const double ki = rint((xt3[ax] + xr[ax] - pa[ax]) * iL[ax]);
-                            d[ax] = pb[ax] - pa[ax];
-                            if (kj != ki) d[ax] = d[ax] + (kj - ki) * Ls[ax];
-                        }
-                        return norm2_exact(d[0], d[1], d[2]) < rl2 && j != it;
-                    };
-                    auto excluded = [&](bool hit, const float4 c) -> bool {
+                for (int k = 0; k < kRounds; ++k) {
+                    full = full || n + kWave > kCw;
+                    if (full || r1 + k >= rounds) continue;
+                    ++r;
+                    const bool in = ((r1 + k) * kWaves + wv) * kSegWave + lane / kSeg < nseg;
+                    const float x = mem[k].x + sg[k].x, y = mem[k].y + sg[k].y, z = mem[k].z + sg[k].z;
+                    // distance from the rows' box; what is no number (a place
+                    // without a member) stays so and is not kept
+                    float gx = fabsf(x) - hx, gy = fabsf(y) - hy, gz = fabsf(z) - hz;
+                    gx = gx <= 0.f ? 0.f : gx;
+                    gy = gy <= 0.f ? 0.f : gy;
+                    gz = gz <= 0.f ? 0.f : gz;
+                    const bool keep = in && gx * gx + gy * gy + gz * gz <= keep2;
+                    const uint64_t kb = __ballot(keep);
+                    if (keep) {
+                        const int q = n + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kb >> 32),
+                                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)kb, 0u));
+                        const int32_t j = __float_as_int(mem[k].w);
+                        float *w = lds_a + base + q;
+                        w[0] = x;
+                        w[kA] = y;
+                        w[2 * kA] = z;
+                        w[3 * kA] = x * x + y * y + z * z;
+                        sh.cj[base + q] = j;
+                        const uint32_t t = (uint32_t)(j - rbase);
+                        if (t < (uint32_t)kTile) sh.selfq[wv][t] = (uint16_t)q;
                         if constexpr (EXCL) {
-                            if (hit) {
-                                const int32_t tj = tag[__float_as_int(c.w)];
-    #pragma unroll
-                                for (int bnd = 0; bnd < kMaxBondCap; ++bnd) hit = hit && part[bnd] != tj;
+                            // rows that this member is a partner of
+                            const int32_t tj = tag[j];
+                            uint32_t h = ex_slot(tj);
+                            for (int32_t v = ex.tag[h]; v != -1; v = ex.tag[h]) {
+                                if (v == tj) {
+                                    const int er = ex.row[h];
+                                    const int slot = atomicAdd(&ex.n[wv][er], 1);
+                                    if (slot < 2 * kMaxBondCap) ex.q[wv][er][slot] = (uint16_t)q;
+                                }
+                                h = (h + 1) & (kExSlots - 1);
                             }
                         }
-                        return hit;
-                    };
-                    // a hit goes to the row's next entry (entries past the
-                    // capacity land on the row's spare slot) and marks its slot
-                    auto append = [&](bool hit, uint64_t mask, int q) {
-                        if (hit) {
-                            const int p = ntot + (int)__builtin_amdgcn_mbcnt_hi(
-                                                     (uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-                            myrow[p < cap ? p : cap] = (uint16_t)q;
-                            atomicOr(&sh.used[q >> 5], 1u << (q & 31));
-                        }
-                        ntot += __popcll(mask);
-                    };
-                    // every lane reads a slot of the chunk, clamped: lanes past
-                    // their line's end take no part
-                    const float4 *cq = sh.cp - q0;
-                    const int qlast = q1 - 1;
-                    for (int qa = base;; qa += 2 * gsz) {
-                        const int qb = qa + gsz;
-                        const bool ona = qa < end, onb = qb < end;
-                        if (__ballot(ona) == 0ull) break;
-                        const float4 ca = cq[qa < qlast ? qa : qlast];
-                        const float4 cb = cq[qb < qlast ? qb : qlast];
-                        const float dxa = ca.x - xt.x, dya = ca.y - xt.y, dza = ca.z - xt.z;
-                        const float dxb = cb.x - xt.x, dyb = cb.y - xt.y, dzb = cb.z - xt.z;
-                        const float r2a = dxa * dxa + dya * dya + dza * dza;
-                        const float r2b = dxb * dxb + dyb * dyb + dzb * dzb;
-                        bool ha = ona && r2a < lo_f && __float_as_int(ca.w) != it;
-                        bool hb = onb && r2b < lo_f && __float_as_int(cb.w) != it;
-                        const bool ba = ona && r2a >= lo_f && r2a <= hi_f;
-                        const bool bb = onb && r2b >= lo_f && r2b <= hi_f;
-                        if (__builtin_expect(__ballot(ba || bb) != 0ull, 0)) {
-                            if (ba) ha = exact(ca);
-                            if (bb) hb = exact(cb);
-                        }
-                        ha = excluded(ha, ca);
-                        hb = excluded(hb, cb);
-                        const uint64_t ma = __ballot(ha), mb = __ballot(hb);
-                        append(ha, ma, qa);
-                        append(hb, mb, qb);
                     }
-                    if (lane == 0) sh.rown[t] = ntot;
+                    n += __popcll(kb);
                 }
-            } else {
-                // lanes to lines, one thread per row.  Two rows share a wave, 32
-                // lanes each, two members per lane per pass: the fewest passes P
-                // such that ceil(len / 2P) lanes for every non-empty line of the
-                // row (in this chunk) take at most 32 lanes.  Kept per row: the
-                // non-empty lines in order with their first lanes (then the lanes
-                // used), and a mask with the last lane of each line but the last.
-                if (tid < kTile) {
-                    int lens[kRuns];
-                    int tot = 0;
-    #pragma unroll
-                    for (int r = 0; r < kRuns; ++r) {
-                        const uint32_t rv = sh.runc[tid][r];
-                        const int x0_ = (int)(rv & 0xffffu), x1_ = (int)(rv >> 16);
-                        lens[r] = x1_ > x0_ ? x1_ - x0_ : 0;
-                        tot += lens[r];
-                    }
-                    // at 2P >= the longest line every non-empty line takes one
-                    // lane (at most nine), so the search ends
-                    int d = 2 * ((tot + 63) >> 6);
-                    d = d > 2 ? d : 2;
-                    for (;;) {
-                        int lanes = 0;
-    #pragma unroll
-                        for (int r = 0; r < kRuns; ++r) lanes += (lens[r] + d - 1) / d;
-                        if (lanes <= 32) break;
-                        d += 2;
-                    }
-                    uint32_t mask = 0u;
-                    int nk = 0, b0 = 0;
-    #pragma unroll
-                    for (int r = 0; r < kRuns; ++r) {
-                        if (lens[r] == 0) continue;
-                        if (nk > 0) mask |= 1u << (b0 - 1);
-                        sh.ln[tid][nk] = (uint8_t)r;
-                        sh.lb[tid][nk] = (uint8_t)b0;
-                        b0 += (lens[r] + d - 1) / d;
-                        ++nk;
-                    }
-                    sh.lb[tid][nk] = (uint8_t)b0;
-                    sh.lmask[tid] = mask;
-                    sh.nk[tid] = (uint8_t)nk;
+            }
+            // the last block's free places: far from every row
+            if (lane < 16 && n + lane < ((n + 15) & ~15)) {
+                float *w = lds_a + base + n + lane;
+                w[0] = 0.f;
+                w[kA] = 0.f;
+                w[2 * kA] = 0.f;
+                w[3 * kA] = 1e30f;
+            }
+
+            // ---- 2. distances, hit masks -------------------------------------------
+            // the matrix operands of the rows: component lane / 16 of row
+            // 16 R + lane % 16, and the accumulator's start
+            int lane_ = lane;
+            asm volatile("" : "+v"(lane_));  // (read anew for each pass, not kept)
+            const int grp = lane_ >> 4, col = lane_ & 15;
+            const float4 *xrow = plan_of(tile)->xrow;
+            float bq[4];
+            v4f cq[4];
+#pragma unroll
+            for (int R = 0; R < 4; ++R) {
+                const float4 x = xrow[16 * R + col];
+                bq[R] = grp == 0 ? -2.f * x.x : (grp == 1 ? -2.f * x.y : (grp == 2 ? -2.f * x.z : 1.f));
+                cq[R] = v4f{x.w, x.w, x.w, x.w};
+            }
+            uint32_t m[kWords][4];
+            uint32_t banded = 0u;  // blocks with a result in the band
+            const float *ap = lds_a + grp * kA + base + col;
+#pragma unroll
+            for (int wd = 0; wd < kWords; ++wd) {
+#pragma unroll
+                for (int R = 0; R < 4; ++R) m[wd][R] = 0u;
+                const int nb = (n + 15) / 16 - 8 * wd;
+                if (nb <= 0) continue;
+                // (each block's operand is read one block ahead)
+                float an = ap[128 * wd];
+#pragma unroll 1
+                for (int i = 0; i < 8 && i < nb; ++i) {
+                    const float av = an;
+                    an = ap[128 * wd + 16 * (i < 7 ? i + 1 : 7)];
+                    float mn = INFINITY;
+                    v4f d[4];
+#pragma unroll
+                    for (int R = 0; R < 4; ++R)
+                        d[R] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bq[R], cq[R], 0, 0, 0);
+#pragma unroll
+                    for (int R = 0; R < 4; ++R)
+#pragma unroll
+                        for (int r_ = 0; r_ < 4; r_ += 2)
+                            mn = fminf(fminf(fabsf(d[R][r_]), fabsf(d[R][r_ + 1])), mn);
+                    banded |= __ballot(mn <= band) != 0ull ? 1u << (8 * wd + i) : 0u;
+#pragma unroll
+                    for (int R = 0; R < 4; ++R)
+#pragma unroll
+                        for (int r_ = 0; r_ < 4; ++r_)
+                            m[wd][R] = __builtin_amdgcn_alignbit(m[wd][R], __float_as_uint(d[R][r_]), 31);
                 }
-                lds_barrier();
-                // rows t0 (lanes 0-31) and t0 + 1 (lanes 32-63) of each wave
-                const int hh = lane >> 5, hl = lane & 31;
-                const float4 *cq = sh.cp - q0;
-                const int qlast = q1 - 1;
-                for (int t0 = 2 * wv; t0 < kTile; t0 += 2 * kWaves) {
-                    const int t = t0 + hh;
-                    const int nk = sh.nk[t];
-                    int ntot = sh.rown[t];
-                    const bool row_on = ntot >= 0 && nk > 0;  // an active row with members in this chunk
-                    if (__ballot(row_on) == 0ull) continue;
-                    // this lane's line: the lines that end before it; its lanes,
-                    // members (cut to the chunk) and stride.  Lanes without a line
-                    // start at the chunk's first slot with nothing to scan.
-                    int base = q0, end = q0, gsz = 1;
-                    if (row_on) {
-                        const int used_lanes = sh.lb[t][nk];
-                        if (hl < used_lanes) {
-                            int k = __popc(sh.lmask[t] & ((1u << hl) - 1u));
-                            k = k < nk - 1 ? k : nk - 1;
-                            const int r = sh.ln[t][k];
-                            const int blo_ = sh.lb[t][k], bhi_ = sh.lb[t][k + 1];
-                            const uint32_t rv = sh.runc[t][r];
-                            gsz = bhi_ - blo_;
-                            base = (int)(rv & 0xffffu) + (hl - blo_);
-                            end = (int)(rv >> 16);
-                        }
-                    }
-                    const float4 xt = sh.xrow[t];
-                    const int32_t it = (int32_t)(row0 + r0 + t);
-                    int32_t part[kMaxBondCap];
-                    if constexpr (EXCL) {
-    #pragma unroll
-                        for (int bnd = 0; bnd < kMaxBondCap; ++bnd) part[bnd] = -1;
-                        if (row_on) {
-                            const int64_t prow = (int64_t)it * S.bond_stride;
-    #pragma unroll
-                            for (int bnd = 0; bnd < kMaxBondCap; ++bnd)
-                                part[bnd] = bnd < S.bond_cap ? ptag[prow + bnd] : -1;
-                        }
-                    }
-                    uint16_t *myrow = srows + t * rstride;
-                    // exact FP64 decision of a candidate whose FP32 distance is
-                    // within the band around r_list
-                    auto exact = [&](const float4 c) -> bool {
-                        const int32_t j = __float_as_int(c.w);
-                        const double4 xa = pos[it], xb = pos[j];
-                        const double cj[3] = {(double)c.x, (double)c.y, (double)c.z};
-                        const double xt3[3] = {(double)xt.x, (double)xt.y, (double)xt.z};
-                        const double pa[3] = {xa.x, xa.y, xa.z}, pb[3] = {xb.x, xb.y, xb.z};
-                        double d[3];
-    #pragma unroll
-                        for (int ax = 0; ax < 3; ++ax) {
-                            // frame images of both: k = round((frame - stored) / L)
-                            const double kj = rint((cj[ax] + xr[ax] - pb[ax]) * iL[ax]);
-                            const double ki = rint((xt3[ax] + xr[ax] - pa[ax]) * iL[ax]);
-                            d[ax] = pb[ax] - pa[ax];
-                            if (kj != ki) d[ax] = d[ax] + (kj - ki) * Ls[ax];
-                        }
-                        return norm2_exact(d[0], d[1], d[2]) < rl2 && j != it;
-                    };
-                    auto excluded = [&](bool hit, const float4 c) -> bool {
-                        if constexpr (EXCL) {
-                            if (hit) {
-                                const int32_t tj = tag[__float_as_int(c.w)];
-    #pragma unroll
-                                for (int bnd = 0; bnd < kMaxBondCap; ++bnd) hit = hit && part[bnd] != tj;
+            }
+            // blocks in word wd of this wave
+            auto blocks = [&](int wd) -> int {
+                const int nb = (n + 15) / 16 - 8 * wd;
+                return nb < 8 ? nb : 8;
+            };
+            if (__builtin_expect(banded != 0u, 0)) {
+                // the blocks with a result in the band once more: there the
+                // FP32 difference decides what it can, else the FP64 test
+                const PlanTile *P = plan_of(tile);
+                const float lo = P->lo, hi = P->hi;
+                for (; banded; banded &= banded - 1u) {
+                    const int i = __ffs((int)banded) - 1;
+                    const float av = ap[16 * i];
+#pragma unroll
+                    for (int R = 0; R < 4; ++R) {
+                        const v4f d = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bq[R], cq[R], 0, 0, 0);
+                        uint32_t open = 0u;
+#pragma unroll
+                        for (int r_ = 0; r_ < 4; ++r_) open |= fabsf(d[r_]) <= band ? 8u >> r_ : 0u;
+                        if (__ballot(open != 0u) == 0ull) continue;
+                        uint32_t hit = 0u;
+#pragma unroll 1
+                        for (uint32_t w = open; w; w &= w - 1u) {
+                            const int q = 16 * i + 4 * grp + 4 - __ffs((int)w);
+                            const float4 xt = xrow[16 * R + col];
+                            const float *ac = lds_a + base + q;
+                            const float ax = ac[0], ay = ac[kA], az = ac[2 * kA];
+                            const float ex_ = ax - xt.x, ey_ = ay - xt.y, ez_ = az - xt.z;
+                            const float r2 = ex_ * ex_ + ey_ * ey_ + ez_ * ez_;
+                            bool in = r2 < lo;
+                            if (!in && r2 <= hi) {
+                                const SysDev &Q = sys[find_sys(tprefix, n_sys, tile)];
+                                const double4 xa = pos[rbase + 16 * R + col], xb = pos[sh.cj[base + q]];
+                                const double fj[3] = {(double)ax, (double)ay, (double)az};
+                                const double fi[3] = {(double)xt.x, (double)xt.y, (double)xt.z};
+                                const double pa[3] = {xa.x, xa.y, xa.z}, pb[3] = {xb.x, xb.y, xb.z};
+                                double dd[3];
+#pragma unroll
+                                for (int c = 0; c < 3; ++c) {
+                                    // frame images of both: k = round((frame - stored) / L)
+                                    const double kj = rint((fj[c] + P->ref[c] - pb[c]) * Q.invL[c]);
+                                    const double ki = rint((fi[c] + P->ref[c] - pa[c]) * Q.invL[c]);
+                                    dd[c] = pb[c] - pa[c];
+                                    if (kj != ki) dd[c] = dd[c] + (kj - ki) * Q.L[c];
+                                }
+                                in = norm2_exact(dd[0], dd[1], dd[2]) < Q.rl2;
                             }
+                            if (in) hit |= w & (0u - w);
                         }
-                        return hit;
-                    };
-                    // a hit goes to its row's next entry (entries past the
-                    // capacity land on the row's spare slot); the count of each
-                    // half of the wave is its own row's
-                    auto append = [&](bool hit, int q) {
-                        const uint64_t m = __ballot(hit);
-                        const uint32_t mlo = (uint32_t)m, mhi = (uint32_t)(m >> 32);
-                        if (hit) {
-                            const int below = hh ? (int)__builtin_amdgcn_mbcnt_hi(mhi, 0u)
-                                                 : (int)__builtin_amdgcn_mbcnt_lo(mlo, 0u);
-                            const int p = ntot + below;
-                            myrow[p < cap ? p : cap] = (uint16_t)q;
+#pragma unroll
+                        for (int wd = 0; wd < kWords; ++wd) {
+                            const int sft = 4 * (blocks(wd) - 1 - (i & 7));
+                            if (i >> 3 == wd) m[wd][R] = (m[wd][R] & ~(open << sft)) | (hit << sft);
                         }
-                        ntot += hh ? __popc(mhi) : __popc(mlo);
-                    };
-                    // every lane reads a slot of the chunk, clamped: lanes past
-                    // their line's end take no part
-                    for (int qa = base;; qa += 2 * gsz) {
-                        const int qb = qa + gsz;
-                        const bool ona = qa < end, onb = qb < end;
-                        if (__ballot(ona) == 0ull) break;
-                        const float4 ca = cq[qa < qlast ? qa : qlast];
-                        const float4 cb = cq[qb < qlast ? qb : qlast];
-                        const float dxa = ca.x - xt.x, dya = ca.y - xt.y, dza = ca.z - xt.z;
-                        const float dxb = cb.x - xt.x, dyb = cb.y - xt.y, dzb = cb.z - xt.z;
-                        const float r2a = dxa * dxa + dya * dya + dza * dza;
-                        const float r2b = dxb * dxb + dyb * dyb + dzb * dzb;
-                        const bool la = r2a < lo_f, lb2 = r2b < lo_f;
-                        bool ha = ona && la && __float_as_int(ca.w) != it;
-                        bool hb = onb && lb2 && __float_as_int(cb.w) != it;
-                        const bool ba = ona && !la && r2a <= hi_f;
-                        const bool bb = onb && !lb2 && r2b <= hi_f;
-                        if (__builtin_expect(__ballot(ba || bb) != 0ull, 0)) {
-                            if (ba) ha = exact(ca);
-                            if (bb) hb = exact(cb);
-                        }
-                        ha = excluded(ha, ca);
-                        hb = excluded(hb, cb);
-                        append(ha, qa);
-                        append(hb, qb);
                     }
-                    if (hl == 0 && row_on) sh.rown[t] = ntot;
                 }
             }
-        }
-        lds_barrier();
-        // ---- 6. halo numbering, rows out ------------------------------------------
-        // writers: every wave but the loader
-        const int wid = wv == 0 ? tid : tid - kWave;
-        constexpr int kWriters = NT - kWave;
-        const bool act0 = tid < kTile && r0 + tid < n_local;
-        const int64_t i0 = row0 + r0 + tid;
-        if (wv == 0) {
-            // longest row of the tile: a wave reduction
-            int n = act0 ? sh.rown[tid] : 0;
-            n = wave_max_full(n < cap ? n : cap);
-            if (tid == 0) sh.info[2] = n;
-        }
-        if constexpr (LPR == 32) {
-            // the staged slots that some row lists (the 64-lane scan marks
-            // them as it finds them)
+            // word g of lane t: row t against the members 4 g + c of the
+            // wave's blocks, block i result c at bit 4 (blocks - 1 - i) + 3 - c
+#pragma unroll
+            for (int wd = 0; wd < kWords; ++wd) turn_masks(m[wd]);
+            auto drop = [&](int q) {
+                const int i = q >> 4, g = (q >> 2) & 3;
+#pragma unroll
+                for (int wd = 0; wd < kWords; ++wd) {
+                    const uint32_t bit = 1u << ((4 * (blocks(wd) - 1 - (i & 7)) + 3 - (q & 3)) & 31);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) m[wd][v] &= g == v && i >> 3 == wd ? ~bit : ~0u;
+                }
+            };
+            const int sq = sh.selfq[wv][lane];
+            if (sq != 0xFFFF) drop(sq);
+            if constexpr (EXCL) {
+                const int en = ex.n[wv][lane] < 2 * kMaxBondCap ? ex.n[wv][lane] : 2 * kMaxBondCap;
+                for (int b = 0; b < en; ++b) drop(ex.q[wv][lane][b]);
+            }
+            int c = 0;
+#pragma unroll
+            for (int wd = 0; wd < kWords; ++wd)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    uint32_t used = 0u;
+                    if (8 * 16 * wd < n) used = wave_or(m[wd][g]);
+                    c += __popc(m[wd][g]);
+                    if (lane == 0) sh.used[(wd * kWaves + wv) * 4 + g] = used;
+                }
+            sh.cnt[wv][lane] = (uint16_t)c;
+            if (lane == 0) sh.left[wv] = r < rounds;
+            if (dyn && tid == kWave) sh.grab[0] = grabbed;
             lds_barrier();
-            const int kmax_ = uni(sh.info[2]);
-            for (int e = tid; e < kmax_ * kTile; e += NT) {
-                const int t = e & (kTile - 1), k = e >> 6;
-                int n = sh.rown[t];
-                n = n < cap ? n : cap;
-                if (k < n) {
-                    const int q = srows[t * rstride + k];
-                    atomicOr(&sh.used[q >> 5], 1u << (q & 31));
-                }
-            }
-            lds_barrier();  // every mark made before the words are counted
-        }
-        const int nwords = (nslot + 31) / 32;
-        for (int q = tid; q < nwords; q += NT) sh.wpre[q] = __popc(sh.used[q]);
-        lds_barrier();
-        const int nhalo = uni(block_scan_w<NT>(sh.wpre, nwords, sh.scan));
-        if (nhalo > halo_cap) {
-            if (tid == 0) latch(st, 11 /*HALO_OVERFLOW*/, nhalo);
-            if (act0) nn[i0] = 0;
-            if (tid == 0) halo_n[tile] = 0;
-            continue;
-        }
-        int32_t *hl = halo + (int64_t)tile * halo_cap;
-        for (int q = loader ? nslot : wid; q < nslot; q += kWriters) {
-            const uint32_t word = sh.used[q >> 5];
-            if (word & (1u << (q & 31))) {
-                const int h = sh.wpre[q >> 5] + __popc(word & ((1u << (q & 31)) - 1u));
-                int32_t j;
-                if (one_chunk) {
-                    j = __float_as_int(sh.cp[q].w);
-                } else {
-                    const int u = upper_idx(sh.ustart, nu, q);
-                    j = cell_idx[(int64_t)sh.ucell[u] * cell_cap + (q - sh.ustart[u])];
-                }
-                hl[h] = j;
-            }
-        }
-        const int kmax = uni(sh.info[2]);
-        if (tid == 0) {
-            halo_n[tile] = (int32_t)((uint32_t)nhalo | ((uint32_t)kmax << 16) | (sh.info[1] ? 0x80000000u : 0u));
-            // per-pair images or a halo beyond the force pass's LDS staging
-            if (sh.info[1] || nhalo > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
-        }
-        uint16_t *out = nlist + nl0 + (int64_t)(r0 >> 6) * cap * kTile;
-        // four entries of a thread at a time, their LDS reads issued together
-        constexpr int kOut = 4;
-        for (int e0 = loader ? kmax * kTile : wid; e0 < kmax * kTile; e0 += kOut * kWriters) {
-            int q[kOut];
+
+            // ---- 3. halo numbering, this pass's part of every row --------------------
+            bool left = false;
+            int p = ntot;
 #pragma unroll
-            for (int b = 0; b < kOut; ++b) {
-                const int e = e0 + b * kWriters;
-                const int k = e >> 6, t = e & 63;
-                const int n = sh.rown[t];
-                q[b] = e < kmax * kTile && k < n && k < cap ? (int)srows[t * rstride + k] : -1;
+            for (int w = 0; w < kWaves; ++w) {
+                const int cw_ = sh.cnt[w][lane];
+                p += w < wv ? cw_ : 0;
+                ntot += cw_;
+                left = left || sh.left[w] != 0;
             }
+            left = uni((int)left) != 0;
+            whole = pass == 0 && !left;
+            const uint32_t uw = lane < kWords * kWaves * 4 ? sh.used[lane] : 0u;
+            const int hown = __popc(uw);
+            const int hi_ = wave_scan_incl(hown);
+            const int hv = hbase + hi_ - hown;  // halo index before each word
+            if constexpr (EXCL)
+                if (!left && more) insert_partners(t_next);
+            uint16_t *myrow = srows + lane * rstride;
+            uint16_t *out = nlist + (int64_t)tile * cap * kTile;
+            int32_t *hl = halo + (int64_t)tile * halo_cap;
 #pragma unroll
-            for (int b = 0; b < kOut; ++b) {
-                const int e = e0 + b * kWriters;
-                if (e < kmax * kTile) {
-                    uint16_t v = 0;
-                    if (q[b] >= 0) {
-                        const uint32_t word = sh.used[q[b] >> 5];
-                        v = (uint16_t)(sh.wpre[q[b] >> 5] + __popc(word & ((1u << (q[b] & 31)) - 1u)));
+            for (int wd = 0; wd < kWords; ++wd) {
+                if (8 * 16 * wd >= n) continue;
+                const int nb = blocks(wd);
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const uint32_t used = (uint32_t)__builtin_amdgcn_readlane((int)uw, (wd * kWaves + wv) * 4 + g);
+                    const int first = __builtin_amdgcn_readlane(hv, (wd * kWaves + wv) * 4 + g);
+                    if (lane < 32 && ((used >> lane) & 1u)) {
+                        const int h = first + __popc(used & ((1u << lane) - 1u));
+                        const int q = 16 * (8 * wd + nb - 1 - (lane >> 2)) + 4 * g + 3 - (lane & 3);
+                        if (h < halo_cap) hl[h] = sh.cj[base + q];
                     }
-                    out[e] = v;
+#pragma unroll 1
+                    for (uint32_t w = m[wd][g]; w; w &= w - 1u) {
+                        const uint32_t low = (w & (0u - w)) - 1u;
+                        const uint16_t h = (uint16_t)(first + __popc(used & low));
+                        // entries past the capacity land on the row's spare slot
+                        if (whole) myrow[p < cap ? p : cap] = h;
+                        else if (p < cap) out[p * kTile + lane] = h;
+                        ++p;
+                    }
+                }
+            }
+            hbase += __builtin_amdgcn_readlane(hi_, kWave - 1);
+            lds_barrier();
+            if (!left) break;
+        }
+        if (more) {
+            read_head(t_next);
+            read_segments(t_next, 0);
+        }
+
+        // ---- 4. rows out --------------------------------------------------------
+        if (nu >= 0) {  // (else built by the general kernel)
+            const bool act = lane < nrows;
+            const int n = ntot < cap ? ntot : cap;
+            const int kmax = wave_max_full(act ? n : 0);
+            const bool fits = hbase <= halo_cap;
+            if (tid == 0) {
+                halo_n[tile] = fits ? (int32_t)((uint32_t)hbase | ((uint32_t)kmax << 16) | (pp ? 0x80000000u : 0u)) : 0;
+                // per-pair images or a halo beyond the force pass's LDS staging
+                if (fits && (pp || hbase > halo_lds)) rare_list[atomicAdd(rare_n, 1)] = tile;
+                if (!fits) latch(st, 11 /*HALO_OVERFLOW*/, hbase);
+            }
+            if (wv == 0 && act) {
+                nn[rbase + lane] = fits ? n : 0;
+                if (fits && ntot > cap) latch(st, 5 /*NLIST_OVERFLOW*/, ntot);
+            }
+            if (fits && whole) {
+                // two rows' entries per lane, two entries of all rows per wave
+                uint32_t *out = reinterpret_cast<uint32_t *>(nlist + (int64_t)tile * cap * kTile);
+                const int ta = 2 * (lane & 31);
+                const int na = __shfl(n, ta, kWave), nb2 = __shfl(n, ta + 1, kWave);
+                const uint16_t *ra = srows + ta * rstride, *rb = ra + rstride;
+                for (int k = 2 * wv + (lane >> 5); k < kmax; k += 2 * kWaves) {
+                    const uint32_t va = k < na ? ra[k] : 0u, vb = k < nb2 ? rb[k] : 0u;
+                    out[k * 32 + (lane & 31)] = va | (vb << 16);
                 }
             }
         }
-        if (act0) {
-            const int n = sh.rown[tid];
-            nn[i0] = n < cap ? n : cap;
-            if (n > cap) latch(st, 5 /*NLIST_OVERFLOW*/, n);
-        }
+        if (!more) break;
+        t_cur = t_next;
+        t_next = dyn ? dfirst + uni(sh.grab[0]) : rebuilt_from(t_next + tstep);
+        lds_barrier();  // the rows are read, and the next index
     }
 }
 
 // ---------------------------------------------------------------------------
 // host-side launchers
 // ---------------------------------------------------------------------------
-
-static int capped(int64_t blocks) { return (int)(blocks < kRebuildGrid ? (blocks > 0 ? blocks : 1) : kRebuildGrid); }
 
 void launch_bin(const LaunchCtx &L, const double4 *pos, int nvt_w)
 {
@@ -1821,92 +1447,98 @@ void launch_cell_sort(const LaunchCtx &L, const double4 *pos)
     int64_t n_sort = L.n_cells < 8192 ? L.n_cells : 8192;
     n_sort = (n_sort + kDies - 1) / kDies * kDies;
     const int n_plan = L.tiles_local < kPlanGrid ? L.tiles_local : kPlanGrid;
-    const PlanPtrs plan = plan_ptrs(L.plan, L.tiles_local);
+    if (L.line_rows) {
+        launch_cells_and_lines(L, pos, (int)n_sort, n_plan);
+        return;
+    }
     const dim3 grid((unsigned)(n_sort + n_plan));
     if (L.cell_cap <= 64)
         hipLaunchKernelGGL(k_cells_and_plan<1>, grid, dim3(kWave), 0, L.stream, (int)n_sort, L.sys, L.cprefix, L.n_sys,
                            L.tprefix_local, L.tiles_local, pos, L.n_cells, L.cell_count, L.cell_size, L.cell_idx,
-                           L.cell_xf, L.cell_cap, L.xbuild, L.slow_list, L.slow_n, plan, L.flag, L.sflag,
+                           L.cell_xf, L.cell_cap, L.xbuild, L.slow_list, L.slow_n, L.plan,
+                           plan_stride(L.seg_cap), L.flag, L.sflag,
                            L.halo_n, L.halo_lds, L.rare_list, L.rare_n);
     else
         hipLaunchKernelGGL(k_cells_and_plan<2>, grid, dim3(kWave), 0, L.stream, (int)n_sort, L.sys, L.cprefix, L.n_sys,
                            L.tprefix_local, L.tiles_local, pos, L.n_cells, L.cell_count, L.cell_size, L.cell_idx,
-                           L.cell_xf, L.cell_cap, L.xbuild, L.slow_list, L.slow_n, plan, L.flag, L.sflag,
+                           L.cell_xf, L.cell_cap, L.xbuild, L.slow_list, L.slow_n, L.plan,
+                           plan_stride(L.seg_cap), L.flag, L.sflag,
                            L.halo_n, L.halo_lds, L.rare_list, L.rare_n);
 }
 
-int nlist_row_stride(int cap)
+int nlist_chunk() { return kWave; }
+int nlist_block(bool line_rows) { return line_rows ? 512 : kFastThreads; }
+bool nlist_shape_ok(int chunk, int block)
 {
-    // uint16 entries per staged row; an odd number of words keeps the
-    // transposed read-out free of bank conflicts
-    // one spare entry past the capacity takes the writes of an overflowing row
-    int r = cap + 1 + ((cap + 1) & 1);
-    if (((r / 2) & 1) == 0) r += 2;
-    return r;
+    return (chunk == 32 || chunk == 64) && (block == 256 || block == 512);
 }
 
-int nlist_lanes_per_row() { return kWave; }
-int nlist_block() { return kFastThreads; }
-bool nlist_shape_ok(int lanes_per_row, int block)
+// Room for the segments of a tile's cells in its plan: 150 cells (a compact
+// tile of 64 rows touches 40 to 100 once the far ones are dropped) of the
+// densest occupancy to expect; tiles with more go to the general build.
+int build_seg_cap(double cell_mean)
 {
-    return (lanes_per_row == 32 || lanes_per_row == 64) && (block == 256 || block == 512);
+    const int per_cell = (int)std::ceil((cell_mean + 3.0 * std::sqrt(cell_mean)) / kSeg);
+    return std::min(std::max(150 * per_cell, kSegMin), 2040);
 }
 
-size_t fast_build_lds_bytes(int cap) { return sizeof(FastShared) + (size_t)kTile * nlist_row_stride(cap) * 2; }
-
-size_t build_plan_bytes(int64_t tiles)
+size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows)
 {
-    // the carving of plan_ptrs, with every part rounded to 256 bytes
-    auto r = [](size_t b) { return (b + 255) / 256 * 256; };
-    const size_t t = (size_t)(tiles > 0 ? tiles : 1);
-    return r(sizeof(int4) * t) + r(sizeof(int2) * t * kUMax) + r(sizeof(float4) * t * kUMax) +
-           r(sizeof(float4) * t * kTile) + r(sizeof(uint32_t) * t * kTile * kRuns) +
-           r(sizeof(float) * t * kTile * kRuns);
+    return line_rows ? line_plan_bytes(tiles) : (size_t)(tiles > 0 ? tiles : 1) * (size_t)plan_stride(seg_cap);
+}
+
+int cell_xf_slots(int cell_cap) { return cell_xf_stride(cell_cap); }
+
+// LDS beside FastShared: the staged positions, and in their place the rows.
+template <bool EXCL, int NT, int LPR>
+static int fast_dyn(int cap)
+{
+    const int rows = kTile * nlist_row_stride(cap) * 2;
+    return std::max(rows, 4 * build_astride(build_chunk(LPR)) * (int)sizeof(float));
 }
 
 template <bool EXCL, int NT, int LPR>
-static hipError_t fast_attr(int dyn)
+static hipError_t fast_attr(int cap)
 {
     return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_build_fast<EXCL, NT, LPR>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, dyn);
+                               hipFuncAttributeMaxDynamicSharedMemorySize, fast_dyn<EXCL, NT, LPR>(cap));
 }
 
 hipError_t prepare_nlist(int cap)
 {
-    const int dyn = kTile * nlist_row_stride(cap) * 2;
-    const hipError_t es[8] = {fast_attr<false, 512, 64>(dyn), fast_attr<false, 256, 64>(dyn),
-                              fast_attr<false, 512, 32>(dyn), fast_attr<false, 256, 32>(dyn),
-                              fast_attr<true, 512, 64>(dyn),  fast_attr<true, 256, 64>(dyn),
-                              fast_attr<true, 512, 32>(dyn),  fast_attr<true, 256, 32>(dyn)};
+    const hipError_t es[8] = {fast_attr<false, 512, 64>(cap), fast_attr<false, 256, 64>(cap),
+                              fast_attr<false, 512, 32>(cap), fast_attr<false, 256, 32>(cap),
+                              fast_attr<true, 512, 64>(cap),  fast_attr<true, 256, 64>(cap),
+                              fast_attr<true, 512, 32>(cap),  fast_attr<true, 256, 32>(cap)};
     for (hipError_t e : es)
         if (e != hipSuccess) return e;
-    return hipSuccess;
+    return prepare_lines(cap);
 }
 
 template <bool EXCL, int NT, int LPR>
-static void fast_inst(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int blocks, int rs, size_t dyn,
-                      const PlanPtrs &plan)
+static void fast_inst(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int blocks, int rs)
 {
+    const int dyn = fast_dyn<EXCL, NT, LPR>(L.nlist_cap);
     hipLaunchKernelGGL((k_build_fast<EXCL, NT, LPR>), dim3(blocks), dim3(NT), dyn, L.stream, L.sys, L.tprefix_local,
-                       L.n_sys, L.tiles_local, pos, tag, L.ptag, L.cell_size, L.cell_idx, L.cell_xf, L.cell_cap,
-                       L.nlist, L.nn, L.nlist_cap, rs, L.halo, L.halo_n, L.halo_cap, plan, L.halo_lds, L.rare_list,
-                       L.rare_n, L.tile_ctr, L.cell_count, L.n_cells, L.flag, L.sflag, L.build_count, L.status);
+                       L.n_sys, L.tiles_local, pos, tag, L.ptag, L.bond_stride, L.cell_xf, L.nlist, L.nn, L.nlist_cap, rs, L.halo,
+                       L.halo_n, L.halo_cap, L.plan, plan_stride(L.seg_cap), L.halo_lds, L.rare_list, L.rare_n,
+                       L.tile_ctr, L.cell_count, L.n_cells, L.flag, L.sflag, L.build_count, L.status);
 }
 
 template <bool EXCL>
-static void fast_shape(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int blocks, int rs, size_t dyn,
-                       const PlanPtrs &plan, int w, int block)
+static void fast_shape(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int blocks, int rs,
+                       int w, int block)
 {
     if (w == 32) {
-        if (block == 256) fast_inst<EXCL, 256, 32>(L, pos, tag, blocks, rs, dyn, plan);
-        else fast_inst<EXCL, 512, 32>(L, pos, tag, blocks, rs, dyn, plan);
+        if (block == 256) fast_inst<EXCL, 256, 32>(L, pos, tag, blocks, rs);
+        else fast_inst<EXCL, 512, 32>(L, pos, tag, blocks, rs);
     } else {
-        if (block == 256) fast_inst<EXCL, 256, 64>(L, pos, tag, blocks, rs, dyn, plan);
-        else fast_inst<EXCL, 512, 64>(L, pos, tag, blocks, rs, dyn, plan);
+        if (block == 256) fast_inst<EXCL, 256, 64>(L, pos, tag, blocks, rs);
+        else fast_inst<EXCL, 512, 64>(L, pos, tag, blocks, rs);
     }
 }
 
-// w: lanes per row of the framed build (64 or 32); block: its threads per
+// w: chunk of the framed build (64 or 32); block: its threads per
 // workgroup (512 or 256).  The general build's shape is fixed.
 void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int w, int block)
 {
@@ -1918,17 +1550,17 @@ void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, in
     }
     const int blocks = capped(L.tiles_local);
     const int rs = nlist_row_stride(L.nlist_cap);
-    const size_t dyn = (size_t)kTile * rs * 2;
-    const PlanPtrs plan = plan_ptrs(L.plan, L.tiles_local);
     if (L.has_bonds) {
-        fast_shape<true>(L, pos, tag, blocks, rs, dyn, plan, w, block);
+        if (L.line_rows) launch_build_lines(L, pos, tag, block);
+        else fast_shape<true>(L, pos, tag, blocks, rs, w, block);
         hipLaunchKernelGGL(k_build_tile<true>, dim3(blocks), dim3(kBuildThreads), 0, L.stream, L.sys,
                            L.tprefix_local, L.n_sys, L.tiles_local, pos, tag, L.ptag, L.cell_size,
                            L.cell_idx, L.cell_cap, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
                            L.halo_cap, L.xbuild, L.slow_list, L.slow_n, L.halo_lds, L.rare_list, L.rare_n, L.flag,
                            nullptr, L.status);
     } else {
-        fast_shape<false>(L, pos, tag, blocks, rs, dyn, plan, w, block);
+        if (L.line_rows) launch_build_lines(L, pos, tag, block);
+        else fast_shape<false>(L, pos, tag, blocks, rs, w, block);
         hipLaunchKernelGGL(k_build_tile<false>, dim3(blocks), dim3(kBuildThreads), 0, L.stream, L.sys,
                            L.tprefix_local, L.n_sys, L.tiles_local, pos, tag, L.ptag, L.cell_size,
                            L.cell_idx, L.cell_cap, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,

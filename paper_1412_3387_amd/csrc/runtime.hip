@@ -40,7 +40,8 @@ struct Layout {
     size_t ptag, pdir, prow, btmp, hash, slow_list, rare_list, plan, sort_ws, ghost_ws, total;
     // sizes
     int64_t rows, tiles_local, tiles_all, n_cells, nlist_entries, hash_slots;
-    int cell_cap, nlist_cap, bond_cap, halo_cap, halo_lds;
+    int cell_cap, nlist_cap, bond_cap, halo_cap, halo_lds, seg_cap;
+    bool line_rows;  // the list build with line-ordered rows: mixed-precision DPD
     std::vector<SysDev> sys;
     std::vector<int32_t> tpl_host, tpa_host;
     std::vector<int64_t> cpre_host;
@@ -103,11 +104,11 @@ bool valid(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
                     (p[u].dt != q.dt || p[u].nvt_T0 != q.nvt_T0 || p[u].nvt_tau != q.nvt_tau))
                     return false;
         }
-        // launch shapes: the framed build takes 64 or 32 lanes per row and 512
-        // or 256 threads per workgroup (one shape for all systems); the force
+        // launch shapes: the framed build takes a chunk (64 or 32) and 512 or
+        // 256 threads per workgroup (one shape for all systems); the force
         // pass runs 64 rows x tpp_force lanes per workgroup
-        if (q.tpp_nlist != 0 && !nlist_shape_ok(q.tpp_nlist, nlist_block())) return false;
-        if (q.block_nlist != 0 && !nlist_shape_ok(nlist_lanes_per_row(), q.block_nlist)) return false;
+        if (q.tpp_nlist != 0 && !nlist_shape_ok(q.tpp_nlist, nlist_block(false))) return false;
+        if (q.block_nlist != 0 && !nlist_shape_ok(nlist_chunk(), q.block_nlist)) return false;
         if (q.tpp_nlist != p[0].tpp_nlist || q.block_nlist != p[0].block_nlist) return false;
         if (q.block_force != 0 && (q.tpp_force == 0 || q.block_force != 64 * q.tpp_force)) return false;
         if (b.n_local < 0 || b.n_cap < b.n_local || b.n_cap > (int64_t)1 << 30) return false;
@@ -127,6 +128,8 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
     Lo.nlist_cap = 0;
     Lo.cell_cap = 0;
     Lo.bond_cap = 0;
+    Lo.seg_cap = 0;
+    Lo.line_rows = p[0].pair == HOOMD_PAIR_DPD && p[0].precision == HOOMD_MIXED;
     int64_t row = 0, tile = 0, tile_all = 0, cell = 0, nl = 0, hslot = 0;
     Lo.tpl_host.push_back(0);
     Lo.tpa_host.push_back(0);
@@ -250,6 +253,8 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
             int cc = (int)std::ceil((2.0 * mean + 16.0) / 8.0) * 8;
             Lo.cell_cap = std::max(Lo.cell_cap, std::min(cc, 128));
         }
+        S.seg_cap = build_seg_cap((double)b.n_cap / (double)ncell);
+        Lo.seg_cap = std::max(Lo.seg_cap, S.seg_cap);
         // bonded systems: a tag -> row table with at least twice as many
         // slots as rows (locals and ghosts)
         S.hash0 = hslot;
@@ -313,7 +318,7 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
     Lo.cell_count = take(sizeof(int32_t) * (size_t)cell);
     Lo.cell_size = take(sizeof(int32_t) * (size_t)cell);
     Lo.cell_idx = take(sizeof(int32_t) * (size_t)cell * Lo.cell_cap);
-    Lo.cell_xf = take(sizeof(float4) * (size_t)cell * Lo.cell_cap);
+    Lo.cell_xf = take(sizeof(float4) * (size_t)cell * cell_xf_slots(Lo.cell_cap));
     const size_t brows = Lo.bond_cap > 0 ? rows * (size_t)Lo.bond_cap : 1;
     Lo.ptag = take(sizeof(int32_t) * brows);
     Lo.pdir = take(sizeof(int32_t) * brows);
@@ -322,7 +327,7 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
     Lo.hash = take(sizeof(int2) * (size_t)std::max<int64_t>(Lo.hash_slots, 1));
     Lo.slow_list = take(sizeof(int32_t) * (size_t)std::max<int64_t>(tile, 1));
     Lo.rare_list = take(sizeof(int32_t) * (size_t)std::max<int64_t>(tile, 1));
-    Lo.plan = take(build_plan_bytes(tile));
+    Lo.plan = take(build_plan_bytes(tile, Lo.seg_cap, Lo.line_rows));
     Lo.sort_ws = take(sort_workspace_bytes((int64_t)rows));
     Lo.ghost_ws = take(ghost_workspace_bytes((int64_t)rows, n_sys));
     Lo.total = off;
@@ -395,12 +400,10 @@ void default_tuning(hoomd_ctx *c)
 {
     // neighbours per particle and particles per CU decide the lane count;
     // the autotuner refines these on the live state
-    // the build always runs 4 lanes per row, one 64-row tile per 256-thread
-    // workgroup; the force pass runs W lanes per row, one tile per 64 W
-    // threads
+    // the force pass runs W lanes per row, one tile per 64 W threads
     const double per_cu = (double)c->lay.tiles_local * 64.0 / 256.0;
-    c->tpp_nlist = nlist_lanes_per_row();
-    c->block_nlist = nlist_block();
+    c->tpp_nlist = nlist_chunk();
+    c->block_nlist = nlist_block(c->lay.line_rows);
     if (c->prm[0].tpp_nlist > 0) c->tpp_nlist = c->prm[0].tpp_nlist;
     if (c->prm[0].block_nlist > 0) c->block_nlist = c->prm[0].block_nlist;
     c->fixed_nlist = c->prm[0].tpp_nlist > 0 || c->prm[0].block_nlist > 0;
@@ -624,6 +627,9 @@ int hoomd_init(hoomd_ctx **out, const hoomd_params *params, int32_t n_sys, const
     L.slow_n = flag_ptr(c, 6);
     L.rare_list = ws_ptr<int32_t>(c, lay.rare_list);
     L.plan = ws_ptr<char>(c, lay.plan);
+    L.seg_cap = lay.seg_cap;
+    L.line_rows = lay.line_rows;
+    L.sorted = params[0].sort_period > 0;
     L.rare_n = flag_ptr(c, 7);
     L.tile_ctr = ws_ptr<int32_t>(c, lay.tile_ctr);
     L.status = ws_ptr<Status>(c, lay.status);
