@@ -12,17 +12,17 @@
 // Neighbour list: one workgroup per tile of 64 consecutive rows (Morton
 // ordered rows make a tile one or a few compact clusters).  The workgroup
 //   1. collects the stencil cells of all its rows and sorts out the
-//      distinct ones (bitonic sort in LDS), so any tile shape works,
-//   2. stages the members of those cells (positions and row numbers) in LDS,
-//      a chunk at a time,
-//   3. lets W = 8 lanes per particle stride over the members of the
-//      particle's own 27 stencil cells and test |x_j - x_i|^2 < r_list^2 in
-//      FP64 (minimum image written as the stencil's image shift, which for
-//      every pair inside r_list is bitwise the shift the exact quotient
-//      gives), compacting hits into the row with a 64-bit ballot,
-//   4. marks every staged member that some row uses, numbers the marked
-//      members in staging order -- the tile's halo -- and rewrites the rows
+//      distinct ones (a bitmap or a sort in LDS), so any tile shape works,
+//   2. lets W lanes per particle stride over the members of the particle's
+//      own 27 stencil cells and test |x_j - x_i|^2 < r_list^2 in FP64
+//      (minimum image written as the stencil's image shift, which for every
+//      pair inside r_list is bitwise the shift the exact quotient gives),
+//      compacting hits into the row with a 64-bit ballot,
+//   3. marks every member that some row uses, numbers the marked members in
+//      the order of their cells -- the tile's halo -- and rewrites the rows
 //      as 16-bit halo indices.
+// That is the general build; tiles that fit one unwrapped frame take the
+// framed build further below.
 // The force pass then loads each halo position once per tile into LDS
 // instead of once per neighbour from L2.
 //
@@ -40,14 +40,11 @@
 
 namespace md {
 
-constexpr int kBuildThreads = 512;   // 64 rows x 8 lanes
-constexpr int kBuildW = 8;
-constexpr int kChunk = 2048;         // members staged at once
+constexpr int kBuildThreads = 512;   // threads per tile of the general build's own launch
+constexpr int kChunk = 2048;         // members it stages at once
 constexpr int kSlotMax = 16384;      // members of a tile's stencil cells
 constexpr int kKeys = 2048;          // 64 rows x 27 stencil cells, padded
-constexpr int kKpt = kKeys / kBuildThreads;  // stencil keys per thread
-static_assert(kKeys % kBuildThreads == 0 && kKeys <= 8 * kBuildThreads, "key split");
-static_assert(kBuildThreads == kTile * kBuildW, "one row per lane group");
+constexpr int kCellBits = 1 << 17;   // cells of a system whose stencil cells are marked in a bitmap
 constexpr int kStencil = 27;
 
 // ---------------------------------------------------------------------------
@@ -132,78 +129,69 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
 // tile-halo neighbour list
 // ---------------------------------------------------------------------------
 
-struct BuildShared {
-    double cx[kChunk], cy[kChunk], cz[kChunk];
-    int32_t cj[kChunk];
-    int32_t keys[kKeys];              // stencil cells, then distinct cells
-    int32_t ucount[kKeys];            // flags / members of each distinct cell
-    int32_t ustart[kKeys + 1];        // first slot of each distinct cell
-    uint32_t used[kSlotMax / 32];
-    int32_t wpre[kSlotMax / 32 + 1];
-    int16_t su[kTile][kStencil];      // distinct-cell index of each row's stencil cell (-1: none)
-    int8_t sm[kTile][kStencil];       // image code (mx+1) + 3 (my+1) + 9 (mz+1)
-    int32_t scan[kBuildThreads];
-    int32_t ext[6];                   // min / max cell offset from the first row
-    int32_t info[4];                  // distinct cells, per-pair image flag, longest row
+// LDS of a tile of the general build; CH members staged at once (0: none are).
+template <int CH>
+struct GeneralStage {
+    double cx[CH], cy[CH], cz[CH];
+    int32_t cj[CH];
 };
+template <>
+struct GeneralStage<0> {
+};
+template <int CH>
+struct GeneralShared {
+    union {
+        GeneralStage<CH> stage;
+        uint32_t bits[kCellBits / 32];    // stencil cells met, where the system has few enough cells
+        int32_t tmp[kKeys];               // stencil cells to sort, counts to scan, ranks of used slots
+    };
+    int32_t keys[kTile * kStencil + 1];   // distinct stencil cells, ascending
+    uint16_t ustart[kTile * kStencil + 1];  // first slot of each distinct cell
+    uint32_t used[kSlotMax / 32];
+    int16_t su[kTile][kStencil];          // distinct-cell index of each row's stencil cell (-1: none)
+    int8_t sm[kTile][kStencil];           // image code (mx+1) + 3 (my+1) + 9 (mz+1)
+    int32_t scan[kBuildThreads / kWave];
+    int32_t ext[6];                       // min / max cell offset from the first row
+    int32_t info[4];                      // (unused), per-pair image flag, longest row
+};
+static_assert(kSlotMax < 65536, "slots of a tile in 16 bits");
 
-// Exclusive scan of n <= 8 * NT values held in LDS `a` (in place) by a block
-// of NT threads; returns the total.
-template <int NT>
-__device__ __forceinline__ int block_scan(int32_t *a, int n, int32_t *scan)
+// Index of the largest entry <= x in the ascending 16-bit array a[0..n).
+__device__ __forceinline__ int upper_idx16(const uint16_t *a, int n, int x)
 {
-    const int tid = threadIdx.x;
-    const int b = 8 * tid;
-    int v[8];
-    int sum = 0;
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        v[k] = b + k < n ? a[b + k] : 0;
-        sum += v[k];
+    int lo = 0, hi = n;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if ((int)a[mid] <= x) lo = mid;
+        else hi = mid;
     }
-    scan[tid] = sum;
-    __syncthreads();
-    for (int off = 1; off < NT; off <<= 1) {
-        const int add = tid >= off ? scan[tid - off] : 0;
-        __syncthreads();
-        scan[tid] += add;
-        __syncthreads();
-    }
-    int run = tid > 0 ? scan[tid - 1] : 0;
-    const int total = scan[NT - 1];
-#pragma unroll
-    for (int k = 0; k < 8; ++k)
-        if (b + k < n) {
-            a[b + k] = run;
-            run += v[k];
-        }
-    __syncthreads();
-    return total;
+    return lo;
 }
 
-__device__ __forceinline__ int block_scan8(int32_t *a, int n, int32_t *scan)
-{
-    return block_scan<kBuildThreads>(a, n, scan);
-}
-
-template <bool EXCL>
-__global__ __launch_bounds__(kBuildThreads) void k_build_tile(
-    const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
+// The general build of one tile by NT threads.  A launch has few such tiles, so
+// one tile's latency bounds it.  The distinct stencil cells come out of a
+// bitmap of the system's cells where it has at most kCellBits: a sort of the
+// 1,728 keys is 66 passes with a barrier each and stays for larger systems.
+// Rows of these tiles lie far apart and share few cells, so (CH = 0) each row
+// reads its own stencil from memory rather than all rows every staged chunk
+// (CH > 0, which keeps the entries of a row in the order of the chunks: the
+// bits of mixed-precision DPD sums).  Sort, chunks of 2,048 and a launch of its
+// own took 70 - 127 us; inside the framed launch, staged 512 at a time, that
+// launch took 147 us (DPD, 100,000 particles), 265 us (64 WCA melts) and
+// 189 us (LJ, 255,000), and reading directly 88, 193 and 157 us.
+template <bool EXCL, int NT, int CH>
+__device__ __forceinline__ void general_tile(
+    GeneralShared<CH> &sh, int tile, const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys,
     const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
     const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
     uint16_t *__restrict__ nlist, int32_t *__restrict__ nn, int cap, int32_t *__restrict__ halo,
-    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild,
-    const int32_t *__restrict__ list, const int32_t *__restrict__ list_n, int halo_lds,
-    int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n,
-    const int32_t *__restrict__ flag, int32_t *build_count, Status *st)
+    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild, int halo_lds,
+    int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, Status *st)
 {
-    if (*flag == 0) return;
-    // with a list: only the tiles named there (those the framed build passed on)
-    const int ntiles = list ? *list_n : tiles;
-    if ((int)blockIdx.x >= ntiles && !(build_count && blockIdx.x == 0)) return;
-    __shared__ BuildShared sh;
-    constexpr int W = kBuildW;
+    constexpr int W = NT / kTile;
     constexpr int P = kWave / W;
+    constexpr int kKpt = kKeys / NT;  // stencil keys per thread
+    static_assert(kKeys % NT == 0 && kKeys <= 8 * NT, "key split");
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int w = tid >> 6;
@@ -212,47 +200,51 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
     const int t = w * P + pl;  // particle slot in the tile
     const uint64_t seg = segment_bits(pl, P);
     const uint64_t below = lanemask_lt();
-    if (build_count && blockIdx.x == 0 && tid == 0) atomicAdd(build_count, 1);
 
-    int64_t tfirst = blockIdx.x, tend = ntiles;
-    int tstep = gridDim.x;
-    if (!list) die_range(blockIdx.x, gridDim.x, ntiles, tfirst, tend, tstep);
-    for (int it = (int)tfirst; it < tend; it += tstep) {
-        const int tile = list ? list[it] : it;
-        const int s = find_sys(tprefix, n_sys, tile);
-        const SysDev &S = sys[s];
-        // per-system constants, held in registers for the whole tile
-        const double Lx = S.L[0], Ly = S.L[1], Lz = S.L[2];
-        const double iLx = S.invL[0], iLy = S.invL[1], iLz = S.invL[2];
-        const int bx = S.bins[0], by = S.bins[1], bz = S.bins[2];
-        const int px = S.per[0], py = S.per[1], pz = S.per[2];
-        const int64_t row0 = S.row0, cell0 = S.cell0, nl0 = S.nl0;
-        const int n_local = S.n_local;
-        const double rl2 = S.rl2;
-        const int r0 = (tile - S.tile0) * kTile;
-        const int r = r0 + t;
-        const bool active = r < n_local;
-        const int64_t i = row0 + (active ? r : r0);
-        const double4 xi = pos[i];
-        int ci[3];
-        ci[0] = cell_coord(xi.x, S.lo[0], S.scale[0], bx);
-        ci[1] = cell_coord(xi.y, S.lo[1], S.scale[1], by);
-        ci[2] = cell_coord(xi.z, S.lo[2], S.scale[2], bz);
-        const double4 x0 = pos[row0 + r0];
-        const int c0[3] = {cell_coord(x0.x, S.lo[0], S.scale[0], bx), cell_coord(x0.y, S.lo[1], S.scale[1], by),
-                           cell_coord(x0.z, S.lo[2], S.scale[2], bz)};
+    const int s = find_sys(tprefix, n_sys, tile);
+    const SysDev &S = sys[s];
+    // per-system constants, held in registers for the whole tile
+    const double Lx = S.L[0], Ly = S.L[1], Lz = S.L[2];
+    const double iLx = S.invL[0], iLy = S.invL[1], iLz = S.invL[2];
+    const int bx = S.bins[0], by = S.bins[1], bz = S.bins[2];
+    const int px = S.per[0], py = S.per[1], pz = S.per[2];
+    const int64_t row0 = S.row0, cell0 = S.cell0, nl0 = S.nl0;
+    const int n_local = S.n_local;
+    const double rl2 = S.rl2;
+    const int64_t ncell = (int64_t)bx * by * bz;
+    const bool marks = ncell <= kCellBits;
+    const int r0 = (tile - S.tile0) * kTile;
+    const int r = r0 + t;
+    const bool active = r < n_local;
+    const int64_t i = row0 + (active ? r : r0);
+    const double4 xi = pos[i];
+    int ci[3];
+    ci[0] = cell_coord(xi.x, S.lo[0], S.scale[0], bx);
+    ci[1] = cell_coord(xi.y, S.lo[1], S.scale[1], by);
+    ci[2] = cell_coord(xi.z, S.lo[2], S.scale[2], bz);
+    const double4 x0 = pos[row0 + r0];
+    const int c0[3] = {cell_coord(x0.x, S.lo[0], S.scale[0], bx), cell_coord(x0.y, S.lo[1], S.scale[1], by),
+                       cell_coord(x0.z, S.lo[2], S.scale[2], bz)};
 
-        // ---- 1. distinct stencil cells of the tile ---------------------------
-        // stencil k = (oz * 3 + oy) * 3 + ox over the de-duplicated offsets
-        if (tid < 3) {
-            sh.ext[tid] = INT32_MAX;
-            sh.ext[3 + tid] = INT32_MIN;
-        }
-        if (tid == 0) sh.info[2] = 0;
-        for (int k = sl; k < kStencil; k += W) {
+    // ---- 1. distinct stencil cells of the tile -------------------------------
+    // stencil k = (oz * 3 + oy) * 3 + ox over the de-duplicated offsets
+    if (tid < 3) {
+        sh.ext[tid] = INT32_MAX;
+        sh.ext[3 + tid] = INT32_MIN;
+    }
+    if (tid == 0) sh.info[2] = 0;
+    const int nbits = marks ? ((int)ncell + 31) / 32 : 0;
+    for (int k = tid; k < nbits; k += NT) sh.bits[k] = 0u;
+    __syncthreads();
+    // the key of every row's stencil cell, kept for the lookup below
+    int32_t mykeys[(kStencil + W - 1) / W];
+#pragma unroll
+    for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
+        const int k = sl + q * W;
+        int key = INT32_MAX;
+        int code = 0;
+        if (k < kStencil) {
             const int ox = k % 3, oy = (k / 3) % 3, oz = k / 9;
-            int key = INT32_MAX;
-            int code = 0;
             if (active && ox < S.nst[0] && oy < S.nst[1] && oz < S.nst[2]) {
                 const int off[3] = {S.st[0][ox], S.st[1][oy], S.st[2][oz]};
                 const int bins[3] = {bx, by, bz};
@@ -279,147 +271,167 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
                 }
                 if (inside) key = (cc[2] * by + cc[1]) * bx + cc[0];
             }
-            sh.keys[t * kStencil + k] = key;
             sh.sm[t][k] = (int8_t)code;
-        }
-        for (int k = kTile * kStencil + tid; k < kKeys; k += kBuildThreads) sh.keys[k] = INT32_MAX;
-        __syncthreads();
-        if (active && sl == 0) {
-            const int bins[3] = {bx, by, bz};
-            const int per[3] = {px, py, pz};
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                const int d = ci[a] - c0[a];
-                const int rel = per[a] ? wrap_rel(d, bins[a]) : d;
-                atomicMin(&sh.ext[a], rel);
-                atomicMax(&sh.ext[3 + a], rel);
+            if (marks) {
+                if (key != INT32_MAX) atomicOr(&sh.bits[key >> 5], 1u << (key & 31));
+            } else {
+                sh.tmp[t * kStencil + k] = key;
             }
         }
-        // the key of every row's stencil cell, kept for the lookup below
-        int32_t mykeys[(kStencil + W - 1) / W];
+        mykeys[q] = key;
+    }
+    if (active && sl == 0) {
+        const int bins[3] = {bx, by, bz};
+        const int per[3] = {px, py, pz};
 #pragma unroll
-        for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
-            const int k = sl + q * W;
-            mykeys[q] = k < kStencil ? sh.keys[t * kStencil + k] : INT32_MAX;
+        for (int a = 0; a < 3; ++a) {
+            const int d = ci[a] - c0[a];
+            const int rel = per[a] ? wrap_rel(d, bins[a]) : d;
+            atomicMin(&sh.ext[a], rel);
+            atomicMax(&sh.ext[3 + a], rel);
         }
-        __syncthreads();
-        // bitonic sort of the keys
+    }
+    if (!marks)
+        for (int k = kTile * kStencil + tid; k < kKeys; k += NT) sh.tmp[k] = INT32_MAX;
+    __syncthreads();
+    int nu;
+    if (marks) {
+        // the marked cells in order: each thread's share of the words
+        const int per_thread = (nbits + NT - 1) / NT;
+        const int k0 = tid * per_thread, k1 = k0 + per_thread < nbits ? k0 + per_thread : nbits;
+        int c = 0;
+        for (int k = k0; k < k1; ++k) c += __popc(sh.bits[k]);
+        int p = block_rank<NT>(c, sh.scan, nu);
+        for (int k = k0; k < k1; ++k)
+            for (uint32_t m = sh.bits[k]; m; m &= m - 1u) sh.keys[p++] = 32 * k + __ffs((int)m) - 1;
+    } else {
+        // bitonic sort, then the first of each run of equal keys
         for (int k = 2; k <= kKeys; k <<= 1) {
             for (int j = k >> 1; j > 0; j >>= 1) {
-                for (int e = tid; e < kKeys / 2; e += kBuildThreads) {
+                for (int e = tid; e < kKeys / 2; e += NT) {
                     const int a = ((e & ~(j - 1)) << 1) | (e & (j - 1));
                     const int b = a | j;
-                    const int32_t ka = sh.keys[a], kb = sh.keys[b];
+                    const int32_t ka = sh.tmp[a], kb = sh.tmp[b];
                     if ((ka > kb) == ((a & k) == 0)) {
-                        sh.keys[a] = kb;
-                        sh.keys[b] = ka;
+                        sh.tmp[a] = kb;
+                        sh.tmp[b] = ka;
                     }
                 }
                 __syncthreads();
             }
         }
-        // distinct keys: flag first occurrences, scan, compact (kKpt keys
-        // per thread)
-        int flg[kKpt];
-        int32_t kv[kKpt];
-#pragma unroll
+        int c = 0;
         for (int k = 0; k < kKpt; ++k) {
             const int q = kKpt * tid + k;
-            kv[k] = sh.keys[q];
-            flg[k] = (kv[k] != INT32_MAX && (q == 0 || kv[k] != sh.keys[q - 1])) ? 1 : 0;
-            sh.ucount[q] = flg[k];
+            c += sh.tmp[q] != INT32_MAX && (q == 0 || sh.tmp[q] != sh.tmp[q - 1]) ? 1 : 0;
         }
-        __syncthreads();
-        const int nu = block_scan8(sh.ucount, kKeys, sh.scan);
+        int p = block_rank<NT>(c, sh.scan, nu);
+        for (int k = 0; k < kKpt; ++k) {
+            const int q = kKpt * tid + k;
+            if (sh.tmp[q] != INT32_MAX && (q == 0 || sh.tmp[q] != sh.tmp[q - 1])) sh.keys[p++] = sh.tmp[q];
+        }
+    }
+    if (tid == 0) {
+        int pp = 0;
+        const double Ls[3] = {Lx, Ly, Lz};
+        const int bins[3] = {bx, by, bz};
+        const int per[3] = {px, py, pz};
+        for (int a = 0; a < 3; ++a)
+            if (per[a] && (double)(sh.ext[3 + a] - sh.ext[a] + 3) * (Ls[a] / bins[a]) >= 0.5 * Ls[a]) pp = 1;
+        sh.info[1] = pp;
+    }
+    __syncthreads();
+    // member counts of the distinct cells and their prefix
+    int nslot;
+    {
+        constexpr int kPer = (kTile * kStencil + NT - 1) / NT;
+        int n[kPer], c = 0;
 #pragma unroll
-        for (int k = 0; k < kKpt; ++k)
-            if (flg[k]) sh.keys[sh.ucount[kKpt * tid + k]] = kv[k];
-        if (tid == 0) {
-            int pp = 0;
-            const double Ls[3] = {Lx, Ly, Lz};
-            const int bins[3] = {bx, by, bz};
-            const int per[3] = {px, py, pz};
-            for (int a = 0; a < 3; ++a)
-                if (per[a] && (double)(sh.ext[3 + a] - sh.ext[a] + 3) * (Ls[a] / bins[a]) >= 0.5 * Ls[a]) pp = 1;
-            sh.info[1] = pp;
+        for (int k = 0; k < kPer; ++k) {
+            const int u = kPer * tid + k;
+            n[k] = u < nu ? cell_size[cell0 + sh.keys[u]] : 0;
+            c += n[k];
         }
-        __syncthreads();
-        // member counts of the distinct cells and their prefix
-        for (int u = tid; u < nu; u += kBuildThreads) sh.ucount[u] = cell_size[cell0 + sh.keys[u]];
-        __syncthreads();
-        const int nslot = block_scan8(sh.ucount, nu, sh.scan);
-        for (int u = tid; u < nu; u += kBuildThreads) sh.ustart[u] = sh.ucount[u];
-        if (tid == 0) sh.ustart[nu] = nslot;
-        // each row's stencil cells as distinct-cell indices
+        int p = block_rank<NT>(c, sh.scan, nslot);
 #pragma unroll
-        for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
-            const int k = sl + q * W;
-            if (k < kStencil) sh.su[t][k] = mykeys[q] == INT32_MAX ? (int16_t)-1 : (int16_t)upper_idx(sh.keys, nu, mykeys[q]);
+        for (int k = 0; k < kPer; ++k) {
+            const int u = kPer * tid + k;
+            if (u < nu) sh.ustart[u] = (uint16_t)(p < 65535 ? p : 65535);
+            p += n[k];
         }
-        if (nslot > kSlotMax) {
-            if (tid == 0) latch(st, 11 /*HALO_OVERFLOW*/, nslot);
-            if (active && sl == 0) nn[i] = 0;
-            if (tid == 0) halo_n[tile] = 0;
-            __syncthreads();
-            continue;
-        }
-        for (int q = tid; q < (nslot + 31) / 32; q += kBuildThreads) sh.used[q] = 0u;
+        if (tid == 0) sh.ustart[nu] = (uint16_t)(nslot < 65535 ? nslot : 65535);
+    }
+    // each row's stencil cells as distinct-cell indices
+#pragma unroll
+    for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
+        const int k = sl + q * W;
+        if (k < kStencil) sh.su[t][k] = mykeys[q] == INT32_MAX ? (int16_t)-1 : (int16_t)upper_idx(sh.keys, nu, mykeys[q]);
+    }
+    if (nslot > kSlotMax) {
+        if (tid == 0) latch(st, 11 /*HALO_OVERFLOW*/, nslot);
+        if (active && sl == 0) nn[i] = 0;
+        if (tid == 0) halo_n[tile] = 0;
+        __syncthreads();
+        return;
+    }
+    for (int q = tid; q < (nslot + 31) / 32; q += NT) sh.used[q] = 0u;
 
-        // ---- 2./3. stage chunks, scan each row's stencil ------------------------
-        int32_t part[kMaxBondCap];
-        if constexpr (EXCL) {
+    // ---- 2./3. stage chunks, scan each row's stencil --------------------------
+    int32_t part[kMaxBondCap];
+    if constexpr (EXCL) {
 #pragma unroll
-            for (int b = 0; b < kMaxBondCap; ++b) part[b] = -1;
-            if (active) {
-                const int64_t prow = i * S.bond_stride;
-                for (int b = 0; b < S.bond_cap && b < kMaxBondCap; ++b) part[b] = ptag[prow + b];
-            }
+        for (int b = 0; b < kMaxBondCap; ++b) part[b] = -1;
+        if (active) {
+            const int64_t prow = i * S.bond_stride;
+            for (int b = 0; b < S.bond_cap && b < kMaxBondCap; ++b) part[b] = ptag[prow + b];
         }
-        const int64_t rowbase = nl0 + (int64_t)(r >> 6) * cap * kTile + (r & 63);
-        const bool fx_ = px && bx < 3, fy_ = py && by < 3, fz_ = pz && bz < 3;
-        const bool few = fx_ || fy_ || fz_;
-        const bool few_axis[3] = {fx_, fy_, fz_};
-        // offset of the particle inside its cell and the cell widths (FP32),
-        // for the conservative per-cell distance test
-        const float cellw[3] = {(float)(Lx / bx), (float)(Ly / by), (float)(Lz / bz)};
-        const float frel[3] = {(float)(xi.x - S.lo[0]) - (float)ci[0] * cellw[0],
-                               (float)(xi.y - S.lo[1]) - (float)ci[1] * cellw[1],
-                               (float)(xi.z - S.lo[2]) - (float)ci[2] * cellw[2]};
-        const float rl2f = (float)rl2 * 1.0001f + 1e-3f;
-        int ntot = 0;
-        for (int q0 = 0; q0 < nslot; q0 += kChunk) {
-            const int q1 = q0 + kChunk < nslot ? q0 + kChunk : nslot;
+    }
+    const int64_t rowbase = nl0 + (int64_t)(r >> 6) * cap * kTile + (r & 63);
+    const bool fx_ = px && bx < 3, fy_ = py && by < 3, fz_ = pz && bz < 3;
+    const bool few = fx_ || fy_ || fz_;
+    const bool few_axis[3] = {fx_, fy_, fz_};
+    // offset of the particle inside its cell and the cell widths (FP32),
+    // for the conservative per-cell distance test
+    const float cellw[3] = {(float)(Lx / bx), (float)(Ly / by), (float)(Lz / bz)};
+    const float frel[3] = {(float)(xi.x - S.lo[0]) - (float)ci[0] * cellw[0],
+                           (float)(xi.y - S.lo[1]) - (float)ci[1] * cellw[1],
+                           (float)(xi.z - S.lo[2]) - (float)ci[2] * cellw[2]};
+    const float rl2f = (float)rl2 * 1.0001f + 1e-3f;
+    // whether a stencil cell's nearest face lies beyond r_list of the row (FP32
+    // with a relative margin: it never drops a cell that can hold a neighbour)
+    auto out_of_reach = [&](int k) {
+        const int ox = k % 3, oy = (k / 3) % 3, oz = k / 9;
+        const int offs[3] = {S.st[0][ox < S.nst[0] ? ox : 0], S.st[1][oy < S.nst[1] ? oy : 0],
+                             S.st[2][oz < S.nst[2] ? oz : 0]};
+        float g2 = 0.f;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            if (offs[a] == 0 || few_axis[a]) continue;
+            const float g = offs[a] < 0 ? frel[a] : cellw[a] - frel[a];
+            g2 += g > 0.f ? g * g : 0.f;
+        }
+        return g2 > rl2f;
+    };
+    int ntot = 0;
+    if constexpr (CH > 0) {
+        for (int q0 = 0; q0 < nslot; q0 += CH) {
+            const int q1 = q0 + CH < nslot ? q0 + CH : nslot;
             __syncthreads();
-            for (int q = q0 + tid; q < q1; q += kBuildThreads) {
-                const int u = upper_idx(sh.ustart, nu, q);
+            for (int q = q0 + tid; q < q1; q += NT) {
+                const int u = upper_idx16(sh.ustart, nu, q);
                 const int32_t j = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
                 const double4 xj = pos[j];
-                sh.cx[q - q0] = xj.x;
-                sh.cy[q - q0] = xj.y;
-                sh.cz[q - q0] = xj.z;
-                sh.cj[q - q0] = j;
+                sh.stage.cx[q - q0] = xj.x;
+                sh.stage.cy[q - q0] = xj.y;
+                sh.stage.cz[q - q0] = xj.z;
+                sh.stage.cj[q - q0] = j;
             }
             __syncthreads();
             if (!active) continue;
             for (int k = 0; k < kStencil; ++k) {
                 const int u = sh.su[t][k];
                 if (u < 0) continue;
-                // skip a neighbour cell whose nearest face lies beyond r_list
-                // (FP32 with a relative margin: it never drops a cell that can
-                // hold a neighbour)
-                {
-                    const int ox = k % 3, oy = (k / 3) % 3, oz = k / 9;
-                    float g2 = 0.f;
-                    const int offs[3] = {S.st[0][ox < S.nst[0] ? ox : 0], S.st[1][oy < S.nst[1] ? oy : 0],
-                                         S.st[2][oz < S.nst[2] ? oz : 0]};
-#pragma unroll
-                    for (int a = 0; a < 3; ++a) {
-                        if (offs[a] == 0 || few_axis[a]) continue;
-                        const float g = offs[a] < 0 ? frel[a] : cellw[a] - frel[a];
-                        g2 += g > 0.f ? g * g : 0.f;
-                    }
-                    if (g2 > rl2f) continue;
-                }
+                if (out_of_reach(k)) continue;
                 const int code = sh.sm[t][k];
                 const double sx = Lx * (double)(code % 3 - 1);
                 const double sy = Ly * (double)((code / 3) % 3 - 1);
@@ -433,16 +445,16 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
                     int qq[2];
                     int32_t jj[2];
                     double ddx[2], ddy[2], ddz[2];
-#pragma unroll
+    #pragma unroll
                     for (int v = 0; v < 2; ++v) {
                         qq[v] = k0 + sl + v * W;
                         const int qs = (qq[v] < a1 ? qq[v] : a0) - q0;
-                        jj[v] = sh.cj[qs];
-                        ddx[v] = sh.cx[qs] - xi.x;
-                        ddy[v] = sh.cy[qs] - xi.y;
-                        ddz[v] = sh.cz[qs] - xi.z;
+                        jj[v] = sh.stage.cj[qs];
+                        ddx[v] = sh.stage.cx[qs] - xi.x;
+                        ddy[v] = sh.stage.cy[qs] - xi.y;
+                        ddz[v] = sh.stage.cz[qs] - xi.z;
                     }
-#pragma unroll
+    #pragma unroll
                     for (int v = 0; v < 2; ++v) {
                         if (few) {
                             // fewer than 3 cells: several images share a cell, take the nearest
@@ -458,12 +470,12 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
                         if constexpr (EXCL) {
                             if (hit[v]) {
                                 const int32_t tj = tag[jj[v]];
-#pragma unroll
+    #pragma unroll
                                 for (int b = 0; b < kMaxBondCap; ++b) hit[v] = hit[v] && (part[b] != tj);
                             }
                         }
                     }
-#pragma unroll
+    #pragma unroll
                     for (int v = 0; v < 2; ++v) {
                         const uint64_t mask = __ballot(hit[v]) & seg;
                         if (hit[v]) {
@@ -476,57 +488,166 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
                 }
             }
         }
-        if (active && sl == 0) atomicMax(&sh.info[2], ntot < cap ? ntot : cap);
-        __syncthreads();
-        // ---- 4. halo numbering and row rewrite ---------------------------------
-        const int nwords = (nslot + 31) / 32;
-        for (int q = tid; q < nwords; q += kBuildThreads) sh.wpre[q] = __popc(sh.used[q]);
-        __syncthreads();
-        const int nhalo = block_scan8(sh.wpre, nwords, sh.scan);
-        if (nhalo > halo_cap) {
-            if (tid == 0) latch(st, 11 /*HALO_OVERFLOW*/, nhalo);
-            if (active && sl == 0) nn[i] = 0;
-            if (tid == 0) halo_n[tile] = 0;
-            __syncthreads();
-            continue;
+    } else {
+        // Rows far apart share few cells: each row's W lanes read the members
+        // of its own stencil, one run over all cells, V loads in flight.
+        constexpr int V = 4;
+#pragma unroll
+        for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
+            const int k = sl + q * W;
+            if (k < kStencil && sh.su[t][k] >= 0 && out_of_reach(k)) sh.su[t][k] = (int16_t)-1;
         }
-        // halo list: row number of every used member, in staging order
-        int32_t *hl = halo + (int64_t)tile * halo_cap;
-        for (int q = tid; q < nslot; q += kBuildThreads) {
-            const uint32_t word = sh.used[q >> 5];
-            if (word & (1u << (q & 31))) {
-                const int u = upper_idx(sh.ustart, nu, q);
-                const int h = sh.wpre[q >> 5] + __popc(word & ((1u << (q & 31)) - 1u));
-                hl[h] = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
+        __syncthreads();
+        int k = -1, start = 0, end = 0, u = 0;  // the stencil cell of this lane's member, its place in the run
+        for (int base = 0;; base += V * W) {
+            bool ok[V];
+            int qq[V], code[V];
+            int32_t jj[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const int x = base + v * W + sl;
+                while (k < kStencil && x >= end) {
+                    ++k;
+                    start = end;
+                    if (k < kStencil) {
+                        u = sh.su[t][k];
+                        if (u >= 0) end += sh.ustart[u + 1] - sh.ustart[u];
+                    }
+                }
+                ok[v] = k < kStencil;
+                qq[v] = 0;
+                code[v] = 13;
+                int64_t at = 0;
+                if (ok[v]) {
+                    qq[v] = sh.ustart[u] + (x - start);
+                    code[v] = sh.sm[t][k];
+                    at = (cell0 + sh.keys[u]) * cell_cap + (x - start);
+                }
+                jj[v] = cell_idx[at];
+            }
+            if (__ballot(ok[0]) == 0) break;  // lanes ahead of the first are past the end as well
+            double ddx[V], ddy[V], ddz[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                if (!ok[v]) jj[v] = (int32_t)i;
+                ddx[v] = pos[jj[v]].x - xi.x;
+                ddy[v] = pos[jj[v]].y - xi.y;
+                ddz[v] = pos[jj[v]].z - xi.z;
+            }
+#pragma unroll
+            for (int v = 0; v < V; ++v) {
+                const double sx = Lx * (double)(code[v] % 3 - 1);
+                const double sy = Ly * (double)((code[v] / 3) % 3 - 1);
+                const double sz = Lz * (double)(code[v] / 9 - 1);
+                ddx[v] = fx_ ? min_image(ddx[v], Lx, iLx) : ddx[v] - sx;
+                ddy[v] = fy_ ? min_image(ddy[v], Ly, iLy) : ddy[v] - sy;
+                ddz[v] = fz_ ? min_image(ddz[v], Lz, iLz) : ddz[v] - sz;
+                bool hit = ok[v] && jj[v] != (int32_t)i && norm2_exact(ddx[v], ddy[v], ddz[v]) < rl2;
+                if constexpr (EXCL) {
+                    if (hit) {
+                        const int32_t tj = tag[jj[v]];
+#pragma unroll
+                        for (int b = 0; b < kMaxBondCap; ++b) hit = hit && (part[b] != tj);
+                    }
+                }
+                const uint64_t mask = __ballot(hit) & seg;
+                if (hit) {
+                    const int p = ntot + __popcll(mask & below);
+                    if (p < cap) nlist[rowbase + (int64_t)p * kTile] = (uint16_t)qq[v];
+                    atomicOr(&sh.used[qq[v] >> 5], 1u << (qq[v] & 31));
+                }
+                ntot += __popcll(mask);
             }
         }
-        if (tid == 0) {
-            halo_n[tile] = (int32_t)((uint32_t)nhalo | ((uint32_t)sh.info[2] << 16) | (sh.info[1] ? 0x80000000u : 0u));
-            // per-pair images or a halo beyond the force pass's LDS staging
-            if (sh.info[1] || nhalo > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
-        }
-        __threadfence_block();
-        __syncthreads();
-        if (active) {
-            const int n = ntot < cap ? ntot : cap;
-            for (int k = sl; k < n; k += 2 * W) {
-                const int64_t a = rowbase + (int64_t)k * kTile;
-                const int64_t b = a + (int64_t)W * kTile;
-                const bool has_b = k + W < n;
-                const int qa = nlist[a];
-                const int qb = has_b ? nlist[b] : 0;
-                const uint32_t wa = sh.used[qa >> 5], wb = sh.used[qb >> 5];
-                nlist[a] = (uint16_t)(sh.wpre[qa >> 5] + __popc(wa & ((1u << (qa & 31)) - 1u)));
-                if (has_b) nlist[b] = (uint16_t)(sh.wpre[qb >> 5] + __popc(wb & ((1u << (qb & 31)) - 1u)));
-            }
-            if (sl == 0) {
-                nn[i] = n;
-                xbuild[i] = xi;
-                if (ntot > cap) latch(st, 5 /*NLIST_OVERFLOW*/, ntot);
-            }
-        }
-        __syncthreads();
     }
+    if (active && sl == 0) atomicMax(&sh.info[2], ntot < cap ? ntot : cap);
+    __syncthreads();
+    // ---- 4. halo numbering and row rewrite -------------------------------------
+    const int nwords = (nslot + 31) / 32;
+    int nhalo;
+    {
+        constexpr int kPer = (kSlotMax / 32 + NT - 1) / NT;
+        int n[kPer], c = 0;
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int q = kPer * tid + k;
+            n[k] = q < nwords ? __popc(sh.used[q]) : 0;
+            c += n[k];
+        }
+        int p = block_rank<NT>(c, sh.scan, nhalo);
+        // (the staged members are no longer read)
+#pragma unroll
+        for (int k = 0; k < kPer; ++k) {
+            const int q = kPer * tid + k;
+            if (q < nwords) sh.tmp[q] = p;
+            p += n[k];
+        }
+    }
+    __syncthreads();
+    if (nhalo > halo_cap) {
+        if (tid == 0) latch(st, 11 /*HALO_OVERFLOW*/, nhalo);
+        if (active && sl == 0) nn[i] = 0;
+        if (tid == 0) halo_n[tile] = 0;
+        __syncthreads();
+        return;
+    }
+    // halo list: row number of every used member, in staging order
+    int32_t *hl = halo + (int64_t)tile * halo_cap;
+    for (int q = tid; q < nslot; q += NT) {
+        const uint32_t word = sh.used[q >> 5];
+        if (word & (1u << (q & 31))) {
+            const int u = upper_idx16(sh.ustart, nu, q);
+            const int h = sh.tmp[q >> 5] + __popc(word & ((1u << (q & 31)) - 1u));
+            hl[h] = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
+        }
+    }
+    if (tid == 0) {
+        halo_n[tile] = (int32_t)((uint32_t)nhalo | ((uint32_t)sh.info[2] << 16) | (sh.info[1] ? 0x80000000u : 0u));
+        // per-pair images or a halo beyond the force pass's LDS staging
+        if (sh.info[1] || nhalo > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (active) {
+        const int n = ntot < cap ? ntot : cap;
+        for (int k = sl; k < n; k += 2 * W) {
+            const int64_t a = rowbase + (int64_t)k * kTile;
+            const int64_t b = a + (int64_t)W * kTile;
+            const bool has_b = k + W < n;
+            const int qa = nlist[a];
+            const int qb = has_b ? nlist[b] : 0;
+            const uint32_t wa = sh.used[qa >> 5], wb = sh.used[qb >> 5];
+            nlist[a] = (uint16_t)(sh.tmp[qa >> 5] + __popc(wa & ((1u << (qa & 31)) - 1u)));
+            if (has_b) nlist[b] = (uint16_t)(sh.tmp[qb >> 5] + __popc(wb & ((1u << (qb & 31)) - 1u)));
+        }
+        if (sl == 0) {
+            nn[i] = n;
+            xbuild[i] = xi;
+            if (ntot > cap) latch(st, 5 /*NLIST_OVERFLOW*/, ntot);
+        }
+    }
+    __syncthreads();
+}
+
+// The general build as a launch of its own, behind the line-ordered build.
+template <bool EXCL>
+__global__ __launch_bounds__(kBuildThreads) void k_build_tile(
+    const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys,
+    const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
+    const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
+    uint16_t *__restrict__ nlist, int32_t *__restrict__ nn, int cap, int32_t *__restrict__ halo,
+    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild,
+    const int32_t *__restrict__ list, const int32_t *__restrict__ list_n, int halo_lds,
+    int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, const int32_t *__restrict__ flag, Status *st)
+{
+    if (*flag == 0) return;
+    const int ntiles = *list_n;
+    if ((int)blockIdx.x >= ntiles) return;
+    __shared__ GeneralShared<kChunk> sh;
+    for (int it = blockIdx.x; it < ntiles; it += gridDim.x)
+        general_tile<EXCL, kBuildThreads, kChunk>(sh, list[it], sys, tprefix, n_sys, pos, tag, ptag, cell_size,
+                                                  cell_idx, cell_cap, nlist, nn, cap, halo, halo_n, halo_cap, xbuild,
+                                                  halo_lds, rare_list, rare_n, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -559,7 +680,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
 //     in LDS and written out coalesced.
 // Tiles that do not fit (a frame wider than a periodic box, fewer than three
 // cells on a periodic axis, too many distinct cells or members) are appended
-// to a device list and built by k_build_tile.
+// to a device list and built in general.
 
 constexpr int kFastThreads = 256;    // threads per workgroup by default (4 waves)
 constexpr int kBoxDense = 160;       // cells of a frame box looked at without marking the stencils first
@@ -623,6 +744,11 @@ struct ExShared {
 // 16 banks apart, so that one read of 16 members' four components meets every
 // bank once.
 constexpr int build_astride(int kc) { return kc + 16 + (64 - kc % 64) % 64; }
+template <int NT>
+constexpr int kExShared = (int)((sizeof(ExShared<NT>) + 15) / 16 * 16);
+template <int NT, int LPR>
+constexpr int kFastShared = (int)((sizeof(FastShared<NT, LPR>) + 15) / 16 * 16);
+
 
 // The plan of one tile per wave (workgroups of one wave: no block barriers
 // wait on other waves, so many tiles are in flight per CU).  Lane t takes
@@ -1010,6 +1136,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     int32_t *__restrict__ halo, int32_t *__restrict__ halo_n, int halo_cap, const char *__restrict__ plan,
     int64_t plan_stride, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n,
     int32_t *__restrict__ tile_ctr, int32_t *__restrict__ cell_count, int64_t n_cells,
+    const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
+    double4 *__restrict__ xbuild, const int32_t *__restrict__ slow_list, const int32_t *__restrict__ slow_n,
     const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *build_count, Status *st)
 {
     if (*flag == 0) return;
@@ -1022,15 +1150,28 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     constexpr int kRounds = 5;                     // staging reads of a lane in flight
     constexpr int kSegWave = kWave / kSeg;         // segments a wave stages at once
     static_assert(kWords * kWaves * 4 <= kWave, "one-wave scan of the marks");
-    __shared__ Sh sh;
-    __shared__ typename std::conditional<EXCL, ExShared<NT>, char>::type ex;
-    // the staged positions, then (all distances taken) the rows' halo indices
-    // [kTile][rstride]
-    extern __shared__ float lds_a[];
+    // LDS: this structure and the exclusions', then the staged positions in
+    // whose place (all distances taken) the rows' halo indices [kTile][rstride]
+    // are put together
+    extern __shared__ float4 lds_all[];
+    Sh &sh = *reinterpret_cast<Sh *>(lds_all);
+    using Ex = ExShared<NT>;
+    Ex &ex = *reinterpret_cast<Ex *>(reinterpret_cast<char *>(lds_all) + kFastShared<NT, LPR>);
+    float *const lds_a =
+        reinterpret_cast<float *>(reinterpret_cast<char *>(lds_all) + kFastShared<NT, LPR> + (EXCL ? kExShared<NT> : 0));
     uint16_t *const srows = reinterpret_cast<uint16_t *>(lds_a);
     int tid = threadIdx.x;
     const int wv = uni(tid >> 6);
     if (blockIdx.x == 0 && tid == 0) atomicAdd(build_count, 1);
+
+    // The tiles that the plan passed on, first: they take longest, and beside
+    // the framed ones their time hides (as a launch of their own after these
+    // they added it to most builds, and an empty launch to every step).
+    for (int it = blockIdx.x; it < *slow_n; it += gridDim.x)
+        general_tile<EXCL, NT, 0>(*reinterpret_cast<GeneralShared<0> *>(lds_all), slow_list[it],
+                                              sys, tprefix, n_sys, pos, tag, ptag, cell_size, cell_idx, cell_cap,
+                                              nlist, nn, cap, halo, halo_n, halo_cap, xbuild, halo_lds, rare_list,
+                                              rare_n, st);
 
     // Each die's workgroups walk one contiguous run of tiles.  With one
     // system every tile of the run is built, and the tiles are handed out one
@@ -1489,12 +1630,15 @@ size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows)
 
 int cell_xf_slots(int cell_cap) { return cell_xf_stride(cell_cap); }
 
-// LDS beside FastShared: the staged positions, and in their place the rows.
+// LDS of the framed launch: the shared structures, the staged positions (in
+// their place the rows), or a tile of the general build.
 template <bool EXCL, int NT, int LPR>
 static int fast_dyn(int cap)
 {
     const int rows = kTile * nlist_row_stride(cap) * 2;
-    return std::max(rows, 4 * build_astride(build_chunk(LPR)) * (int)sizeof(float));
+    const int framed = kFastShared<NT, LPR> + (EXCL ? kExShared<NT> : 0) +
+                       std::max(rows, 4 * build_astride(build_chunk(LPR)) * (int)sizeof(float));
+    return std::max(framed, (int)sizeof(GeneralShared<0>));
 }
 
 template <bool EXCL, int NT, int LPR>
@@ -1522,7 +1666,8 @@ static void fast_inst(const LaunchCtx &L, const double4 *pos, const int32_t *tag
     hipLaunchKernelGGL((k_build_fast<EXCL, NT, LPR>), dim3(blocks), dim3(NT), dyn, L.stream, L.sys, L.tprefix_local,
                        L.n_sys, L.tiles_local, pos, tag, L.ptag, L.bond_stride, L.cell_xf, L.nlist, L.nn, L.nlist_cap, rs, L.halo,
                        L.halo_n, L.halo_cap, L.plan, plan_stride(L.seg_cap), L.halo_lds, L.rare_list, L.rare_n,
-                       L.tile_ctr, L.cell_count, L.n_cells, L.flag, L.sflag, L.build_count, L.status);
+                       L.tile_ctr, L.cell_count, L.n_cells, L.cell_size, L.cell_idx, L.cell_cap, L.xbuild, L.slow_list,
+                       L.slow_n, L.flag, L.sflag, L.build_count, L.status);
 }
 
 template <bool EXCL>
@@ -1550,23 +1695,20 @@ void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, in
     }
     const int blocks = capped(L.tiles_local);
     const int rs = nlist_row_stride(L.nlist_cap);
-    if (L.has_bonds) {
-        if (L.line_rows) launch_build_lines(L, pos, tag, block);
-        else fast_shape<true>(L, pos, tag, blocks, rs, w, block);
-        hipLaunchKernelGGL(k_build_tile<true>, dim3(blocks), dim3(kBuildThreads), 0, L.stream, L.sys,
-                           L.tprefix_local, L.n_sys, L.tiles_local, pos, tag, L.ptag, L.cell_size,
-                           L.cell_idx, L.cell_cap, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
-                           L.halo_cap, L.xbuild, L.slow_list, L.slow_n, L.halo_lds, L.rare_list, L.rare_n, L.flag,
-                           nullptr, L.status);
-    } else {
-        if (L.line_rows) launch_build_lines(L, pos, tag, block);
+    if (!L.line_rows) {
+        if (L.has_bonds) fast_shape<true>(L, pos, tag, blocks, rs, w, block);
         else fast_shape<false>(L, pos, tag, blocks, rs, w, block);
-        hipLaunchKernelGGL(k_build_tile<false>, dim3(blocks), dim3(kBuildThreads), 0, L.stream, L.sys,
-                           L.tprefix_local, L.n_sys, L.tiles_local, pos, tag, L.ptag, L.cell_size,
-                           L.cell_idx, L.cell_cap, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
-                           L.halo_cap, L.xbuild, L.slow_list, L.slow_n, L.halo_lds, L.rare_list, L.rare_n, L.flag,
-                           nullptr, L.status);
+        return;
     }
+    launch_build_lines(L, pos, tag, block);
+    auto general = [&](auto k) {
+        hipLaunchKernelGGL(k, dim3(blocks), dim3(kBuildThreads), 0, L.stream, L.sys, L.tprefix_local, L.n_sys, pos, tag,
+                           L.ptag, L.cell_size, L.cell_idx, L.cell_cap, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
+                           L.halo_cap, L.xbuild, L.slow_list, L.slow_n, L.halo_lds, L.rare_list, L.rare_n, L.flag,
+                           L.status);
+    };
+    if (L.has_bonds) general(k_build_tile<true>);
+    else general(k_build_tile<false>);
 }
 
 }  // namespace md

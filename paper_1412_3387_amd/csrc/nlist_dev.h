@@ -171,6 +171,27 @@ __device__ __forceinline__ int wave_scan_incl(int v)
     return dpp_add<0x143, 0xC>(v);  // row_bcast 31 into rows 2 and 3
 }
 
+// Sum of v over the threads before this one in a block of NT; total gets the
+// sum over all.  scan holds NT / 64 words in LDS.
+template <int NT>
+__device__ __forceinline__ int block_rank(int v, int32_t *scan, int &total)
+{
+    constexpr int NW = NT / kWave;
+    const int w = threadIdx.x >> 6;
+    const int incl = wave_scan_incl(v);
+    if (lane_id() == kWave - 1) scan[w] = incl;
+    __syncthreads();
+    int before = 0;
+    total = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+        before += q < w ? scan[q] : 0;
+        total += scan[q];
+    }
+    __syncthreads();  // scan free again
+    return before + incl - v;
+}
+
 // Floats as integers of the same order, and back (NaN apart).
 __device__ __forceinline__ int float_order(float v)
 {

@@ -74,3 +74,28 @@ def test_bonded_lattice_at_the_list_radius(orc, B, bond_cap):
     ctx.build_nlist(True)
     ctx.check()
     assert neighbor_sets_equal(orc, ctx, pos, m.L, 2.0 ** (1.0 / 6.0), 0.4, bonds=bonds.astype(np.int32)) == []
+
+
+# boxes with more cells than the bitmap of stencil cells covers (131,072) and
+# with fewer, two cells across an axis (nearest images), one row in the last tile
+@pytest.mark.parametrize("n,L,shape", [(5000, (160.0, 161.0, 158.0), (64, 256)), (5000, (147.0, 147.0, 147.0), (64, 256)),
+                                       (1985, (6.5, 30.0, 12.0), (64, 256)), (1985, (6.5, 30.0, 12.0), (32, 512)),
+                                       (4097, (18.0, 18.0, 18.0), (64, 512)), (65, (9.0, 6.0, 6.0), (32, 256))])
+@pytest.mark.parametrize("bonded", [False, True])
+def test_scattered_rows_in_the_general_build(orc, B, n, L, shape, bonded):
+    """Rows in random order: no tile fits one frame, every row reads its own
+    stencil, in the same launch as the framed tiles."""
+    rng = np.random.default_rng(n)
+    L = np.array(L)
+    pos = inputs.wrap(rng.uniform(0, 1, (n, 3)) * L, L)
+    sysd = dict(pos=pos, vel=np.zeros_like(pos), L=L)
+    bonds = None
+    if bonded:
+        bonds = sysd["bonds"] = np.stack([np.arange(0, n - 1, 2), np.arange(1, n, 2)], axis=1).astype(np.int32)
+    ctx = B.Context([B.ModelParams(precision=B.FP64, sort_period=0, nlist_cap=256, tpp_nlist=shape[0],
+                                   block_nlist=shape[1], bond_cap=2 if bonded else 0, fene_R0=400.0)], [sysd])
+    ctx.build_nlist(True)
+    ctx.check()
+    assert ctx.general_tiles() > 0
+    kw = dict(bonds=bonds) if bonded else {}
+    assert neighbor_sets_equal(orc, ctx, pos, L, 2.5, 0.4, **kw) == []
