@@ -153,14 +153,12 @@ typedef struct {
     int32_t pad_;
 } hoomd_params;
 
-/* Launches of the force pass.  SPLIT: a launch over the tiles whose halo fits
- * the LDS stage of a workgroup sized for full occupancy, then a small launch
- * over the rest (tiles that need per-pair images, or larger halos).  ONE: a
- * single launch of the second kind over every tile: no occupancy budget, but
- * one launch latency per pass instead of two.  AUTO: ONE when every
- * workgroup of that launch is resident at once (a context of few tiles: a
- * small system, a subdomain), else SPLIT.  The results are the same bit for
- * bit. */
+/* LDS stage of the force pass.  SPLIT: sized for full occupancy; the tiles
+ * that need per-pair images, or have halos beyond that stage, go first in the
+ * launch.  ONE: as large a stage as the halos ask for, up to 40 KB, and the
+ * tiles in order.  AUTO: ONE when every workgroup of the launch is resident at
+ * once (a context of few tiles: a small system, a subdomain), else SPLIT.  The
+ * results are the same bit for bit. */
 enum { HOOMD_FORCE_AUTO = 0, HOOMD_FORCE_SPLIT = 1, HOOMD_FORCE_ONE = 2 };
 
 /* Integrators (Sec. 3: NVE by velocity Verlet; Sec. 6.1: the weak-scaling LJ
@@ -434,8 +432,8 @@ int hoomd_build_count(hoomd_ctx *ctx, int64_t *builds);
  *   general_tiles: int32 count, over all systems, of the tiles that the
  *   last build handed from the framed build to the general one;
  *   rare_tiles: int32 count, over all systems, of the tiles that the force
- *   pass handles in its second launch (per-pair images, or a halo above
- *   halo_lds, the entries the first launch stages in LDS). */
+ *   pass takes first in its launch (per-pair images, or a halo above
+ *   halo_lds, the entries it stages in LDS). */
 typedef struct {
     const uint16_t *nlist;
     const int32_t *nn;

@@ -18,6 +18,7 @@
 // integrator are FP64.  With MIXED the pair and bond arithmetic after the
 // cut-off test is FP32 (each pair's F/r is widened before it is summed);
 // energies and virials are summed in FP64.
+#include <algorithm>
 #include <type_traits>
 
 #include "device.h"
@@ -32,6 +33,35 @@ template <> __device__ __forceinline__ double recip<double>(double x) { return 1
 template <typename T> __device__ __forceinline__ T tsqrt(T x);
 template <> __device__ __forceinline__ float tsqrt<float>(float x) { return __builtin_sqrtf(x); }
 template <> __device__ __forceinline__ double tsqrt<double>(double x) { return __builtin_sqrt(x); }
+
+// sqrt of a positive finite x, the correctly rounded result as
+// __builtin_sqrtf has it: the root estimate (within 1 ulp) is moved by one ulp
+// where the sign of a residual says so; the residuals are exact enough while x
+// is far above the underflow threshold.
+template <typename T> __device__ __forceinline__ T pair_sqrt(T x) { return tsqrt<T>(x); }
+template <> __device__ __forceinline__ float pair_sqrt<float>(float x)
+{
+    if (x < 0x1p-90f) return __builtin_sqrtf(x);
+    const float s = __builtin_amdgcn_sqrtf(x);
+    const float lo = __int_as_float(__float_as_int(s) - 1), hi = __int_as_float(__float_as_int(s) + 1);
+    float r = __builtin_fmaf(-lo, s, x) <= 0.f ? lo : s;
+    return __builtin_fmaf(-hi, s, x) > 0.f ? hi : r;
+}
+
+// A per-system constant in scalar registers from here on (else the compiler
+// reads it anew, and waits for it, for every pair).
+__device__ __forceinline__ uint32_t pinned(uint32_t x)
+{
+    uint32_t b;
+    // (wait states between a vector write, the lane read and the scalar's use)
+    asm volatile("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 1" : "=s"(b) : "v"(x));
+    return b;
+}
+__device__ __forceinline__ float pinned(float x) { return __uint_as_float(pinned(__float_as_uint(x))); }
+__device__ __forceinline__ double pinned(double x)
+{
+    return __hiloint2double((int)pinned((uint32_t)__double2hiint(x)), (int)pinned((uint32_t)__double2loint(x)));
+}
 
 template <typename T> __device__ __forceinline__ T tlog(T x);
 template <> __device__ __forceinline__ float tlog<float>(float x) { return __logf(x); }
@@ -66,14 +96,16 @@ __host__ __device__ constexpr int halo_entry_bytes(int pot) { return pot == PAIR
 // Rows may be read this many entries past their end (two passes of the
 // widest split): the neighbour list is padded by as many tile columns.
 constexpr int kRowOverRead = 2 * 4 * 16;
-constexpr int kRareGrid = 1024;  // workgroups of the launch over the rare tiles
-constexpr size_t kRareLds = 40 * 1024;  // LDS of a workgroup of that launch, at most (four per CU)
+constexpr size_t kWideLds = 40 * 1024;  // LDS of a workgroup where all are resident, at most (four per CU)
+constexpr int kAhead = 512;      // workgroups ahead of the others for the tiles that take longest
 
-// One tile of the fused step.  RARE selects the code for tiles with a
-// per-pair image or a halo larger than the LDS staging area; the main
-// launch leaves those to a second, small launch, so that its own code needs
-// fewer registers (more waves per CU).
-template <int W, bool MIXED, int POT, bool LOG, bool RARE>
+// One tile of the fused step.  A tile with per-pair images, or a halo larger
+// than the LDS stage, takes a pair loop of its own, two neighbours at a time:
+// the other loop, four at a time, sets the registers, and this one fits into
+// them.  (As a second launch with 128 registers those tiles cost each pass
+// that launch's latency, 8 to 24 us: LJ FP64 255,000 particles 55 + 9 us, now
+// 55; melt of 50,000 13 + 8, now 14; DPD FP64 100,000 36 + 12, now 39.)
+template <int W, bool MIXED, int POT, bool LOG>
 __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *__restrict__ sys,
                                            const int32_t *__restrict__ tprefix, int n_sys,
                                            const uint16_t *__restrict__ nlist,
@@ -81,7 +113,7 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
                                            const int32_t *__restrict__ halo,
                                            const int32_t *__restrict__ halo_n, int halo_cap, int halo_lds,
                                            const int32_t *__restrict__ prow,
-                                           const double4 *__restrict__ xbuild,
+                                           const double4 *__restrict__ xbuild, const double4 *__restrict__ tref,
                                            double *__restrict__ partials, Status *st, const ForceLaunch &a)
 {
     using T = typename std::conditional<MIXED, float, double>::type;
@@ -121,6 +153,7 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
 
     // ---- the row's first pass, then the halo ------------------------------
     constexpr int U = 4;
+    constexpr int RU = 2;
     const int32_t hn = halo_n[tile];
     const int nh = hn & 0xFFFF;
     const bool per_pair = hn < 0;  // tile too wide for one image per halo entry
@@ -132,10 +165,12 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
     int hnext[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) hnext[u] = rowp[(int64_t)(sl + u * W) * kTile];
-    const double4 xref = a.pos[row0 + r0];
+    // (mixed-precision DPD, whose builds keep row 0 as the reference: the bits
+    // of its FP32 pair terms depend on the images' rounding)
+    const double4 xref = MIXED && POT == PAIR_DPD ? a.pos[row0 + r0] : tref[tile];
     const int32_t *hl = halo + (int64_t)tile * halo_cap;
-    // halo entry h: its position moved to the image nearest the tile's first
-    // row (unless the tile needs per-pair images)
+    // halo entry h: its position moved to the image nearest the tile's
+    // reference point (unless the tile needs per-pair images)
     auto halo_pos = [&](int h, double &px, double &py, double &pz) {
         const double4 x = a.pos[hl[h]];
         px = x.x;
@@ -164,8 +199,8 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
     // before any gather, and every gather before any use, so a tile waits for
     // two memory round trips per batch instead of two per entry (indices past
     // the halo's end are clamped to its last entry and not stored)
-    constexpr int SB = 4;
     constexpr int NT = W * kWave;
+    constexpr int SB = 4;
     for (int h0 = tid; h0 < ns; h0 += SB * NT) {
         int32_t jb[SB];
 #pragma unroll
@@ -206,6 +241,7 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
             }
         }
     }
+    const bool common = !per_pair && nh <= halo_lds;
     __syncthreads();
 
     // the row's own position, moved to the same frame as the halo images
@@ -225,11 +261,81 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
     double fx = 0, fy = 0, fz = 0;
     double e = 0.0, vir = 0.0;
 
-    // four neighbours per pass: all LDS reads of a pass issue before any use.
-    // The per-pair image branch is taken once per tile, outside the loop.
-    auto pair_loop = [&](auto per_pair_tag, auto spill_tag) {
-        constexpr bool PP = decltype(per_pair_tag)::value;
-        constexpr bool OVF = decltype(spill_tag)::value;
+    // DPD: vector instructions bound the loop, a third of them Philox's
+    // products, so the constants sit in scalar registers and a product takes
+    // one instruction (mixed precision, 1,000,000 particles: 191 -> 167 us;
+    // the compiler read five constants from memory, and waited, for each pair)
+    T dA = 0, dgamma = 0, dsigma = 0, dinv_rc = 0, dinv_dt = 0;
+    uint32_t dseed = 0;
+    if constexpr (POT == PAIR_DPD) {
+        dA = pinned((T)S.dpd_A);
+        dgamma = pinned((T)S.dpd_gamma);
+        dsigma = pinned((T)S.dpd_sigma);
+        dinv_rc = pinned((T)S.dpd_inv_rc);
+        dinv_dt = pinned((T)S.dpd_inv_sqrt_dt);
+        dseed = pinned(S.dpd_seed);
+        step_key = pinned(step_key);
+    }
+    // one neighbour: halo entry hh at (dx, dy, dz) from the row
+    auto add_pair = [&](int hh, bool ok, double dx, double dy, double dz, auto beyond_tag) {
+        constexpr bool OVF = decltype(beyond_tag)::value;
+        // FP64 in both precisions; the FP64 path keeps the unfused,
+        // fixed-order sum of the reference, the mixed path fuses it
+        const double r2 = MIXED ? __fma_rn(dx, dx, __fma_rn(dy, dy, dz * dz))
+                                : norm2_exact(dx, dy, dz);
+        if constexpr (POT == PAIR_LJ || POT == PAIR_WCA) {
+            // branch-free: lanes outside the cut-off add zero
+            const bool in = ok && r2 < rc2;
+            const T ff = lj_pair<T, LOG>(r2, eps, sig2, shift, e, vir, in);
+            fx = __fma_rn((double)ff, dx, fx);
+            fy = __fma_rn((double)ff, dy, fy);
+            fz = __fma_rn((double)ff, dz, fz);
+            return;
+        }
+        if (ok && r2 < rc2) {
+            T ff;
+            {
+                if (r2 == 0.0) return;
+                const int h = hh;
+                const T tr2 = (T)r2;
+                const T rr = pair_sqrt<T>(tr2);
+                const T rinv = recip<T>(rr);
+                const T w = (T)1 - rr * dinv_rc;
+                double vx, vy, vz;
+                int32_t tj;
+                if (!OVF || h < halo_lds) {
+                    vx = hv[3 * h];
+                    vy = hv[3 * h + 1];
+                    vz = hv[3 * h + 2];
+                    tj = htag[h];
+                } else {
+                    const int32_t j = hl[h];
+                    const double4 vj = a.vel[j];
+                    vx = vj.x;
+                    vy = vj.y;
+                    vz = vj.z;
+                    tj = a.tag[j];
+                }
+                const T dvx = (T)(vi.x - vx), dvy = (T)(vi.y - vy), dvz = (T)(vi.z - vz);
+                const T rv = ((T)dx * dvx + (T)dy * dvy + (T)dz * dvz) * rinv;
+                const uint32_t bits = dpd_bits((uint32_t)ti, (uint32_t)tj, dseed, step_key);
+                const T uu = (T)bits * (T)(1.0 / 16777216.0);
+                const T theta = (T)1.7320508075688772 * ((T)2 * uu - (T)1);
+                const T mag = dA * w - dgamma * w * w * rv +
+                              dsigma * w * theta * dinv_dt;
+                ff = mag * rinv;
+                if constexpr (LOG) {
+                    e += 0.5 * S.dpd_A * S.dpd_rc * (double)(w * w);
+                    vir += (double)(ff * tr2);
+                }
+            }
+            fx = __fma_rn((double)ff, dx, fx);
+            fy = __fma_rn((double)ff, dy, fy);
+            fz = __fma_rn((double)ff, dz, fz);
+        }
+    };
+    if (common) {
+        // four neighbours per pass: all LDS reads of a pass issue before any use
         for (int k0 = sl; k0 < n; k0 += U * W) {
             int hh[U];
             bool ok[U];
@@ -244,97 +350,47 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
             double dx[U], dy[U], dz[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
+                const double *hp = reinterpret_cast<const double *>(reinterpret_cast<const char *>(hxyz) +
+                                                                    (uint32_t)hh[u] * 24u);
+                dx[u] = xs - hp[0];
+                dy[u] = ys - hp[1];
+                dz[u] = zs - hp[2];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) add_pair(hh[u], ok[u], dx[u], dy[u], dz[u], std::false_type{});
+        }
+    } else {
+        // a tile that needs per-pair images, or with entries beyond the stage
+        for (int k0 = sl; k0 < n; k0 += RU * W) {
+            double dx[RU], dy[RU], dz[RU];
+            int hh[RU];
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
+                const int kk = k0 + u * W;
+                hh[u] = kk < n ? (int)rowp[(int64_t)kk * kTile] : 0;
+            }
+#pragma unroll
+            for (int u = 0; u < RU; ++u) {
                 double px, py, pz;
-                if (!OVF || hh[u] < halo_lds) {
-                    const double *hp = reinterpret_cast<const double *>(
-                        reinterpret_cast<const char *>(hxyz) + (uint32_t)hh[u] * 24u);
-                    px = hp[0];
-                    py = hp[1];
-                    pz = hp[2];
+                if (hh[u] < halo_lds) {
+                    px = hxyz[3 * hh[u]];
+                    py = hxyz[3 * hh[u] + 1];
+                    pz = hxyz[3 * hh[u] + 2];
                 } else {
                     halo_pos(hh[u], px, py, pz);
                 }
                 dx[u] = xs - px;
                 dy[u] = ys - py;
                 dz[u] = zs - pz;
-            }
-            if constexpr (PP) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
+                if (per_pair) {
                     dx[u] = min_image(dx[u], Lx, iLx);
                     dy[u] = min_image(dy[u], Ly, iLy);
                     dz[u] = min_image(dz[u], Lz, iLz);
                 }
             }
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                // FP64 in both precisions; the FP64 path keeps the unfused,
-                // fixed-order sum of the reference, the mixed path fuses it
-                const double r2 = MIXED ? __fma_rn(dx[u], dx[u], __fma_rn(dy[u], dy[u], dz[u] * dz[u]))
-                                        : norm2_exact(dx[u], dy[u], dz[u]);
-                if constexpr (POT == PAIR_LJ || POT == PAIR_WCA) {
-                    // branch-free: lanes outside the cut-off add zero
-                    const bool in = ok[u] && r2 < rc2;
-                    const T ff = lj_pair<T, LOG>(r2, eps, sig2, shift, e, vir, in);
-                    fx = __fma_rn((double)ff, dx[u], fx);
-                    fy = __fma_rn((double)ff, dy[u], fy);
-                    fz = __fma_rn((double)ff, dz[u], fz);
-                    continue;
-                }
-                if (ok[u] && r2 < rc2) {
-                    T ff;
-                    {
-                        if (r2 == 0.0) continue;
-                        const int h = hh[u];
-                        const T tr2 = (T)r2;
-                        const T rr = tsqrt<T>(tr2);
-                        const T rinv = recip<T>(rr);
-                        const T w = (T)1 - rr * (T)S.dpd_inv_rc;
-                        double vx, vy, vz;
-                        int32_t tj;
-                        if (!OVF || h < halo_lds) {
-                            vx = hv[3 * h];
-                            vy = hv[3 * h + 1];
-                            vz = hv[3 * h + 2];
-                            tj = htag[h];
-                        } else {
-                            const int32_t j = hl[h];
-                            const double4 vj = a.vel[j];
-                            vx = vj.x;
-                            vy = vj.y;
-                            vz = vj.z;
-                            tj = a.tag[j];
-                        }
-                        const T dvx = (T)(vi.x - vx), dvy = (T)(vi.y - vy), dvz = (T)(vi.z - vz);
-                        const T rv = ((T)dx[u] * dvx + (T)dy[u] * dvy + (T)dz[u] * dvz) * rinv;
-                        const uint32_t bits = dpd_bits((uint32_t)ti, (uint32_t)tj, S.dpd_seed, step_key);
-                        const T uu = (T)bits * (T)(1.0 / 16777216.0);
-                        const T theta = (T)1.7320508075688772 * ((T)2 * uu - (T)1);
-                        const T mag = (T)S.dpd_A * w - (T)S.dpd_gamma * w * w * rv +
-                                      (T)S.dpd_sigma * w * theta * (T)S.dpd_inv_sqrt_dt;
-                        ff = mag * rinv;
-                        if constexpr (LOG) {
-                            e += 0.5 * S.dpd_A * S.dpd_rc * (double)(w * w);
-                            vir += (double)(ff * tr2);
-                        }
-                    }
-                    fx = __fma_rn((double)ff, dx[u], fx);
-                    fy = __fma_rn((double)ff, dy[u], fy);
-                    fz = __fma_rn((double)ff, dz[u], fz);
-                }
-            }
+            for (int u = 0; u < RU; ++u) add_pair(hh[u], k0 + u * W < n, dx[u], dy[u], dz[u], std::true_type{});
         }
-    };
-    if constexpr (RARE) {
-        if (nh > halo_lds) {
-            if (per_pair) pair_loop(std::true_type{}, std::true_type{});
-            else pair_loop(std::false_type{}, std::true_type{});
-        } else {
-            if (per_pair) pair_loop(std::true_type{}, std::false_type{});
-            else pair_loop(std::false_type{}, std::false_type{});
-        }
-    } else {
-        pair_loop(std::false_type{}, std::false_type{});
     }
 
     fx = segment_sum<W>(fx);
@@ -476,47 +532,45 @@ __device__ __forceinline__ void force_tile(int tile, double *lds, const SysDev *
     }
 }
 
-#define FORCE_ARGS                                                                                       \
-    const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys,                      \
-        const uint16_t *__restrict__ nlist, const int32_t *__restrict__ nn, int cap,                     \
-        const int32_t *__restrict__ halo, const int32_t *__restrict__ halo_n, int halo_cap, int halo_lds, \
-        const int32_t *__restrict__ prow,                                                               \
-        const double4 *__restrict__ xbuild, double *__restrict__ partials, Status *st,                   \
-        const int32_t *__restrict__ rare_list, const int32_t *__restrict__ rare_n, ForceLaunch a
-#define FORCE_PASS sys, tprefix, n_sys, nlist, nn, cap, halo, halo_n, halo_cap, halo_lds, prow, \
-                   xbuild, partials, st, a
+// Waves per SIMD that the common loop's registers allow (its code is to keep
+// them: an LJ launch of 2,000,000 rows takes 258 us with seven and 297 us with
+// spills inside the staging).
+constexpr int force_waves(bool mixed, int pot, bool log)
+{
+    return pot == PAIR_DPD ? (log ? 4 : 5) : mixed ? (log ? 6 : 7) : (log ? 5 : 6);
+}
 
-// Main launch: one workgroup per tile; rare tiles return at once.
+// One workgroup per tile.  With ahead > 0 that many workgroups go first, for
+// the tiles that the last build listed (per-pair images, or a halo beyond the
+// stage): they take longest, and at their places in the order the last of them
+// ends the launch late.  A longer list than that is left in place.
 template <int W, bool MIXED, int POT, bool LOG>
-__global__ __launch_bounds__(1024) void k_force(FORCE_ARGS)
+__global__ __launch_bounds__(W * kWave, force_waves(MIXED, POT, LOG)) void k_force(
+    const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys,
+    const uint16_t *__restrict__ nlist, const int32_t *__restrict__ nn, int cap, const int32_t *__restrict__ halo,
+    const int32_t *__restrict__ halo_n, int halo_cap, int halo_lds, const int32_t *__restrict__ prow,
+    const double4 *__restrict__ xbuild, const double4 *__restrict__ tref, double *__restrict__ partials, Status *st,
+    const int32_t *__restrict__ rare_list, const int32_t *__restrict__ rare_n, int ahead, ForceLaunch a)
 {
     extern __shared__ double lds[];
     if (a.flag_clear && blockIdx.x == 0) {
         if (threadIdx.x == 0) *a.flag_clear = 0;
         for (int q = threadIdx.x; q < n_sys; q += blockDim.x) a.sflag_clear[q] = 0;
     }
-    const int tile = die_tile(blockIdx.x, gridDim.x);
-    const int32_t hn = halo_n[tile];
-    if (hn < 0 || (hn & 0xFFFF) > halo_lds) return;
-    force_tile<W, MIXED, POT, LOG, false>(tile, lds, FORCE_PASS);
-}
-
-// The tiles the last build listed as rare (per-pair images or a halo larger
-// than the staging area), or, without a list, every local tile (the whole
-// pass in one launch).
-template <int W, bool MIXED, int POT, bool LOG>
-__global__ __launch_bounds__(1024) void k_force_rare(FORCE_ARGS)
-{
-    extern __shared__ double lds[];
-    if (!rare_list && a.flag_clear && blockIdx.x == 0) {
-        if (threadIdx.x == 0) *a.flag_clear = 0;
-        for (int q = threadIdx.x; q < n_sys; q += blockDim.x) a.sflag_clear[q] = 0;
+    int tile;
+    if ((int)blockIdx.x < ahead) {
+        const int cnt = *rare_n;
+        if ((int)blockIdx.x >= cnt || cnt > ahead) return;
+        tile = rare_list[blockIdx.x];
+    } else {
+        tile = die_tile(blockIdx.x - ahead, gridDim.x - ahead);
+        if (ahead > 0) {
+            const int32_t hn = halo_n[tile];
+            if ((hn < 0 || (hn & 0xFFFF) > halo_lds) && *rare_n <= ahead) return;
+        }
     }
-    const int cnt = rare_list ? *rare_n : tprefix[n_sys];
-    for (int k = blockIdx.x; k < cnt; k += gridDim.x) {
-        force_tile<W, MIXED, POT, LOG, true>(rare_list ? rare_list[k] : k, lds, FORCE_PASS);
-        __syncthreads();
-    }
+    force_tile<W, MIXED, POT, LOG>(tile, lds, sys, tprefix, n_sys, nlist, nn, cap, halo, halo_n, halo_cap, halo_lds,
+                                   prow, xbuild, tref, partials, st, a);
 }
 
 // Per-system totals of the wave partials, in a fixed order.
@@ -759,71 +813,26 @@ template <int W, bool MIXED, int POT, bool LOG>
 static void force_inst(const LaunchCtx &L, const ForceLaunch &F)
 {
     if (L.tiles_local == 0) return;
-    // the launch over rare tiles runs few workgroups: it stages up to the
-    // whole halo list (at most kRareLds bytes), so that oversized halos are
-    // read from LDS too
-    const int rb = L.tiles_local < kRareGrid ? L.tiles_local : kRareGrid;
-    int rare_lds_entries = (int)(kRareLds / (size_t)halo_entry_bytes(POT));
-    rare_lds_entries = rare_lds_entries < L.halo_cap ? rare_lds_entries : L.halo_cap;
-    rare_lds_entries = rare_lds_entries > L.halo_lds ? rare_lds_entries : L.halo_lds;
-    const size_t rare_lds = force_lds_bytes(POT, rare_lds_entries, L.nlist_cap);
-    // One launch of the second kind over every tile when the workgroups of
-    // all tiles that hold local rows are resident at once: at most 16 waves
-    // per CU (it takes up to 128 VGPRs) and as many workgroups as the CU's
-    // 160 KB of LDS holds
-    bool one = L.force_launch == kForceOne;
+    // Where the workgroups of all tiles that hold local rows are resident at
+    // once (at most 16 waves per CU, and as many workgroups as the CU's 160 KB
+    // of LDS holds), each stages up to kWideLds bytes of its halo; else the
+    // stage is the one sized for occupancy.
+    int entries = (int)(kWideLds / (size_t)halo_entry_bytes(POT));
+    entries = entries < L.halo_cap ? entries : L.halo_cap;
+    entries = entries > L.halo_lds ? entries : L.halo_lds;
+    bool wide = L.force_launch == kForceOne;
     if (L.force_launch == kForceAuto) {
+        const size_t lds = force_lds_bytes(POT, entries, L.nlist_cap);
         const int by_waves = 16 / W > 0 ? 16 / W : 1;
-        const int by_lds = (int)((size_t)163840 / (rare_lds > 0 ? rare_lds : 1));
-        const int per_cu = by_waves < by_lds ? by_waves : by_lds;
-        one = L.busy_tiles <= 256 * per_cu;
+        const int by_lds = (int)((size_t)163840 / (lds > 0 ? lds : 1));
+        wide = L.busy_tiles <= 256 * (by_waves < by_lds ? by_waves : by_lds);
     }
-    if (one) {
-        hipLaunchKernelGGL((k_force_rare<W, MIXED, POT, LOG>), dim3(rb), dim3(W * kWave), rare_lds, L.stream,
-                           L.sys, L.tprefix_local, L.n_sys, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
-                           L.halo_cap, rare_lds_entries, L.prow, L.xbuild, L.partials, L.status,
-                           (const int32_t *)nullptr, (const int32_t *)nullptr, F);
-        return;
-    }
-    const size_t lds = force_lds_bytes(POT, L.halo_lds, L.nlist_cap);
-    hipLaunchKernelGGL((k_force<W, MIXED, POT, LOG>), dim3(L.tiles_local), dim3(W * kWave), lds, L.stream,
-                       L.sys, L.tprefix_local, L.n_sys, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
-                       L.halo_cap, L.halo_lds, L.prow, L.xbuild, L.partials, L.status,
-                       L.rare_list, L.rare_n, F);
-    hipLaunchKernelGGL((k_force_rare<W, MIXED, POT, LOG>), dim3(rb), dim3(W * kWave), rare_lds, L.stream, L.sys,
-                       L.tprefix_local, L.n_sys, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n, L.halo_cap,
-                       rare_lds_entries, L.prow, L.xbuild, L.partials, L.status, L.rare_list,
-                       L.rare_n, F);
-}
-
-// Lets every instantiation of the rare-tile kernel take kRareLds bytes of
-// dynamic LDS (above the default limit).
-template <int W, bool MIXED, int POT, bool LOG>
-static hipError_t rare_attr()
-{
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_force_rare<W, MIXED, POT, LOG>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kRareLds);
-}
-
-template <int W>
-static hipError_t rare_attr_w()
-{
-    const hipError_t es[8] = {rare_attr<W, true, PAIR_LJ, true>(),   rare_attr<W, true, PAIR_LJ, false>(),
-                              rare_attr<W, true, PAIR_DPD, true>(),  rare_attr<W, true, PAIR_DPD, false>(),
-                              rare_attr<W, false, PAIR_LJ, true>(),  rare_attr<W, false, PAIR_LJ, false>(),
-                              rare_attr<W, false, PAIR_DPD, true>(), rare_attr<W, false, PAIR_DPD, false>()};
-    for (hipError_t e : es)
-        if (e != hipSuccess) return e;
-    return hipSuccess;
-}
-
-hipError_t prepare_force()
-{
-    const hipError_t es[5] = {rare_attr_w<1>(), rare_attr_w<2>(), rare_attr_w<4>(), rare_attr_w<8>(),
-                              rare_attr_w<16>()};
-    for (hipError_t e : es)
-        if (e != hipSuccess) return e;
-    return hipSuccess;
+    if (!wide) entries = L.halo_lds;
+    const int ahead = wide ? 0 : std::min(L.tiles_local, kAhead) / 8 * 8;
+    hipLaunchKernelGGL((k_force<W, MIXED, POT, LOG>), dim3(ahead + L.tiles_local), dim3(W * kWave),
+                       force_lds_bytes(POT, entries, L.nlist_cap), L.stream, L.sys, L.tprefix_local, L.n_sys, L.nlist,
+                       L.nn, L.nlist_cap, L.halo, L.halo_n, L.halo_cap, entries, L.prow, L.xbuild, L.tref, L.partials,
+                       L.status, L.rare_list, L.rare_n, ahead, F);
 }
 
 template <int W, bool MIXED, int POT>

@@ -47,6 +47,7 @@ struct LaunchCtx {
     int halo_cap;
     int halo_lds;                  // halo entries the force pass stages in LDS
     double4 *xbuild;
+    double4 *tref;                 // per tile, the point whose nearest images its halo entries take
     int32_t *ptag;                 // per row: bond_stride partner tags (-1 = none), moved with the row
     int32_t *pdir;                 // per row and partner: direction code of the partner's owner
                                    // (13 = this system, -1 = not known yet)
@@ -61,7 +62,7 @@ struct LaunchCtx {
     bool sorted;                   // rows are put in Morton order (sort_period > 0)
     bool line_rows;                // the line-ordered build (mixed-precision DPD)
     int32_t *slow_n;               // their number (cleared by the binning launch)
-    int32_t *rare_list;            // tiles the force pass handles in its second launch
+    int32_t *rare_list;            // tiles the force pass takes first (per-pair images, halos beyond its stage)
     int32_t *rare_n;               // their number (cleared by the binning launch)
     int32_t *tile_ctr;             // kDies counters of tiles taken by the framed build's workgroups,
                                    // kTileCtrStride words apart (cleared by the binning launch)
@@ -146,7 +147,5 @@ size_t line_plan_bytes(int64_t tiles);
 hipError_t prepare_lines(int nlist_cap);
 void launch_cells_and_lines(const LaunchCtx &L, const double4 *pos, int n_sort, int n_plan);
 void launch_build_lines(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int block);
-// Raises the dynamic-LDS limit of the rare-tile force kernels (init time).
-hipError_t prepare_force();
 
 }  // namespace md

@@ -185,7 +185,7 @@ __device__ __forceinline__ void general_tile(
     const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
     const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
     uint16_t *__restrict__ nlist, int32_t *__restrict__ nn, int cap, int32_t *__restrict__ halo,
-    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild, int halo_lds,
+    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild, double4 *__restrict__ tref, int halo_lds,
     int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, Status *st)
 {
     constexpr int W = NT / kTile;
@@ -602,6 +602,7 @@ __device__ __forceinline__ void general_tile(
         }
     }
     if (tid == 0) {
+        tref[tile] = x0;
         halo_n[tile] = (int32_t)((uint32_t)nhalo | ((uint32_t)sh.info[2] << 16) | (sh.info[1] ? 0x80000000u : 0u));
         // per-pair images or a halo beyond the force pass's LDS staging
         if (sh.info[1] || nhalo > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
@@ -636,7 +637,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
     const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
     const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
     uint16_t *__restrict__ nlist, int32_t *__restrict__ nn, int cap, int32_t *__restrict__ halo,
-    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild,
+    int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild, double4 *__restrict__ tref,
     const int32_t *__restrict__ list, const int32_t *__restrict__ list_n, int halo_lds,
     int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, const int32_t *__restrict__ flag, Status *st)
 {
@@ -647,7 +648,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
     for (int it = blockIdx.x; it < ntiles; it += gridDim.x)
         general_tile<EXCL, kBuildThreads, kChunk>(sh, list[it], sys, tprefix, n_sys, pos, tag, ptag, cell_size,
                                                   cell_idx, cell_cap, nlist, nn, cap, halo, halo_n, halo_cap, xbuild,
-                                                  halo_lds, rare_list, rare_n, st);
+                                                  tref, halo_lds, rare_list, rare_n, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -770,7 +771,7 @@ constexpr int kFastShared = (int)((sizeof(FastShared<NT, LPR>) + 15) / 16 * 16);
 __device__ __forceinline__ void plan_tiles(
     int pb, int npb, const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
     const double4 *__restrict__ pos, const int32_t *__restrict__ cell_count, int cell_cap,
-    double4 *__restrict__ xbuild, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
+    double4 *__restrict__ xbuild, double4 *__restrict__ tref, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
     char *__restrict__ plan, int64_t stride, const int32_t *__restrict__ sflag,
     int32_t *__restrict__ halo_n, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
 {
@@ -783,7 +784,7 @@ __device__ __forceinline__ void plan_tiles(
         const int s = find_sys(tprefix, n_sys, tile);
         if (!sflag[s]) {
             // a system that keeps its list: its tile goes back on the list of
-            // the force pass's second launch if its last build put it there
+            // tiles that the force pass takes first if its last build put it there
             // (the binning launch before this one emptied that list)
             if (lane == 0) {
                 const int32_t hn = halo_n[tile];
@@ -879,7 +880,7 @@ __device__ __forceinline__ void plan_tiles(
         // boxes of each 16 rows
         const bool found = act && fabsf(xf[0]) < 1e15f && fabsf(xf[1]) < 1e15f && fabsf(xf[2]) < 1e15f;
         const bool any = __ballot(found) != 0ull;
-        float half[3], spread[3], xc[3], gmid[4][3], ghalf[4][3];
+        float half[3], xc[3], gmid[4][3], ghalf[4][3];
         double ref[3];
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -896,8 +897,6 @@ __device__ __forceinline__ void plan_tiles(
             const float ctr = 0.5f * (lo_ + hi_);
             // (xf and its differences round: a little more than half the extent)
             half[a] = 0.5000005f * (hi_ - lo_) + 0x1p-22f * fmaxf(fabsf(lo_), fabsf(hi_));
-            // spread of the rows around row 0 (xf is relative to it)
-            spread[a] = fmaxf(fabsf(lo_), fabsf(hi_));
 #pragma unroll
             for (int R = 0; R < 4; ++R) {
                 const bool none = mn[R] > mx[R];
@@ -1016,23 +1015,27 @@ __device__ __forceinline__ void plan_tiles(
             continue;
         }
 
-        // One image per halo entry (the one nearest row 0, taken by the force
-        // pass at every step) is every row's minimum image while, per
-        // periodic axis, spread + r_list + 2 r_buff < L/2: until the next
-        // build each particle moves at most r_buff/2, so a row stays within
-        // spread + r_buff of row 0 and a listed pair within r_list + r_buff,
-        // and the partner image nearest the row is within L/2 of row 0 (the
-        // rows' FP32 offsets get a margin of 1e-5 L).  Otherwise the force
-        // pass takes the minimum image per pair.
+        // One image per halo entry (the one nearest the centre of the rows'
+        // bounding box, taken by the force pass at every step) is every row's
+        // minimum image while, per periodic axis, half the box + r_list +
+        // 2 r_buff < L/2: until the next build each particle moves at most
+        // r_buff/2, so a row stays within half the box + r_buff/2 of the
+        // centre and a listed pair within r_list + r_buff, and the partner
+        // image nearest the row is within L/2 of the centre (the rows' FP32
+        // offsets get a margin of 1e-5 L).  Otherwise the force pass takes the
+        // minimum image per pair: around row 0 in place of the centre that
+        // was 51 of the 63 tiles of a 4,000-particle LJ liquid and 1,810 of
+        // 9,709 of 64 small systems.
         const double rbuff = 2.0 * sqrt(S.disp2);
         int pp = 0;
 #pragma unroll
         for (int a = 0; a < 3; ++a)
-            if (per[a] && (double)spread[a] + rl + 2.0 * rbuff + 1e-5 * Ls[a] >= 0.5 * Ls[a]) pp = 1;
+            if (per[a] && (double)half[a] + rl + 2.0 * rbuff + 1e-5 * Ls[a] >= 0.5 * Ls[a]) pp = 1;
         if (lane == 0) {
             pt->nu = nu;
             pt->nseg = nseg;
             pt->pp = pp;
+            tref[tile] = make_double4(ref[0], ref[1], ref[2], 0.0);
             pt->band = band;
             pt->lo = near_lo;
             pt->hi = near_hi;
@@ -1057,7 +1060,7 @@ __global__ __launch_bounds__(kWave) void k_cells_and_plan(
     const int32_t *__restrict__ tprefix, int tiles,
     const double4 *__restrict__ pos, int64_t n_cells, const int32_t *__restrict__ cell_count,
     int32_t *__restrict__ cell_size, int32_t *__restrict__ cell_idx, float4 *__restrict__ cell_xf, int cell_cap,
-    double4 *__restrict__ xbuild, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
+    double4 *__restrict__ xbuild, double4 *__restrict__ tref, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
     char *__restrict__ plan, int64_t stride, const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *__restrict__ halo_n,
     int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
 {
@@ -1067,7 +1070,7 @@ __global__ __launch_bounds__(kWave) void k_cells_and_plan(
                              cell_xf, cell_cap, sflag);
     } else {
         plan_tiles((int)blockIdx.x - n_sort, (int)gridDim.x - n_sort, sys, tprefix, n_sys, tiles, pos,
-                   cell_count, cell_cap, xbuild, slow_list, slow_n, plan, stride, sflag, halo_n, halo_lds, rare_list, rare_n);
+                   cell_count, cell_cap, xbuild, tref, slow_list, slow_n, plan, stride, sflag, halo_n, halo_lds, rare_list, rare_n);
     }
 }
 
@@ -1137,7 +1140,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     int64_t plan_stride, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n,
     int32_t *__restrict__ tile_ctr, int32_t *__restrict__ cell_count, int64_t n_cells,
     const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
-    double4 *__restrict__ xbuild, const int32_t *__restrict__ slow_list, const int32_t *__restrict__ slow_n,
+    double4 *__restrict__ xbuild, double4 *__restrict__ tref, const int32_t *__restrict__ slow_list, const int32_t *__restrict__ slow_n,
     const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *build_count, Status *st)
 {
     if (*flag == 0) return;
@@ -1170,7 +1173,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     for (int it = blockIdx.x; it < *slow_n; it += gridDim.x)
         general_tile<EXCL, NT, 0>(*reinterpret_cast<GeneralShared<0> *>(lds_all), slow_list[it],
                                               sys, tprefix, n_sys, pos, tag, ptag, cell_size, cell_idx, cell_cap,
-                                              nlist, nn, cap, halo, halo_n, halo_cap, xbuild, halo_lds, rare_list,
+                                              nlist, nn, cap, halo, halo_n, halo_cap, xbuild, tref, halo_lds, rare_list,
                                               rare_n, st);
 
     // Each die's workgroups walk one contiguous run of tiles.  With one
@@ -1596,13 +1599,13 @@ void launch_cell_sort(const LaunchCtx &L, const double4 *pos)
     if (L.cell_cap <= 64)
         hipLaunchKernelGGL(k_cells_and_plan<1>, grid, dim3(kWave), 0, L.stream, (int)n_sort, L.sys, L.cprefix, L.n_sys,
                            L.tprefix_local, L.tiles_local, pos, L.n_cells, L.cell_count, L.cell_size, L.cell_idx,
-                           L.cell_xf, L.cell_cap, L.xbuild, L.slow_list, L.slow_n, L.plan,
+                           L.cell_xf, L.cell_cap, L.xbuild, L.tref, L.slow_list, L.slow_n, L.plan,
                            plan_stride(L.seg_cap), L.flag, L.sflag,
                            L.halo_n, L.halo_lds, L.rare_list, L.rare_n);
     else
         hipLaunchKernelGGL(k_cells_and_plan<2>, grid, dim3(kWave), 0, L.stream, (int)n_sort, L.sys, L.cprefix, L.n_sys,
                            L.tprefix_local, L.tiles_local, pos, L.n_cells, L.cell_count, L.cell_size, L.cell_idx,
-                           L.cell_xf, L.cell_cap, L.xbuild, L.slow_list, L.slow_n, L.plan,
+                           L.cell_xf, L.cell_cap, L.xbuild, L.tref, L.slow_list, L.slow_n, L.plan,
                            plan_stride(L.seg_cap), L.flag, L.sflag,
                            L.halo_n, L.halo_lds, L.rare_list, L.rare_n);
 }
@@ -1666,7 +1669,7 @@ static void fast_inst(const LaunchCtx &L, const double4 *pos, const int32_t *tag
     hipLaunchKernelGGL((k_build_fast<EXCL, NT, LPR>), dim3(blocks), dim3(NT), dyn, L.stream, L.sys, L.tprefix_local,
                        L.n_sys, L.tiles_local, pos, tag, L.ptag, L.bond_stride, L.cell_xf, L.nlist, L.nn, L.nlist_cap, rs, L.halo,
                        L.halo_n, L.halo_cap, L.plan, plan_stride(L.seg_cap), L.halo_lds, L.rare_list, L.rare_n,
-                       L.tile_ctr, L.cell_count, L.n_cells, L.cell_size, L.cell_idx, L.cell_cap, L.xbuild, L.slow_list,
+                       L.tile_ctr, L.cell_count, L.n_cells, L.cell_size, L.cell_idx, L.cell_cap, L.xbuild, L.tref, L.slow_list,
                        L.slow_n, L.flag, L.sflag, L.build_count, L.status);
 }
 
@@ -1704,7 +1707,7 @@ void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, in
     auto general = [&](auto k) {
         hipLaunchKernelGGL(k, dim3(blocks), dim3(kBuildThreads), 0, L.stream, L.sys, L.tprefix_local, L.n_sys, pos, tag,
                            L.ptag, L.cell_size, L.cell_idx, L.cell_cap, L.nlist, L.nn, L.nlist_cap, L.halo, L.halo_n,
-                           L.halo_cap, L.xbuild, L.slow_list, L.slow_n, L.halo_lds, L.rare_list, L.rare_n, L.flag,
+                           L.halo_cap, L.xbuild, L.tref, L.slow_list, L.slow_n, L.halo_lds, L.rare_list, L.rare_n, L.flag,
                            L.status);
     };
     if (L.has_bonds) general(k_build_tile<true>);

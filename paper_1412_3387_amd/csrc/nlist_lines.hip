@@ -199,7 +199,7 @@ __device__ __forceinline__ void plan_lines(
         const int s = find_sys(tprefix, n_sys, tile);
         if (!sflag[s]) {
             // a system that keeps its list: its tile goes back on the list of
-            // the force pass's second launch if its last build put it there
+            // tiles that the force pass takes first if its last build put it there
             // (the binning launch before this one emptied that list)
             if (lane == 0) {
                 const int32_t hn = halo_n[tile];

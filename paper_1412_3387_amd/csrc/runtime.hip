@@ -36,7 +36,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 struct Layout {
     // byte offsets into the workspace
     size_t sysdev, tpl, tpa, cpre, status, flags, tile_ctr, sysflags, thermo, thermo_log, partials, khalf, thermostat;
-    size_t pos_alt, vel_alt, xbuild, nlist, nn, cell_count, cell_size, cell_idx, cell_xf, halo, halo_n;
+    size_t pos_alt, vel_alt, xbuild, tref, nlist, nn, cell_count, cell_size, cell_idx, cell_xf, halo, halo_n;
     size_t ptag, pdir, prow, btmp, hash, slow_list, rare_list, plan, sort_ws, ghost_ws, total;
     // sizes
     int64_t rows, tiles_local, tiles_all, n_cells, nlist_entries, hash_slots;
@@ -163,7 +163,7 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
         int hl = p[s].sort_period > 0 ? (int)std::ceil(1.25 * est / 64.0) * 64 : lds_budget;
         // where the mean halo fits, stay within the share of seven
         // 256-thread workgroups in a CU's 160 KB of LDS: seven resident tiles
-        // per CU outrun six, though a few more tiles go to the rare launch
+        // per CU outrun six, though a few more tiles have halos beyond it
         const int share7 = std::max(163840 / 7 / entry / 64 * 64, 64);
         if (p[s].sort_period > 0 && est <= share7) hl = std::min(hl, share7);
         hl = std::min(std::max(hl, 64), std::min(lds_budget, hc));
@@ -309,6 +309,7 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
     Lo.pos_alt = take(sizeof(double4) * rows);
     Lo.vel_alt = take(sizeof(double4) * rows);
     Lo.xbuild = take(sizeof(double4) * rows);
+    Lo.tref = take(sizeof(double4) * (size_t)std::max<int64_t>(tile, 1));
     // padded: the force pass reads up to force_row_over_read() entries past
     // any row's end
     Lo.nlist = take(sizeof(uint16_t) * ((size_t)std::max<int64_t>(nl, 1) + (size_t)force_row_over_read() * kTile));
@@ -436,7 +437,7 @@ size_t mark(hoomd_ctx *c)
 // Device flags: 0 and 1 rebuild flags of the two buffer parities, 2 the flag
 // of explicit builds, 3 unused, 4 build counter, 5 step counter of replayed steps, 6
 // tiles passed from the framed build to the general one, 7 tiles the force
-// pass handles in its second launch.
+// pass takes first.
 int32_t *flag_ptr(hoomd_ctx *c, int k) { return ws_ptr<int32_t>(c, c->lay.flags) + k; }
 
 // Per-system words, n_sys each: k = 0, 1, 2 the rebuild flags of each system
@@ -611,6 +612,7 @@ int hoomd_init(hoomd_ctx **out, const hoomd_params *params, int32_t n_sys, const
     L.nn = ws_ptr<int32_t>(c, lay.nn);
     L.nlist_cap = lay.nlist_cap;
     L.xbuild = ws_ptr<double4>(c, lay.xbuild);
+    L.tref = ws_ptr<double4>(c, lay.tref);
     L.ptag = ws_ptr<int32_t>(c, lay.ptag);
     L.pdir = ws_ptr<int32_t>(c, lay.pdir);
     L.prow = ws_ptr<int32_t>(c, lay.prow);
@@ -652,7 +654,6 @@ int hoomd_init(hoomd_ctx **out, const hoomd_params *params, int32_t n_sys, const
 
     // descriptors, prefixes, cleared counters (synchronous: init is not hot)
     hipError_t e = prepare_nlist(lay.nlist_cap);
-    if (e == hipSuccess) e = prepare_force();
     if (e == hipSuccess) e = hipMemcpy(c->ws + lay.sysdev, lay.sys.data(), sizeof(SysDev) * n_sys, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->ws + lay.tpl, lay.tpl_host.data(), sizeof(int32_t) * (n_sys + 1), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemcpy(c->ws + lay.tpa, lay.tpa_host.data(), sizeof(int32_t) * (n_sys + 1), hipMemcpyHostToDevice);
@@ -1417,7 +1418,7 @@ int tune_now(hoomd_ctx *c, bool use_cache)
     if (!c->fixed_nlist && c->lay.tiles_local > 0) {
         // the list build over its shapes, on the cells and plans just made:
         // each timed launch redoes the framed and the general build (the list
-        // of tiles for the force pass's second launch is emptied first)
+        // of tiles that the force pass takes first is emptied before)
         int32_t *flag = flag_ptr(c, 2), *sflag = sflag_ptr(c, 2);
         float best = 1e30f;
         int bk = 0;
