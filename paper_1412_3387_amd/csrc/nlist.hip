@@ -129,7 +129,9 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
 // tile-halo neighbour list
 // ---------------------------------------------------------------------------
 
-// LDS of a tile of the general build; CH members staged at once (0: none are).
+// LDS of a tile of the general build; CH members staged at once (0: all of a
+// tile with at most kGeneralStage, else none).
+constexpr int kGeneralStage = 896;
 template <int CH>
 struct GeneralStage {
     double cx[CH], cy[CH], cz[CH];
@@ -137,6 +139,8 @@ struct GeneralStage {
 };
 template <>
 struct GeneralStage<0> {
+    double cx[kGeneralStage], cy[kGeneralStage], cz[kGeneralStage];
+    int32_t own[kTile];   // staged place of each row
 };
 template <int CH>
 struct GeneralShared {
@@ -177,8 +181,9 @@ __device__ __forceinline__ int upper_idx16(const uint16_t *a, int n, int x)
 // (CH > 0, which keeps the entries of a row in the order of the chunks: the
 // bits of mixed-precision DPD sums).  Sort, chunks of 2,048 and a launch of its
 // own took 70 - 127 us; inside the framed launch, staged 512 at a time, that
-// launch took 147 us (DPD, 100,000 particles), 265 us (64 WCA melts) and
-// 189 us (LJ, 255,000), and reading directly 88, 193 and 157 us.
+// launch took 147 us (DPD, 100,000 particles), 265 us (64 small systems) and
+// 189 us (LJ, 255,000), and reading directly 70, 187 and 156 us.  A tile whose
+// cells hold at most kGeneralStage members (a small system) reads them once.
 template <bool EXCL, int NT, int CH>
 __device__ __forceinline__ void general_tile(
     GeneralShared<CH> &sh, int tile, const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys,
@@ -489,74 +494,86 @@ __device__ __forceinline__ void general_tile(
             }
         }
     } else {
-        // Rows far apart share few cells: each row's W lanes read the members
-        // of its own stencil, one run over all cells, V loads in flight.
-        constexpr int V = 4;
-#pragma unroll
-        for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
-            const int k = sl + q * W;
-            if (k < kStencil && sh.su[t][k] >= 0 && out_of_reach(k)) sh.su[t][k] = (int16_t)-1;
-        }
+        // Rows far apart share few cells: each of a row's W lanes reads the
+        // members of stencil cells of its own, V at a time (the loads of a
+        // batch are in flight together; instructions and their latency bound
+        // it: with the members of all cells dealt to the lanes one by one, the
+        // cell of each looked for, a launch with 23 such tiles took 143 us, now
+        // 94: 4,000 LJ particles).
+        constexpr int V = 8;
         __syncthreads();
-        int k = -1, start = 0, end = 0, u = 0;  // the stencil cell of this lane's member, its place in the run
-        for (int base = 0;; base += V * W) {
-            bool ok[V];
-            int qq[V], code[V];
-            int32_t jj[V];
+        const bool staged = nslot <= kGeneralStage;
+        if (staged) {
+            for (int q = tid; q < nslot; q += NT) {
+                const int u = upper_idx16(sh.ustart, nu, q);
+                const int32_t j = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
+                const double4 xj = pos[j];
+                sh.stage.cx[q] = xj.x;
+                sh.stage.cy[q] = xj.y;
+                sh.stage.cz[q] = xj.z;
+                const int64_t o = j - (row0 + r0);
+                if (o >= 0 && o < kTile) sh.stage.own[o] = q;
+            }
+            __syncthreads();
+        }
+        const int own = staged && active ? sh.stage.own[t] : -1;
+        for (int k = sl; __ballot(k < kStencil); k += W) {
+            const int u = k < kStencil && !out_of_reach(k) ? sh.su[t][k] : -1;
+            const int start = u < 0 ? 0 : sh.ustart[u];
+            const int m = u < 0 ? 0 : sh.ustart[u + 1] - start;
+            const int64_t at = u < 0 ? 0 : (cell0 + sh.keys[u]) * cell_cap;
+            for (int m0 = 0; __ballot(m0 < m); m0 += V) {
+                bool ok[V];
+                int32_t jj[V];
+                double ddx[V], ddy[V], ddz[V];
+                if (!staged || EXCL) {
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const int x = base + v * W + sl;
-                while (k < kStencil && x >= end) {
-                    ++k;
-                    start = end;
-                    if (k < kStencil) {
-                        u = sh.su[t][k];
-                        if (u >= 0) end += sh.ustart[u + 1] - sh.ustart[u];
+                    for (int v = 0; v < V; ++v) jj[v] = cell_idx[m0 + v < m ? at + m0 + v : 0];
+                }
+                if (staged) {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const int q = m0 + v < m ? start + m0 + v : 0;
+                        ddx[v] = sh.stage.cx[q];
+                        ddy[v] = sh.stage.cy[q];
+                        ddz[v] = sh.stage.cz[q];
+                        ok[v] = m0 + v < m && q != own;
+                    }
+                } else {
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        const int64_t j = m0 + v < m ? jj[v] : i;
+                        ddx[v] = pos[j].x;
+                        ddy[v] = pos[j].y;
+                        ddz[v] = pos[j].z;
+                        ok[v] = j != i;
                     }
                 }
-                ok[v] = k < kStencil;
-                qq[v] = 0;
-                code[v] = 13;
-                int64_t at = 0;
-                if (ok[v]) {
-                    qq[v] = sh.ustart[u] + (x - start);
-                    code[v] = sh.sm[t][k];
-                    at = (cell0 + sh.keys[u]) * cell_cap + (x - start);
-                }
-                jj[v] = cell_idx[at];
-            }
-            if (__ballot(ok[0]) == 0) break;  // lanes ahead of the first are past the end as well
-            double ddx[V], ddy[V], ddz[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                if (!ok[v]) jj[v] = (int32_t)i;
-                ddx[v] = pos[jj[v]].x - xi.x;
-                ddy[v] = pos[jj[v]].y - xi.y;
-                ddz[v] = pos[jj[v]].z - xi.z;
-            }
+                for (int v = 0; v < V; ++v) {
+                    // (the minimum image: for a pair inside r_list the shift of
+                    // its cell, and the nearest image where a cell has several)
+                    double dx = ddx[v] - xi.x, dy = ddy[v] - xi.y, dz = ddz[v] - xi.z;
+                    dx = px ? min_image(dx, Lx, iLx) : dx;
+                    dy = py ? min_image(dy, Ly, iLy) : dy;
+                    dz = pz ? min_image(dz, Lz, iLz) : dz;
+                    bool hit = ok[v] && norm2_exact(dx, dy, dz) < rl2;
+                    if constexpr (EXCL) {
+                        if (hit) {
+                            const int32_t tj = tag[jj[v]];
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const double sx = Lx * (double)(code[v] % 3 - 1);
-                const double sy = Ly * (double)((code[v] / 3) % 3 - 1);
-                const double sz = Lz * (double)(code[v] / 9 - 1);
-                ddx[v] = fx_ ? min_image(ddx[v], Lx, iLx) : ddx[v] - sx;
-                ddy[v] = fy_ ? min_image(ddy[v], Ly, iLy) : ddy[v] - sy;
-                ddz[v] = fz_ ? min_image(ddz[v], Lz, iLz) : ddz[v] - sz;
-                bool hit = ok[v] && jj[v] != (int32_t)i && norm2_exact(ddx[v], ddy[v], ddz[v]) < rl2;
-                if constexpr (EXCL) {
+                            for (int b = 0; b < kMaxBondCap; ++b) hit = hit && (part[b] != tj);
+                        }
+                    }
+                    const uint64_t mask = __ballot(hit) & seg;
                     if (hit) {
-                        const int32_t tj = tag[jj[v]];
-#pragma unroll
-                        for (int b = 0; b < kMaxBondCap; ++b) hit = hit && (part[b] != tj);
+                        const int q = start + m0 + v;
+                        const int p = ntot + __popcll(mask & below);
+                        if (p < cap) nlist[rowbase + (int64_t)p * kTile] = (uint16_t)q;
+                        atomicOr(&sh.used[q >> 5], 1u << (q & 31));
                     }
+                    ntot += __popcll(mask);
                 }
-                const uint64_t mask = __ballot(hit) & seg;
-                if (hit) {
-                    const int p = ntot + __popcll(mask & below);
-                    if (p < cap) nlist[rowbase + (int64_t)p * kTile] = (uint16_t)qq[v];
-                    atomicOr(&sh.used[qq[v] >> 5], 1u << (qq[v] & 31));
-                }
-                ntot += __popcll(mask);
             }
         }
     }
@@ -593,13 +610,27 @@ __device__ __forceinline__ void general_tile(
     }
     // halo list: row number of every used member, in staging order
     int32_t *hl = halo + (int64_t)tile * halo_cap;
-    for (int q = tid; q < nslot; q += NT) {
-        const uint32_t word = sh.used[q >> 5];
-        if (word & (1u << (q & 31))) {
-            const int u = upper_idx16(sh.ustart, nu, q);
-            const int h = sh.tmp[q >> 5] + __popc(word & ((1u << (q & 31)) - 1u));
-            hl[h] = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
+    for (int q0 = tid; q0 < nslot; q0 += 4 * NT) {
+        int64_t at[4];
+        int32_t j[4];
+        int h[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int q = q0 + v * NT;
+            const uint32_t word = q < nslot ? sh.used[q >> 5] : 0u;
+            h[v] = -1;
+            at[v] = 0;
+            if (word & (1u << (q & 31))) {
+                const int u = upper_idx16(sh.ustart, nu, q);
+                h[v] = sh.tmp[q >> 5] + __popc(word & ((1u << (q & 31)) - 1u));
+                at[v] = (cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u]);
+            }
         }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) j[v] = cell_idx[at[v]];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (h[v] >= 0) hl[h[v]] = j[v];
     }
     if (tid == 0) {
         tref[tile] = x0;
@@ -611,15 +642,16 @@ __device__ __forceinline__ void general_tile(
     __syncthreads();
     if (active) {
         const int n = ntot < cap ? ntot : cap;
-        for (int k = sl; k < n; k += 2 * W) {
-            const int64_t a = rowbase + (int64_t)k * kTile;
-            const int64_t b = a + (int64_t)W * kTile;
-            const bool has_b = k + W < n;
-            const int qa = nlist[a];
-            const int qb = has_b ? nlist[b] : 0;
-            const uint32_t wa = sh.used[qa >> 5], wb = sh.used[qb >> 5];
-            nlist[a] = (uint16_t)(sh.tmp[qa >> 5] + __popc(wa & ((1u << (qa & 31)) - 1u)));
-            if (has_b) nlist[b] = (uint16_t)(sh.tmp[qb >> 5] + __popc(wb & ((1u << (qb & 31)) - 1u)));
+        constexpr int V = 8;
+        for (int k0 = sl; k0 < n; k0 += V * W) {
+            int q[V];
+#pragma unroll
+            for (int v = 0; v < V; ++v) q[v] = k0 + v * W < n ? nlist[rowbase + (int64_t)(k0 + v * W) * kTile] : 0;
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (k0 + v * W < n)
+                    nlist[rowbase + (int64_t)(k0 + v * W) * kTile] =
+                        (uint16_t)(sh.tmp[q[v] >> 5] + __popc(sh.used[q[v] >> 5] & ((1u << (q[v] & 31)) - 1u)));
         }
         if (sl == 0) {
             nn[i] = n;
