@@ -409,7 +409,23 @@ void default_tuning(hoomd_ctx *c)
     if (c->prm[0].block_nlist > 0) c->block_nlist = c->prm[0].block_nlist;
     c->fixed_nlist = c->prm[0].tpp_nlist > 0 || c->prm[0].block_nlist > 0;
     c->fixed_force = c->prm[0].tpp_force > 0;
-    c->tpp_force = per_cu > 2048 ? 4 : 8;
+    // More lanes per row shorten a row's chain and fill a small chip's worth of
+    // tiles, fewer waste less on row ends and reductions.  Pass, us, 4 / 8
+    // lanes: LJ (86 entries a row) 8.8 / 8.2 for 16,000 rows, 10.2 / 10.3 for
+    // 32,000, 14.1 / 16.3 for 64,000, 28.5 / 34.2 for 200,000; DPD FP64 15.8 /
+    // 16.1 for 30,000, 32.5 / 37.1 for 100,000; melts (13 entries a row), 2 / 4
+    // / 8 lanes: 8.0 / 8.1 / 9.4 for 20,000, 8.8 / 8.8 / 11.0 for 40,000, 10.4 /
+    // 12.0 / 17.6 for 100,000.  Mixed-precision DPD keeps 8 to 524,288 rows: the
+    // lanes order its sums, on whose last bits its FP32 pair terms depend.
+    double nbar = 0.0;
+    for (int s = 0; s < c->n_sys; ++s) {
+        const double rl = pair_cut(c->prm[s]) + c->prm[s].r_buff;
+        const double vol = c->box[s].L[0] * c->box[s].L[1] * c->box[s].L[2];
+        nbar = std::max(nbar, 4.0 / 3.0 * M_PI * rl * rl * rl * (double)c->box[s].n_cap / vol);
+    }
+    if (c->pair_uniform == PAIR_DPD && c->mixed) c->tpp_force = per_cu > 2048 ? 4 : 8;
+    else if (nbar <= 24.0) c->tpp_force = per_cu > 160 ? 2 : 4;
+    else c->tpp_force = per_cu > 120 ? 4 : 8;
     if (c->prm[0].tpp_force > 0) c->tpp_force = c->prm[0].tpp_force;
     c->block_force = 64 * c->tpp_force;
 }
