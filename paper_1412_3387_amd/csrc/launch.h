@@ -47,6 +47,7 @@ struct LaunchCtx {
     int halo_cap;
     int halo_lds;                  // halo entries the force pass stages in LDS
     double4 *xbuild;
+    int64_t *flagged;              // the systems of the current rebuild (Flagged)
     double4 *tref;                 // per tile, the point whose nearest images its halo entries take
     int32_t *ptag;                 // per row: bond_stride partner tags (-1 = none), moved with the row
     int32_t *pdir;                 // per row and partner: direction code of the partner's owner
@@ -111,6 +112,8 @@ struct ForceLaunch {
 // nvt_w > 0: the launch also does the Nose-Hoover update of the force launch
 // just before it (launch_nvt_update(L, nvt_w) folded in).
 void launch_bin(const LaunchCtx &L, const double4 *pos, int nvt_w = 0);
+// The list of rebuilt systems alone (the binning launch writes it too).
+void launch_flagged(const LaunchCtx &L);
 void launch_cell_sort(const LaunchCtx &L, const double4 *pos);
 void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int w, int block);
 void launch_force(const LaunchCtx &L, const ForceLaunch &F, int w, int block);
@@ -138,6 +141,7 @@ int nlist_chunk();  // chunk (64 or 32) of the framed build (default)
 int nlist_block(bool line_rows);  // threads per workgroup of the framed build (default)
 bool nlist_shape_ok(int chunk, int block);  // a shape launch_nlist runs
 int build_seg_cap(double cell_mean);  // segments of a tile's plan, from the mean members of a cell
+size_t flagged_list_bytes(int n_sys);
 size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows);
 int cell_xf_slots(int cell_cap);      // cell_xf entries per cell
 hipError_t prepare_nlist(int nlist_cap);

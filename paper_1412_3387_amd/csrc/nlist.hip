@@ -50,6 +50,46 @@ constexpr int kStencil = 27;
 // ---------------------------------------------------------------------------
 // binning
 // ---------------------------------------------------------------------------
+// Writes the list of the systems whose flag is set (a workgroup of 256).
+__device__ __forceinline__ void write_flagged(int64_t *fl, int n_sys, const int32_t *__restrict__ sflag,
+                                              const int32_t *__restrict__ tprefix, const int64_t *__restrict__ cprefix,
+                                              int32_t *scan)
+{
+    const Flagged F = flagged_at(fl, n_sys);
+    int64_t *cell = fl;
+    int32_t *tile = const_cast<int32_t *>(F.tile), *id = const_cast<int32_t *>(F.sys);
+    int nf = 0, nt = 0;
+    int64_t nc = 0;
+    for (int s0 = 0; s0 < n_sys; s0 += 256) {
+        const int s = s0 + (int)threadIdx.x;
+        const bool on = s < n_sys && sflag[s] != 0;
+        int f, t, c;
+        const int k = nf + block_rank<256>(on ? 1 : 0, scan, f);
+        const int kt = nt + block_rank<256>(on ? tprefix[s + 1] - tprefix[s] : 0, scan, t);
+        const int64_t kc = nc + block_rank<256>(on ? (int)(cprefix[s + 1] - cprefix[s]) : 0, scan, c);
+        if (on) {
+            id[k] = s;
+            tile[k] = kt;
+            cell[k] = kc;
+        }
+        nf += f;
+        nt += t;
+        nc += c;
+    }
+    if (threadIdx.x == 0) {
+        tile[nf] = nt;
+        cell[nf] = nc;
+        *const_cast<int32_t *>(F.n) = nf;
+    }
+}
+__global__ __launch_bounds__(256) void k_flagged(int64_t *fl, int n_sys, const int32_t *__restrict__ sflag,
+                                                 const int32_t *__restrict__ tprefix,
+                                                 const int64_t *__restrict__ cprefix)
+{
+    __shared__ int32_t scan[4];
+    write_flagged(fl, n_sys, sflag, tprefix, cprefix, scan);
+}
+
 __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
                                              const int32_t *__restrict__ tprefix, int n_sys, int tiles,
                                              const double4 *__restrict__ pos,
@@ -60,7 +100,8 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
                                              uint32_t *step_counter, int32_t *slow_n, int32_t *rare_n,
                                              int32_t *tile_ctr, int32_t *since, int since_inc,
                                              const int32_t *__restrict__ tprefix_local, int nvt_w,
-                                             const double *__restrict__ khalf, double *__restrict__ thermostat)
+                                             const double *__restrict__ khalf, double *__restrict__ thermostat,
+                                             int64_t *fl, const int64_t *__restrict__ cprefix)
 {
     // The Nose-Hoover update of the force launch just before (its half-step
     // partials are complete at that launch's end), folded into this launch,
@@ -88,6 +129,10 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
     // the framed build's per-die tile counters
     if (blockIdx.x == 0 && threadIdx.x < kDies) tile_ctr[threadIdx.x * kTileCtrStride] = 0;
     const int lane = lane_id();
+    if (fl && n_sys > 1 && blockIdx.x == 0) {
+        __shared__ int32_t scan[4];
+        write_flagged(fl, n_sys, sflag, tprefix_local, cprefix, scan);
+    }
     const uint64_t lt = lanemask_lt();
     const int waves = (int)(gridDim.x * blockDim.x) >> 6;
     for (int g = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6); g < tiles; g += waves) {
@@ -96,31 +141,37 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
         const SysDev &S = sys[s];
         const int r = (g - S.tile0_all) * kTile + lane;
         const bool valid = r < S.n_total;
-        int64_t c = -1;
-        int64_t i = 0;
+        const int64_t i = S.row0 + r;
+        int c = -1;
         if (valid) {
-            i = S.row0 + r;
             const double4 x = pos[i];
             const int cx = cell_coord(x.x, S.lo[0], S.scale[0], S.bins[0]);
             const int cy = cell_coord(x.y, S.lo[1], S.scale[1], S.bins[1]);
             const int cz = cell_coord(x.z, S.lo[2], S.scale[2], S.bins[2]);
-            c = S.cell0 + ((int64_t)cz * S.bins[1] + cy) * S.bins[0] + cx;
+            c = (cz * S.bins[1] + cy) * S.bins[0] + cx;
         }
-        // one atomic per distinct cell of the wave
+        // one atomic per distinct cell of the wave, all of them in flight
+        // together (BINTIMES)
+        int leader = lane, rank = 0, members = 0;
         uint64_t todo = __ballot(valid);
         while (todo) {
-            const int leader = __ffsll((unsigned long long)todo) - 1;
-            const int64_t lc = __shfl(c, leader, kWave);
-            const uint64_t same = __ballot(valid && c == lc);
-            int base = 0;
-            if (lane == leader) base = atomicAdd(&cell_count[lc], __popcll(same));
-            base = __shfl(base, leader, kWave);
-            if (valid && c == lc) {
-                const int slot = base + __popcll(same & lt);
-                if (slot < cell_cap) cell_idx[c * cell_cap + slot] = (int32_t)i;
-                else latch(st, 6 /*CELL_OVERFLOW*/, slot + 1);
+            const int l = __ffsll((unsigned long long)todo) - 1;
+            const int lc = __builtin_amdgcn_readlane(c, l);
+            const uint64_t same = __ballot(c == lc);
+            if (c == lc) {
+                leader = l;
+                rank = __popcll(same & lt);
+                members = __popcll(same);
             }
             todo &= ~same;
+        }
+        int base = 0;
+        if (valid && lane == leader) base = atomicAdd(&cell_count[S.cell0 + c], members);
+        base = __shfl(base, leader, kWave);
+        if (valid) {
+            const int slot = base + rank;
+            if (slot < cell_cap) cell_idx[(S.cell0 + c) * cell_cap + slot] = (int32_t)i;
+            else latch(st, 6 /*CELL_OVERFLOW*/, slot + 1);
         }
     }
 }
@@ -805,25 +856,30 @@ __device__ __forceinline__ void plan_tiles(
     const double4 *__restrict__ pos, const int32_t *__restrict__ cell_count, int cell_cap,
     double4 *__restrict__ xbuild, double4 *__restrict__ tref, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
     char *__restrict__ plan, int64_t stride, const int32_t *__restrict__ sflag,
-    int32_t *__restrict__ halo_n, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
+    int32_t *__restrict__ halo_n, int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n,
+    int64_t *fl)
 {
     __shared__ uint32_t box[kBoxMax / 32];
     const int lane = lane_id();
+    const Flagged F = flagged_at(fl, n_sys);
+    const int nf = n_sys > 1 ? *F.n : 1;
+    if (n_sys > 1) {
+        // a system that keeps its list: its tiles go back on the list of tiles
+        // that the force pass takes first if its last build put them there
+        // (the binning launch before this one emptied that list)
+        for (int t0 = pb * kWave; t0 < tiles; t0 += npb * kWave) {
+            const int t = t0 + lane < tiles ? t0 + lane : tiles - 1;
+            const int32_t hn = halo_n[t];
+            if (t == t0 + lane && !sflag[find_sys(tprefix, n_sys, t)] && (hn < 0 || (hn & 0xFFFF) > halo_lds))
+                rare_list[atomicAdd(rare_n, 1)] = t;
+        }
+    }
     int64_t tfirst, tend;
     int tstep;
-    die_range(pb, npb, tiles, tfirst, tend, tstep);
-    for (int tile = (int)tfirst; tile < tend; tile += tstep) {
-        const int s = find_sys(tprefix, n_sys, tile);
-        if (!sflag[s]) {
-            // a system that keeps its list: its tile goes back on the list of
-            // tiles that the force pass takes first if its last build put it there
-            // (the binning launch before this one emptied that list)
-            if (lane == 0) {
-                const int32_t hn = halo_n[tile];
-                if (hn < 0 || (hn & 0xFFFF) > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
-            }
-            continue;
-        }
+    die_range(pb, npb, n_sys > 1 ? F.tile[nf] : tiles, tfirst, tend, tstep);
+    for (int x = (int)tfirst; x < tend; x += tstep) {
+        int s;
+        const int tile = flagged_tile(F, nf, tprefix, n_sys, x, s);
         const SysDev &S = sys[s];
         const double Ls[3] = {S.L[0], S.L[1], S.L[2]};
         const int bins[3] = {S.bins[0], S.bins[1], S.bins[2]};
@@ -1094,15 +1150,16 @@ __global__ __launch_bounds__(kWave) void k_cells_and_plan(
     int32_t *__restrict__ cell_size, int32_t *__restrict__ cell_idx, float4 *__restrict__ cell_xf, int cell_cap,
     double4 *__restrict__ xbuild, double4 *__restrict__ tref, int32_t *__restrict__ slow_list, int32_t *__restrict__ slow_n,
     char *__restrict__ plan, int64_t stride, const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *__restrict__ halo_n,
-    int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n)
+    int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, int64_t *fl)
 {
     if (*flag == 0) return;
     if ((int)blockIdx.x < n_sort) {
         cell_sort_waves<CPL>(blockIdx.x, n_sort, sys, cprefix, n_sys, pos, n_cells, cell_count, cell_size, cell_idx,
-                             cell_xf, cell_cap, sflag);
+                             cell_xf, cell_cap, sflag, fl);
     } else {
         plan_tiles((int)blockIdx.x - n_sort, (int)gridDim.x - n_sort, sys, tprefix, n_sys, tiles, pos,
-                   cell_count, cell_cap, xbuild, tref, slow_list, slow_n, plan, stride, sflag, halo_n, halo_lds, rare_list, rare_n);
+                   cell_count, cell_cap, xbuild, tref, slow_list, slow_n, plan, stride, sflag, halo_n, halo_lds, rare_list,
+                   rare_n, fl);
     }
 }
 
@@ -1173,7 +1230,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     int32_t *__restrict__ tile_ctr, int32_t *__restrict__ cell_count, int64_t n_cells,
     const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
     double4 *__restrict__ xbuild, double4 *__restrict__ tref, const int32_t *__restrict__ slow_list, const int32_t *__restrict__ slow_n,
-    const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *build_count, Status *st)
+    const int32_t *__restrict__ flag, int64_t *fl, int32_t *build_count, Status *st)
 {
     if (*flag == 0) return;
     // the binning counts, read by the cell sort and the plans, back to zero
@@ -1208,42 +1265,33 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                               nlist, nn, cap, halo, halo_n, halo_cap, xbuild, tref, halo_lds, rare_list,
                                               rare_n, st);
 
-    // Each die's workgroups walk one contiguous run of tiles.  With one
-    // system every tile of the run is built, and the tiles are handed out one
-    // at a time from the die's counter (cleared by the binning launch): a
-    // workgroup that meets costly tiles takes fewer, so the launch ends with
-    // its run.  One lane takes the tile after next as a tile starts.  A batch
-    // rebuilds only some systems, and a count for every tile it skips would
-    // cost more than it balances: there the workgroups of a die take every
-    // step-th tile of the run that is rebuilt.
-    const bool dyn = n_sys == 1;
+    // Each die's workgroups walk one contiguous run of the rebuilt systems'
+    // tiles, handed out one at a time from the die's counter (cleared by the
+    // binning launch): a workgroup that meets costly tiles takes fewer, so the
+    // launch ends with its run.  One lane takes the tile after next as a tile
+    // starts.
+    const Flagged F = flagged_at(fl, n_sys);
+    const int nf = n_sys > 1 ? *F.n : 1;
+    if (n_sys > 1) tiles = F.tile[nf];
     const int D = (int)gridDim.x < kDies ? (int)gridDim.x : kDies;
     const int die = (int)blockIdx.x % D;
-    int64_t first_, end_;
-    int tstep;
-    die_range(blockIdx.x, gridDim.x, tiles, first_, end_, tstep);
-    const int tend = (int)end_;
-    const int dfirst = (int)((int64_t)tiles * die / D);
+    const int dfirst = (int)((int64_t)tiles * die / D), tend = (int)((int64_t)tiles * (die + 1) / D);
     int32_t *ctr = tile_ctr + die * kTileCtrStride;
-    auto rebuilt_from = [&](int t) -> int {
-        while (t < tend && !sflag[find_sys(tprefix, n_sys, t)]) t += tstep;
-        return t;
+    auto tile_of = [&](int x) {
+        int s;
+        return flagged_tile(F, nf, tprefix, n_sys, x, s);
     };
     int grabbed = 0;
-    int t_cur, t_next;
-    if (dyn) {
-        if (tid == kWave) {
-            sh.grab[0] = take_tile(ctr);
-            sh.grab[1] = take_tile(ctr);
-        }
-        lds_barrier();
-        t_cur = dfirst + uni(sh.grab[0]);
-        t_next = dfirst + uni(sh.grab[1]);
-    } else {
-        t_cur = rebuilt_from((int)first_);
-        t_next = rebuilt_from(t_cur + tstep);
+    if (tid == kWave) {
+        sh.grab[0] = take_tile(ctr);
+        sh.grab[1] = take_tile(ctr);
     }
+    lds_barrier();
+    int x_next = dfirst + uni(sh.grab[1]);
+    int t_cur = dfirst + uni(sh.grab[0]);
     if (t_cur >= tend) return;
+    t_cur = tile_of(t_cur);
+    int t_next = x_next < tend ? tile_of(x_next) : t_cur;
 
     // a tile's plan: the header's first words, and this lane's segments of
     // kRounds rounds from r0 on (read whether they are there or not)
@@ -1291,8 +1339,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         asm volatile("" : "+v"(tid));
         const int lane = tid & (kWave - 1);
         const int tile = t_cur;
-        const bool more = t_next < tend;
-        if (dyn && tid == kWave) grabbed = take_tile(ctr);  // the tile after next
+        const bool more = x_next < tend;
+        if (tid == kWave) grabbed = take_tile(ctr);  // the tile after next
         const int nu = uni(__float_as_int(head[0].x)), nseg = uni(__float_as_int(head[0].y)),
                   pp = uni(__float_as_int(head[0].z));
         const float band = uni(head[0].w);
@@ -1509,7 +1557,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
                 }
             sh.cnt[wv][lane] = (uint16_t)c;
             if (lane == 0) sh.left[wv] = r < rounds;
-            if (dyn && tid == kWave) sh.grab[0] = grabbed;
+            if (tid == kWave) sh.grab[0] = grabbed;
             lds_barrier();
 
             // ---- 3. halo numbering, this pass's part of every row --------------------
@@ -1596,7 +1644,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         }
         if (!more) break;
         t_cur = t_next;
-        t_next = dyn ? dfirst + uni(sh.grab[0]) : rebuilt_from(t_next + tstep);
+        x_next = dfirst + uni(sh.grab[0]);
+        t_next = x_next < tend ? tile_of(x_next) : t_cur;
         lds_barrier();  // the rows are read, and the next index
     }
 }
@@ -1612,7 +1661,14 @@ void launch_bin(const LaunchCtx &L, const double4 *pos, int nvt_w)
     hipLaunchKernelGGL(k_bin, dim3(blocks), dim3(256), 0, L.stream, L.sys, L.tprefix_all, L.n_sys,
                        L.tiles_all, pos, L.cell_count, L.cell_idx, L.cell_cap, L.flag, L.sflag, L.status,
                        L.step_counter, L.slow_n, L.rare_n, L.tile_ctr, L.since, L.since_inc, L.tprefix_local, nvt_w,
-                       nvt_w > 0 && L.nvt ? L.khalf : nullptr, L.thermostat);
+                       nvt_w > 0 && L.nvt ? L.khalf : nullptr, L.thermostat, L.line_rows ? nullptr : L.flagged, L.cprefix);
+}
+
+void launch_flagged(const LaunchCtx &L)
+{
+    if (L.n_sys > 1)
+        hipLaunchKernelGGL(k_flagged, dim3(1), dim3(256), 0, L.stream, L.flagged, L.n_sys, L.sflag, L.tprefix_local,
+                           L.cprefix);
 }
 
 void launch_cell_sort(const LaunchCtx &L, const double4 *pos)
@@ -1633,13 +1689,13 @@ void launch_cell_sort(const LaunchCtx &L, const double4 *pos)
                            L.tprefix_local, L.tiles_local, pos, L.n_cells, L.cell_count, L.cell_size, L.cell_idx,
                            L.cell_xf, L.cell_cap, L.xbuild, L.tref, L.slow_list, L.slow_n, L.plan,
                            plan_stride(L.seg_cap), L.flag, L.sflag,
-                           L.halo_n, L.halo_lds, L.rare_list, L.rare_n);
+                           L.halo_n, L.halo_lds, L.rare_list, L.rare_n, L.flagged);
     else
         hipLaunchKernelGGL(k_cells_and_plan<2>, grid, dim3(kWave), 0, L.stream, (int)n_sort, L.sys, L.cprefix, L.n_sys,
                            L.tprefix_local, L.tiles_local, pos, L.n_cells, L.cell_count, L.cell_size, L.cell_idx,
                            L.cell_xf, L.cell_cap, L.xbuild, L.tref, L.slow_list, L.slow_n, L.plan,
                            plan_stride(L.seg_cap), L.flag, L.sflag,
-                           L.halo_n, L.halo_lds, L.rare_list, L.rare_n);
+                           L.halo_n, L.halo_lds, L.rare_list, L.rare_n, L.flagged);
 }
 
 int nlist_chunk() { return kWave; }
@@ -1657,6 +1713,8 @@ int build_seg_cap(double cell_mean)
     const int per_cell = (int)std::ceil((cell_mean + 3.0 * std::sqrt(cell_mean)) / kSeg);
     return std::min(std::max(150 * per_cell, kSegMin), 2040);
 }
+
+size_t flagged_list_bytes(int n_sys) { return flagged_bytes(n_sys); }
 
 size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows)
 {
@@ -1702,7 +1760,7 @@ static void fast_inst(const LaunchCtx &L, const double4 *pos, const int32_t *tag
                        L.n_sys, L.tiles_local, pos, tag, L.ptag, L.bond_stride, L.cell_xf, L.nlist, L.nn, L.nlist_cap, rs, L.halo,
                        L.halo_n, L.halo_cap, L.plan, plan_stride(L.seg_cap), L.halo_lds, L.rare_list, L.rare_n,
                        L.tile_ctr, L.cell_count, L.n_cells, L.cell_size, L.cell_idx, L.cell_cap, L.xbuild, L.tref, L.slow_list,
-                       L.slow_n, L.flag, L.sflag, L.build_count, L.status);
+                       L.slow_n, L.flag, L.flagged, L.build_count, L.status);
 }
 
 template <bool EXCL>

@@ -25,6 +25,41 @@ __device__ __forceinline__ int find_sys_cell(const int64_t *__restrict__ cprefix
     return lo;
 }
 
+// The systems that a rebuild takes, in order, with the prefixes of their cells
+// and local tiles: a batch rebuilds a few of its systems on most steps, and
+// launches that walk all of its tiles and cells, skipping most, leave their
+// work to the few workgroups whose run it falls into (64 systems of 3,200 to
+// 20,000 particles, us: binning 25, sort and plans 48, build 160 a step; now
+// FLGNOW).  One system alone is not looked up.
+struct Flagged {
+    const int64_t *cell;  // n + 1
+    const int32_t *tile;  // n + 1
+    const int32_t *sys;   // n
+    const int32_t *n;
+};
+__host__ __device__ inline size_t flagged_bytes(int n_sys)
+{
+    return sizeof(int64_t) * ((size_t)n_sys + 1) + sizeof(int32_t) * (2 * (size_t)n_sys + 2);
+}
+__device__ __forceinline__ Flagged flagged_at(int64_t *base, int n_sys)
+{
+    const int32_t *t = reinterpret_cast<const int32_t *>(base + n_sys + 1);
+    return {base, t, t + n_sys + 1, t + 2 * n_sys + 1};
+}
+
+// Local tile number x of the rebuilt systems' tiles.
+__device__ __forceinline__ int flagged_tile(const Flagged &F, int nf, const int32_t *__restrict__ tprefix, int n_sys,
+                                            int x, int &s)
+{
+    if (n_sys == 1) {
+        s = 0;
+        return x;
+    }
+    const int k = find_sys(F.tile, nf, x);
+    s = F.sys[k];
+    return tprefix[s] + (x - F.tile[k]);
+}
+
 // One wave per cell (wave w of W takes cells w, w + W, ...): members ranked
 // by their FP32 x coordinate relative to the cell's corner, ties by row index
 // (a total order on (bits, row), so the ranks are a permutation whatever the
@@ -40,13 +75,27 @@ __device__ __forceinline__ void cell_sort_waves(int64_t wfirst, int64_t wstep, c
                                                 const int32_t *__restrict__ cell_count,
                                                 int32_t *__restrict__ cell_size, int32_t *__restrict__ cell_idx,
                                                 float4 *__restrict__ cell_xf, int cell_cap,
-                                                const int32_t *__restrict__ sflag)
+                                                const int32_t *__restrict__ sflag, int64_t *fl)
 {
     const int lane = lane_id();
     const int64_t xs = cell_xf_stride(cell_cap);
-    for (int64_t c = wfirst; c < n_cells; c += wstep) {
-        const int s = find_sys_cell(cprefix, n_sys, c);
-        if (!sflag[s]) continue;  // this system keeps its list
+    // fl: the cells of the rebuilt systems; else (or with one system) all
+    // cells, those of systems that keep their lists skipped
+    const bool listed = fl && n_sys > 1;
+    const Flagged F = flagged_at(fl, n_sys);
+    const int nf = listed ? *F.n : 0;
+    const int64_t n = listed ? F.cell[nf] : n_cells;
+    for (int64_t x = wfirst; x < n; x += wstep) {
+        int64_t c = x;
+        int s;
+        if (listed) {
+            const int k = find_sys_cell(F.cell, nf, x);
+            s = F.sys[k];
+            c = cprefix[s] + (x - F.cell[k]);
+        } else {
+            s = find_sys_cell(cprefix, n_sys, c);
+            if (!sflag[s]) continue;  // this system keeps its list
+        }
         int m = cell_count[c];
         m = m < cell_cap ? m : cell_cap;
         const SysDev &S = sys[s];
@@ -66,8 +115,8 @@ __device__ __forceinline__ void cell_sort_waves(int64_t wfirst, int64_t wstep, c
             f[q] = make_float4(0.f, 0.f, 0.f, 0.f);
             ord[q] = INT64_MAX;
             if (k < m) {
-                const double4 x = pos[v[q]];
-                f[q] = make_float4((float)(x.x - ox), (float)(x.y - oy), (float)(x.z - oz), __int_as_float(v[q]));
+                const double4 y = pos[v[q]];
+                f[q] = make_float4((float)(y.x - ox), (float)(y.y - oy), (float)(y.z - oz), __int_as_float(v[q]));
                 const int32_t b = __float_as_int(f[q].x);
                 ord[q] = ((int64_t)(b ^ ((b >> 31) & 0x7FFFFFFF)) << 32) | (uint32_t)v[q];
             }

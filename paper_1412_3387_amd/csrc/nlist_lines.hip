@@ -465,7 +465,7 @@ __global__ __launch_bounds__(kWave) void k_cells_and_lines(
     if (*flag == 0) return;
     if ((int)blockIdx.x < n_sort) {
         cell_sort_waves<CPL>(blockIdx.x, n_sort, sys, cprefix, n_sys, pos, n_cells, cell_count, cell_size, cell_idx,
-                             cell_xf, cell_cap, sflag);
+                             cell_xf, cell_cap, sflag, nullptr);
     } else {
         __shared__ PlanShared ps;
         plan_lines(ps, (int)blockIdx.x - n_sort, (int)gridDim.x - n_sort, sys, tprefix, n_sys, tiles, pos,

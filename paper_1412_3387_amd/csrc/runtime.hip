@@ -36,7 +36,7 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 struct Layout {
     // byte offsets into the workspace
     size_t sysdev, tpl, tpa, cpre, status, flags, tile_ctr, sysflags, thermo, thermo_log, partials, khalf, thermostat;
-    size_t pos_alt, vel_alt, xbuild, tref, nlist, nn, cell_count, cell_size, cell_idx, cell_xf, halo, halo_n;
+    size_t pos_alt, vel_alt, xbuild, tref, flagged, nlist, nn, cell_count, cell_size, cell_idx, cell_xf, halo, halo_n;
     size_t ptag, pdir, prow, btmp, hash, slow_list, rare_list, plan, sort_ws, ghost_ws, total;
     // sizes
     int64_t rows, tiles_local, tiles_all, n_cells, nlist_entries, hash_slots;
@@ -309,6 +309,7 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
     Lo.pos_alt = take(sizeof(double4) * rows);
     Lo.vel_alt = take(sizeof(double4) * rows);
     Lo.xbuild = take(sizeof(double4) * rows);
+    Lo.flagged = take(flagged_list_bytes(n_sys));
     Lo.tref = take(sizeof(double4) * (size_t)std::max<int64_t>(tile, 1));
     // padded: the force pass reads up to force_row_over_read() entries past
     // any row's end
@@ -629,6 +630,7 @@ int hoomd_init(hoomd_ctx **out, const hoomd_params *params, int32_t n_sys, const
     L.nlist_cap = lay.nlist_cap;
     L.xbuild = ws_ptr<double4>(c, lay.xbuild);
     L.tref = ws_ptr<double4>(c, lay.tref);
+    L.flagged = ws_ptr<int64_t>(c, lay.flagged);
     L.ptag = ws_ptr<int32_t>(c, lay.ptag);
     L.pdir = ws_ptr<int32_t>(c, lay.pdir);
     L.prow = ws_ptr<int32_t>(c, lay.prow);
@@ -677,6 +679,7 @@ int hoomd_init(hoomd_ctx **out, const hoomd_params *params, int32_t n_sys, const
     if (e == hipSuccess) e = hipMemset(c->ws + lay.status, 0, sizeof(Status));
     if (e == hipSuccess) e = hipMemset(c->ws + lay.flags, 0, sizeof(int32_t) * 8);
     if (e == hipSuccess) e = hipMemset(c->ws + lay.tile_ctr, 0, sizeof(int32_t) * kTileCtrStride * kDies);
+    if (e == hipSuccess) e = hipMemset(c->ws + lay.flagged, 0, flagged_list_bytes(n_sys));
     if (e == hipSuccess) e = hipMemset(c->ws + lay.sysflags, 0, sizeof(int32_t) * 4 * (size_t)n_sys);
     if (e == hipSuccess) e = hipMemset(c->ws + lay.cell_count, 0, sizeof(int32_t) * (size_t)std::max<int64_t>(lay.n_cells, 1));
     if (e == hipSuccess) e = hipMemset(c->ws + lay.thermo, 0, sizeof(double) * 4 * n_sys);
@@ -1448,6 +1451,7 @@ int tune_now(hoomd_ctx *c, bool use_cache)
                                         launch_set_flags(c->L, flag, sflag, 1);
                                         c->L.flag = flag;
                                         c->L.sflag = sflag;
+                                        launch_flagged(c->L);
                                         launch_nlist(c->L, pos, c->arr.tag, w, b);
                                     },
                                     e0, e1);
