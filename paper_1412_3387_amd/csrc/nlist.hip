@@ -151,7 +151,7 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
             c = (cz * S.bins[1] + cy) * S.bins[0] + cx;
         }
         // one atomic per distinct cell of the wave, all of them in flight
-        // together (BINTIMES)
+        // together (waited for one by one, 60 us for 2,000,000 LJ rows; 31)
         int leader = lane, rank = 0, members = 0;
         uint64_t todo = __ballot(valid);
         while (todo) {
@@ -180,9 +180,9 @@ __global__ __launch_bounds__(256) void k_bin(const SysDev *__restrict__ sys,
 // tile-halo neighbour list
 // ---------------------------------------------------------------------------
 
-// LDS of a tile of the general build; CH members staged at once (0: all of a
-// tile with at most kGeneralStage, else none).
-constexpr int kGeneralStage = 896;
+// LDS of a tile of the general build; CH members staged at once (0: none, and
+// the rows' first kRowStage entries put together in their place).
+constexpr int kRowStage = 128;
 template <int CH>
 struct GeneralStage {
     double cx[CH], cy[CH], cz[CH];
@@ -190,37 +190,42 @@ struct GeneralStage {
 };
 template <>
 struct GeneralStage<0> {
-    double cx[kGeneralStage], cy[kGeneralStage], cz[kGeneralStage];
-    int32_t own[kTile];   // staged place of each row
+    uint16_t rows[kTile][kRowStage + 2];  // (the stride keeps the rows of a wave on different banks)
 };
 template <int CH>
 struct GeneralShared {
     union {
         GeneralStage<CH> stage;
         uint32_t bits[kCellBits / 32];    // stencil cells met, where the system has few enough cells
-        int32_t tmp[kKeys];               // stencil cells to sort, counts to scan, ranks of used slots
+        int32_t tmp[kKeys];               // stencil cells to sort
     };
     int32_t keys[kTile * kStencil + 1];   // distinct stencil cells, ascending
     uint16_t ustart[kTile * kStencil + 1];  // first slot of each distinct cell
     uint32_t used[kSlotMax / 32];
+    uint16_t ranks[kSlotMax / 32];        // used slots before each word
     int16_t su[kTile][kStencil];          // distinct-cell index of each row's stencil cell (-1: none)
     int8_t sm[kTile][kStencil];           // image code (mx+1) + 3 (my+1) + 9 (mz+1)
     int32_t scan[kBuildThreads / kWave];
     int32_t ext[6];                       // min / max cell offset from the first row
     int32_t info[4];                      // (unused), per-pair image flag, longest row
+    int32_t st[3][3];                     // the stencil's offsets
 };
 static_assert(kSlotMax < 65536, "slots of a tile in 16 bits");
 
-// Index of the largest entry <= x in the ascending 16-bit array a[0..n).
-__device__ __forceinline__ int upper_idx16(const uint16_t *a, int n, int x)
+// Index of the largest entry <= x[v] in the ascending array a[0..n), a[0] <=
+// x[v], for N values at once (a step's reads are in flight together).
+template <int N, typename T>
+__device__ __forceinline__ void upper_many(const T *a, int n, const int (&x)[N], int (&out)[N])
 {
-    int lo = 0, hi = n;
-    while (hi - lo > 1) {
-        const int mid = (lo + hi) >> 1;
-        if ((int)a[mid] <= x) lo = mid;
-        else hi = mid;
+#pragma unroll
+    for (int v = 0; v < N; ++v) out[v] = 0;
+    for (int step = n > 1 ? 1 << (31 - __clz(n - 1)) : 0; step > 0; step >>= 1) {
+#pragma unroll
+        for (int v = 0; v < N; ++v) {
+            const int c = out[v] + step;
+            if ((int)a[c < n ? c : 0] <= x[v] && c < n) out[v] = c;
+        }
     }
-    return lo;
 }
 
 // The general build of one tile by NT threads.  A launch has few such tiles, so
@@ -233,13 +238,14 @@ __device__ __forceinline__ int upper_idx16(const uint16_t *a, int n, int x)
 // bits of mixed-precision DPD sums).  Sort, chunks of 2,048 and a launch of its
 // own took 70 - 127 us; inside the framed launch, staged 512 at a time, that
 // launch took 147 us (DPD, 100,000 particles), 265 us (64 small systems) and
-// 189 us (LJ, 255,000), and reading directly 70, 187 and 156 us.  A tile whose
-// cells hold at most kGeneralStage members (a small system) reads them once.
+// 189 us (LJ, 255,000); reading directly, in FP32 with the exact test beside
+// r_list, it takes 57, 104 and 156 us.
 template <bool EXCL, int NT, int CH>
 __device__ __forceinline__ void general_tile(
     GeneralShared<CH> &sh, int tile, const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys,
     const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
-    const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx, int cell_cap,
+    const int32_t *__restrict__ cell_size, const int32_t *__restrict__ cell_idx,
+    const float4 *__restrict__ cell_xf, int cell_cap,
     uint16_t *__restrict__ nlist, int32_t *__restrict__ nn, int cap, int32_t *__restrict__ halo,
     int32_t *__restrict__ halo_n, int halo_cap, double4 *__restrict__ xbuild, double4 *__restrict__ tref, int halo_lds,
     int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, Status *st)
@@ -248,8 +254,11 @@ __device__ __forceinline__ void general_tile(
     constexpr int P = kWave / W;
     constexpr int kKpt = kKeys / NT;  // stencil keys per thread
     static_assert(kKeys % NT == 0 && kKeys <= 8 * NT, "key split");
-    const int tid = threadIdx.x;
-    const int lane = lane_id();
+    // (worked out anew for each tile: kept across them, what follows from it
+    // would take the registers)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & (kWave - 1);
     const int w = tid >> 6;
     const int pl = lane % P;
     const int sl = lane / P;
@@ -289,11 +298,13 @@ __device__ __forceinline__ void general_tile(
         sh.ext[3 + tid] = INT32_MIN;
     }
     if (tid == 0) sh.info[2] = 0;
+    if (tid < 9) sh.st[tid / 3][tid % 3] = S.st[tid / 3][tid % 3];
+    const int nst[3] = {S.nst[0], S.nst[1], S.nst[2]};
     const int nbits = marks ? ((int)ncell + 31) / 32 : 0;
     for (int k = tid; k < nbits; k += NT) sh.bits[k] = 0u;
     __syncthreads();
     // the key of every row's stencil cell, kept for the lookup below
-    int32_t mykeys[(kStencil + W - 1) / W];
+    int mykeys[(kStencil + W - 1) / W];
 #pragma unroll
     for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
         const int k = sl + q * W;
@@ -301,8 +312,8 @@ __device__ __forceinline__ void general_tile(
         int code = 0;
         if (k < kStencil) {
             const int ox = k % 3, oy = (k / 3) % 3, oz = k / 9;
-            if (active && ox < S.nst[0] && oy < S.nst[1] && oz < S.nst[2]) {
-                const int off[3] = {S.st[0][ox], S.st[1][oy], S.st[2][oz]};
+            if (active && ox < nst[0] && oy < nst[1] && oz < nst[2]) {
+                const int off[3] = {sh.st[0][ox], sh.st[1][oy], sh.st[2][oz]};
                 const int bins[3] = {bx, by, bz};
                 const int per[3] = {px, py, pz};
                 int cc[3];
@@ -418,10 +429,14 @@ __device__ __forceinline__ void general_tile(
         if (tid == 0) sh.ustart[nu] = (uint16_t)(nslot < 65535 ? nslot : 65535);
     }
     // each row's stencil cells as distinct-cell indices
+    {
+        int u[(kStencil + W - 1) / W];
+        upper_many(sh.keys, nu, mykeys, u);
 #pragma unroll
-    for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
-        const int k = sl + q * W;
-        if (k < kStencil) sh.su[t][k] = mykeys[q] == INT32_MAX ? (int16_t)-1 : (int16_t)upper_idx(sh.keys, nu, mykeys[q]);
+        for (int q = 0; q < (kStencil + W - 1) / W; ++q) {
+            const int k = sl + q * W;
+            if (k < kStencil) sh.su[t][k] = mykeys[q] == INT32_MAX ? (int16_t)-1 : (int16_t)u[q];
+        }
     }
     if (nslot > kSlotMax) {
         if (tid == 0) latch(st, 11 /*HALO_OVERFLOW*/, nslot);
@@ -449,16 +464,15 @@ __device__ __forceinline__ void general_tile(
     // offset of the particle inside its cell and the cell widths (FP32),
     // for the conservative per-cell distance test
     const float cellw[3] = {(float)(Lx / bx), (float)(Ly / by), (float)(Lz / bz)};
-    const float frel[3] = {(float)(xi.x - S.lo[0]) - (float)ci[0] * cellw[0],
-                           (float)(xi.y - S.lo[1]) - (float)ci[1] * cellw[1],
-                           (float)(xi.z - S.lo[2]) - (float)ci[2] * cellw[2]};
+    const float frel[3] = {(float)(xi.x - (S.lo[0] + ci[0] * (Lx / bx))), (float)(xi.y - (S.lo[1] + ci[1] * (Ly / by))),
+                           (float)(xi.z - (S.lo[2] + ci[2] * (Lz / bz)))};
     const float rl2f = (float)rl2 * 1.0001f + 1e-3f;
     // whether a stencil cell's nearest face lies beyond r_list of the row (FP32
     // with a relative margin: it never drops a cell that can hold a neighbour)
     auto out_of_reach = [&](int k) {
         const int ox = k % 3, oy = (k / 3) % 3, oz = k / 9;
-        const int offs[3] = {S.st[0][ox < S.nst[0] ? ox : 0], S.st[1][oy < S.nst[1] ? oy : 0],
-                             S.st[2][oz < S.nst[2] ? oz : 0]};
+        const int offs[3] = {sh.st[0][ox < nst[0] ? ox : 0], sh.st[1][oy < nst[1] ? oy : 0],
+                             sh.st[2][oz < nst[2] ? oz : 0]};
         float g2 = 0.f;
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
@@ -474,7 +488,9 @@ __device__ __forceinline__ void general_tile(
             const int q1 = q0 + CH < nslot ? q0 + CH : nslot;
             __syncthreads();
             for (int q = q0 + tid; q < q1; q += NT) {
-                const int u = upper_idx16(sh.ustart, nu, q);
+                int us[1];
+                upper_many(sh.ustart, nu, {q}, us);
+                const int u = us[0];
                 const int32_t j = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
                 const double4 xj = pos[j];
                 sh.stage.cx[q - q0] = xj.x;
@@ -546,84 +562,94 @@ __device__ __forceinline__ void general_tile(
         }
     } else {
         // Rows far apart share few cells: each of a row's W lanes reads the
-        // members of stencil cells of its own, V at a time (the loads of a
-        // batch are in flight together; instructions and their latency bound
-        // it: with the members of all cells dealt to the lanes one by one, the
-        // cell of each looked for, a launch with 23 such tiles took 143 us, now
-        // 94: 4,000 LJ particles).
+        // members of stencil cells of its own from the cells' FP32 copies, V
+        // at a time (a batch's loads are in flight together).  The latency of
+        // reads and instructions bounds it: with FP64 positions behind the row
+        // numbers, two reads one after the other, a launch with 23 such tiles
+        // took 93 us, now 72 (4,000 LJ particles); 16 at a time 72 and more
+        // registers, the lanes of a row side by side in one cell 85.
         constexpr int V = 8;
+        const int xstride = cell_xf_stride(cell_cap);
+        const float Lf[3] = {(float)Lx, (float)Ly, (float)Lz}, iLf[3] = {(float)iLx, (float)iLy, (float)iLz};
+        const float rlf = (float)sqrt(rl2), rl2s = (float)rl2;
         __syncthreads();
-        const bool staged = nslot <= kGeneralStage;
-        if (staged) {
-            for (int q = tid; q < nslot; q += NT) {
-                const int u = upper_idx16(sh.ustart, nu, q);
-                const int32_t j = cell_idx[(cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u])];
-                const double4 xj = pos[j];
-                sh.stage.cx[q] = xj.x;
-                sh.stage.cy[q] = xj.y;
-                sh.stage.cz[q] = xj.z;
-                const int64_t o = j - (row0 + r0);
-                if (o >= 0 && o < kTile) sh.stage.own[o] = q;
-            }
-            __syncthreads();
-        }
-        const int own = staged && active ? sh.stage.own[t] : -1;
         for (int k = sl; __ballot(k < kStencil); k += W) {
             const int u = k < kStencil && !out_of_reach(k) ? sh.su[t][k] : -1;
             const int start = u < 0 ? 0 : sh.ustart[u];
             const int m = u < 0 ? 0 : sh.ustart[u + 1] - start;
-            const int64_t at = u < 0 ? 0 : (cell0 + sh.keys[u]) * cell_cap;
+            const float4 *p = cell_xf + (u < 0 ? 0 : (cell0 + sh.keys[u]) * xstride);
+            // the row in the cell's frame, at the image beside the cell
+            const int o[3] = {k % 3, (k / 3) % 3, k / 9};
+            float xr[3], amax = 0.f;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                xr[a] = frel[a] - (u < 0 ? 0.f : (float)sh.st[a][o[a]]) * cellw[a];
+                amax = fmaxf(amax, fmaxf(fabsf(xr[a]), cellw[a]));
+            }
+            // where |x_j - x_i|^2 - r_list^2 in FP32 does not decide: with u =
+            // 2^-24, each separation of a pair within about r_list is off by at
+            // most eta = 4 u (row + r_list + cell), which moves r^2 by 2 sqrt(3)
+            // r_list eta + 3 eta^2; its three squares, their sums and r_list^2
+            // round to 6 u r^2 more.  Doubled.
+            const float eta = 0x1p-22f * (amax + rlf + amax);
+            const float band = 2.f * (3.4642f * rlf * eta + 3.f * eta * eta + 0x1p-21f * rl2s);
             for (int m0 = 0; __ballot(m0 < m); m0 += V) {
-                bool ok[V];
-                int32_t jj[V];
-                double ddx[V], ddy[V], ddz[V];
-                if (!staged || EXCL) {
+                float4 f[V];
 #pragma unroll
-                    for (int v = 0; v < V; ++v) jj[v] = cell_idx[m0 + v < m ? at + m0 + v : 0];
-                }
-                if (staged) {
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const int q = m0 + v < m ? start + m0 + v : 0;
-                        ddx[v] = sh.stage.cx[q];
-                        ddy[v] = sh.stage.cy[q];
-                        ddz[v] = sh.stage.cz[q];
-                        ok[v] = m0 + v < m && q != own;
-                    }
-                } else {
-#pragma unroll
-                    for (int v = 0; v < V; ++v) {
-                        const int64_t j = m0 + v < m ? jj[v] : i;
-                        ddx[v] = pos[j].x;
-                        ddy[v] = pos[j].y;
-                        ddz[v] = pos[j].z;
-                        ok[v] = j != i;
-                    }
-                }
+                for (int v = 0; v < V; ++v) f[v] = p[m0 + v < m ? m0 + v : 0];
+                uint32_t hits = 0, near = 0;
 #pragma unroll
                 for (int v = 0; v < V; ++v) {
+                    float d[3] = {f[v].x - xr[0], f[v].y - xr[1], f[v].z - xr[2]};
+                    if (few) {
+                        // fewer than 3 cells: several images share a cell, take the nearest
+#pragma unroll
+                        for (int a = 0; a < 3; ++a)
+                            if (few_axis[a]) d[a] = __builtin_fmaf(-Lf[a], rintf(d[a] * iLf[a]), d[a]);
+                    }
+                    const float e = __builtin_fmaf(d[0], d[0], __builtin_fmaf(d[1], d[1], d[2] * d[2])) - rl2s;
+                    const bool ok = m0 + v < m && __float_as_int(f[v].w) != (int32_t)i;
+                    hits |= ok && e < -band ? 1u << v : 0u;
+                    near |= ok && fabsf(e) <= band ? 1u << v : 0u;
+                }
+                while (near) {
                     // (the minimum image: for a pair inside r_list the shift of
-                    // its cell, and the nearest image where a cell has several)
-                    double dx = ddx[v] - xi.x, dy = ddy[v] - xi.y, dz = ddz[v] - xi.z;
+                    // its cell, and the nearest where a cell has several)
+                    const uint32_t bit = near & (0u - near);
+                    near &= near - 1u;
+                    const double4 xj = pos[__float_as_int(p[m0 + __ffs((int)bit) - 1].w)];
+                    double dx = xj.x - xi.x, dy = xj.y - xi.y, dz = xj.z - xi.z;
                     dx = px ? min_image(dx, Lx, iLx) : dx;
                     dy = py ? min_image(dy, Ly, iLy) : dy;
                     dz = pz ? min_image(dz, Lz, iLz) : dz;
-                    bool hit = ok[v] && norm2_exact(dx, dy, dz) < rl2;
-                    if constexpr (EXCL) {
-                        if (hit) {
-                            const int32_t tj = tag[jj[v]];
+                    hits |= norm2_exact(dx, dy, dz) < rl2 ? bit : 0u;
+                }
+                if constexpr (EXCL) {
+                    int32_t tj[V];
 #pragma unroll
-                            for (int b = 0; b < kMaxBondCap; ++b) hit = hit && (part[b] != tj);
-                        }
+                    for (int v = 0; v < V; ++v) tj[v] = tag[hits >> v & 1u ? __float_as_int(f[v].w) : (int32_t)i];
+#pragma unroll
+                    for (int v = 0; v < V; ++v) {
+                        bool keep = true;
+#pragma unroll
+                        for (int b = 0; b < kMaxBondCap; ++b) keep = keep && part[b] != tj[v];
+                        hits &= keep ? ~0u : ~(1u << v);
                     }
-                    const uint64_t mask = __ballot(hit) & seg;
-                    if (hit) {
-                        const int q = start + m0 + v;
-                        const int p = ntot + __popcll(mask & below);
-                        if (p < cap) nlist[rowbase + (int64_t)p * kTile] = (uint16_t)q;
-                        atomicOr(&sh.used[q >> 5], 1u << (q & 31));
-                    }
-                    ntot += __popcll(mask);
+                }
+                // the lanes of a row append one after the other
+                int p2 = ntot;
+                const int c = __popc(hits);
+#pragma unroll
+                for (int q = 0; q < W; ++q) {
+                    const int cq = __shfl(c, q * P + pl, kWave);
+                    p2 += q < sl ? cq : 0;
+                    ntot += cq;
+                }
+                for (; hits; hits &= hits - 1u, ++p2) {
+                    const int q = start + m0 + __ffs((int)hits) - 1;
+                    atomicOr(&sh.used[q >> 5], 1u << (q & 31));
+                    if (p2 < kRowStage) sh.stage.rows[t][p2] = (uint16_t)q;
+                    else if (p2 < cap) nlist[rowbase + (int64_t)p2 * kTile] = (uint16_t)q;
                 }
             }
         }
@@ -643,11 +669,10 @@ __device__ __forceinline__ void general_tile(
             c += n[k];
         }
         int p = block_rank<NT>(c, sh.scan, nhalo);
-        // (the staged members are no longer read)
 #pragma unroll
         for (int k = 0; k < kPer; ++k) {
             const int q = kPer * tid + k;
-            if (q < nwords) sh.tmp[q] = p;
+            if (q < nwords) sh.ranks[q] = (uint16_t)p;
             p += n[k];
         }
     }
@@ -664,18 +689,16 @@ __device__ __forceinline__ void general_tile(
     for (int q0 = tid; q0 < nslot; q0 += 4 * NT) {
         int64_t at[4];
         int32_t j[4];
-        int h[4];
+        int h[4], q[4], u[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) q[v] = q0 + v * NT < nslot ? q0 + v * NT : nslot - 1;
+        upper_many(sh.ustart, nu, q, u);
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const int q = q0 + v * NT;
-            const uint32_t word = q < nslot ? sh.used[q >> 5] : 0u;
-            h[v] = -1;
-            at[v] = 0;
-            if (word & (1u << (q & 31))) {
-                const int u = upper_idx16(sh.ustart, nu, q);
-                h[v] = sh.tmp[q >> 5] + __popc(word & ((1u << (q & 31)) - 1u));
-                at[v] = (cell0 + sh.keys[u]) * cell_cap + (q - sh.ustart[u]);
-            }
+            const uint32_t word = q0 + v * NT < nslot ? sh.used[q[v] >> 5] : 0u;
+            const uint32_t bit = 1u << (q[v] & 31);
+            h[v] = word & bit ? sh.ranks[q[v] >> 5] + __popc(word & (bit - 1u)) : -1;
+            at[v] = (cell0 + sh.keys[u[v]]) * cell_cap + (q[v] - sh.ustart[u[v]]);
         }
 #pragma unroll
         for (int v = 0; v < 4; ++v) j[v] = cell_idx[at[v]];
@@ -697,12 +720,21 @@ __device__ __forceinline__ void general_tile(
         for (int k0 = sl; k0 < n; k0 += V * W) {
             int q[V];
 #pragma unroll
-            for (int v = 0; v < V; ++v) q[v] = k0 + v * W < n ? nlist[rowbase + (int64_t)(k0 + v * W) * kTile] : 0;
+            for (int v = 0; v < V; ++v) {
+                const int k = k0 + v * W;
+                q[v] = 0;
+                if constexpr (CH == 0) {
+                    if (k < n && k < kRowStage) q[v] = sh.stage.rows[t][k];
+                    else if (k < n) q[v] = nlist[rowbase + (int64_t)k * kTile];
+                } else {
+                    if (k < n) q[v] = nlist[rowbase + (int64_t)k * kTile];
+                }
+            }
 #pragma unroll
             for (int v = 0; v < V; ++v)
                 if (k0 + v * W < n)
                     nlist[rowbase + (int64_t)(k0 + v * W) * kTile] =
-                        (uint16_t)(sh.tmp[q[v] >> 5] + __popc(sh.used[q[v] >> 5] & ((1u << (q[v] & 31)) - 1u)));
+                        (uint16_t)(sh.ranks[q[v] >> 5] + __popc(sh.used[q[v] >> 5] & ((1u << (q[v] & 31)) - 1u)));
         }
         if (sl == 0) {
             nn[i] = n;
@@ -730,7 +762,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
     __shared__ GeneralShared<kChunk> sh;
     for (int it = blockIdx.x; it < ntiles; it += gridDim.x)
         general_tile<EXCL, kBuildThreads, kChunk>(sh, list[it], sys, tprefix, n_sys, pos, tag, ptag, cell_size,
-                                                  cell_idx, cell_cap, nlist, nn, cap, halo, halo_n, halo_cap, xbuild,
+                                                  cell_idx, nullptr, cell_cap, nlist, nn, cap, halo, halo_n, halo_cap, xbuild,
                                                   tref, halo_lds, rare_list, rare_n, st);
 }
 
@@ -1261,7 +1293,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // they added it to most builds, and an empty launch to every step).
     for (int it = blockIdx.x; it < *slow_n; it += gridDim.x)
         general_tile<EXCL, NT, 0>(*reinterpret_cast<GeneralShared<0> *>(lds_all), slow_list[it],
-                                              sys, tprefix, n_sys, pos, tag, ptag, cell_size, cell_idx, cell_cap,
+                                              sys, tprefix, n_sys, pos, tag, ptag, cell_size, cell_idx, cell_xf, cell_cap,
                                               nlist, nn, cap, halo, halo_n, halo_cap, xbuild, tref, halo_lds, rare_list,
                                               rare_n, st);
 
