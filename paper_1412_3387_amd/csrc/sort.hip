@@ -9,6 +9,10 @@
 
 namespace md {
 
+// Tiles of a sort whose scatter sums the digit counts itself: 64 of them are
+// eight rounds of reads, about as long as the scan's launches.
+constexpr int64_t kFewTiles = 64;
+
 static size_t a256(size_t x) { return (x + 255) / 256 * 256; }
 
 size_t sort_workspace_bytes(int64_t rows)
@@ -75,6 +79,8 @@ __global__ void k_morton_keys(const SysDev *__restrict__ sys, const int32_t *__r
     vals[i] = (int32_t)i;
 }
 
+// Digit counts of a tile: hist[tile][digit] where the scatter sums them itself
+// (kFewTiles or fewer), else hist[digit][tile] for the scan.
 __global__ __launch_bounds__(256) void k_radix_hist(const uint64_t *__restrict__ keys, int64_t rows,
                                                     int shift, int64_t tiles, int32_t *__restrict__ hist)
 {
@@ -87,11 +93,15 @@ __global__ __launch_bounds__(256) void k_radix_hist(const uint64_t *__restrict__
         if (k < rows) atomicAdd(&h[(keys[k] >> shift) & 0xFF], 1);
     }
     __syncthreads();
-    hist[(int64_t)threadIdx.x * tiles + blockIdx.x] = h[threadIdx.x];
+    hist[tiles <= kFewTiles ? (int64_t)blockIdx.x * 256 + threadIdx.x : (int64_t)threadIdx.x * tiles + blockIdx.x] =
+        h[threadIdx.x];
 }
 
 // Stable scatter.  Wave w of the block owns rows [w*256, w*256+256) of the
-// tile, visited in 4 chunks of 64 in order.
+// tile, visited in 4 chunks of 64 in order.  With at most kFewTiles tiles each
+// block sums the digit counts before its own (a thread per digit, reads
+// side by side) and scans the digits: launches bound a small sort, and the
+// three of the scan go.
 __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restrict__ kin,
                                                        const int32_t *__restrict__ vin,
                                                        uint64_t *__restrict__ kout,
@@ -100,6 +110,7 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restric
                                                        const int32_t *__restrict__ offs)
 {
     __shared__ int32_t wc[4][256];
+    __shared__ int32_t first[256], ws[4];
     const int w = threadIdx.x >> 6;
     const int lane = lane_id();
     for (int d = lane; d < 256; d += 64) wc[w][d] = 0;
@@ -131,41 +142,79 @@ __global__ __launch_bounds__(256) void k_radix_scatter(const uint64_t *__restric
         // the lowest lane of each digit group advances the wave counter
         if (ok[c] && (m & lt) == 0) wc[w][d] = before + __popcll(m);
     }
+    if (tiles <= kFewTiles) {
+        int32_t before = 0, all = 0;  // this thread's digit: in the tiles before this one, in all
+        for (int t0 = 0; t0 < (int)tiles; t0 += 8) {
+            int32_t n[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) n[u] = t0 + u < (int)tiles ? offs[(t0 + u) * 256 + (int)threadIdx.x] : 0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                before += t0 + u < (int)blockIdx.x ? n[u] : 0;
+                all += n[u];
+            }
+        }
+        int32_t inc = all;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int32_t y = __shfl_up(inc, off, kWave);
+            if (lane >= off) inc += y;
+        }
+        if (lane == kWave - 1) ws[w] = inc;
+        __syncthreads();
+        for (int v = 0; v < w; ++v) inc += ws[v];
+        first[threadIdx.x] = inc - all + before;
+    } else {
+        first[threadIdx.x] = offs[(int64_t)threadIdx.x * tiles + blockIdx.x];
+    }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         if (!ok[c]) continue;
-        int p = offs[(int64_t)dig[c] * tiles + blockIdx.x] + local[c];
+        int p = first[dig[c]] + local[c];
         for (int v = 0; v < w; ++v) p += wc[v][dig[c]];
         kout[p] = key[c];
         vout[p] = val[c];
     }
 }
 
+// Rows in their new order (partner entries, tags and owner directions, with
+// them), into scratch; k_rows_back returns them.  A launch each way in place
+// of two gathers and a copy per array.
 __global__ void k_gather_rows(int64_t rows, const int32_t *__restrict__ perm, const double4 *__restrict__ pos,
                               const double4 *__restrict__ vel, const int32_t *__restrict__ tag,
                               double4 *__restrict__ pos_o, double4 *__restrict__ vel_o,
-                              int32_t *__restrict__ tag_o)
-{
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= rows) return;
-    const int32_t o = perm[k];
-    pos_o[k] = pos[o];
-    vel_o[k] = vel[o];
-    tag_o[k] = tag[o];
-}
-
-// The partner entries (tags and owner directions) move with their rows.
-__global__ void k_gather_bonds(int64_t rows, int stride, const int32_t *__restrict__ perm,
-                               const int32_t *__restrict__ ptag, const int32_t *__restrict__ pdir,
-                               int32_t *__restrict__ ptag_o, int32_t *__restrict__ pdir_o)
+                              int32_t *__restrict__ tag_o, int stride, const int32_t *__restrict__ ptag,
+                              const int32_t *__restrict__ pdir, int32_t *__restrict__ ptag_o,
+                              int32_t *__restrict__ pdir_o)
 {
     const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= rows) return;
     const int64_t o = perm[k];
+    pos_o[k] = pos[o];
+    vel_o[k] = vel[o];
+    tag_o[k] = tag[o];
     for (int s = 0; s < stride; ++s) {
         ptag_o[k * stride + s] = ptag[o * stride + s];
         pdir_o[k * stride + s] = pdir[o * stride + s];
+    }
+}
+
+__global__ void k_rows_back(int64_t rows, const double4 *__restrict__ pos, const double4 *__restrict__ vel,
+                            const int32_t *__restrict__ tag, double4 *__restrict__ pos_o,
+                            double4 *__restrict__ vel_o, int32_t *__restrict__ tag_o, int stride,
+                            const int32_t *__restrict__ ptag, const int32_t *__restrict__ pdir,
+                            int32_t *__restrict__ ptag_o, int32_t *__restrict__ pdir_o)
+{
+    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (k >= rows) return;
+    pos_o[k] = pos[k];
+    vel_o[k] = vel[k];
+    tag_o[k] = tag[k];
+    // (entry k of each of the stride runs of rows entries: coalesced)
+    for (int s = 0; s < stride; ++s) {
+        ptag_o[s * rows + k] = ptag[s * rows + k];
+        pdir_o[s * rows + k] = pdir[s * rows + k];
     }
 }
 
@@ -282,25 +331,17 @@ int queue_morton_sort(const LaunchCtx &L, const SortBuffers &B, double4 *pos, do
         const int shift = 8 * p;
         hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)B.tiles), dim3(256), 0, L.stream, B.keys[cur],
                            B.rows, shift, B.tiles, B.hist);
-        launch_scan(L.stream, B.hist, B.hist, 256 * B.tiles, nullptr, B.hist_sums);
+        if (B.tiles > kFewTiles) launch_scan(L.stream, B.hist, B.hist, 256 * B.tiles, nullptr, B.hist_sums);
         hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)B.tiles), dim3(256), 0, L.stream, B.keys[cur],
                            B.vals[cur], B.keys[cur ^ 1], B.vals[cur ^ 1], B.rows, shift, B.tiles, B.hist);
         cur ^= 1;
     }
     const int blocks = (int)((B.rows + 255) / 256);
-    hipLaunchKernelGGL(k_gather_rows, dim3(blocks), dim3(256), 0, L.stream, B.rows, B.vals[cur], pos, vel,
-                       tag, pos_tmp, vel_tmp, B.tag_tmp);
-    if (hipMemcpyAsync(pos, pos_tmp, sizeof(double4) * B.rows, hipMemcpyDeviceToDevice, L.stream) != hipSuccess) return 1;
-    if (hipMemcpyAsync(vel, vel_tmp, sizeof(double4) * B.rows, hipMemcpyDeviceToDevice, L.stream) != hipSuccess) return 1;
-    if (hipMemcpyAsync(tag, B.tag_tmp, sizeof(int32_t) * B.rows, hipMemcpyDeviceToDevice, L.stream) != hipSuccess) return 1;
-    if (L.bond_stride > 0) {
-        // the partner-row table is rebuilt after the sort: it serves as scratch
-        const size_t nb = sizeof(int32_t) * (size_t)B.rows * (size_t)L.bond_stride;
-        hipLaunchKernelGGL(k_gather_bonds, dim3(blocks), dim3(256), 0, L.stream, B.rows, L.bond_stride, B.vals[cur],
-                           L.ptag, L.pdir, L.prow, L.btmp);
-        if (hipMemcpyAsync(L.ptag, L.prow, nb, hipMemcpyDeviceToDevice, L.stream) != hipSuccess) return 1;
-        if (hipMemcpyAsync(L.pdir, L.btmp, nb, hipMemcpyDeviceToDevice, L.stream) != hipSuccess) return 1;
-    }
+    // the partner-row table is rebuilt after the sort: it serves as scratch
+    hipLaunchKernelGGL(k_gather_rows, dim3(blocks), dim3(256), 0, L.stream, B.rows, B.vals[cur], pos, vel, tag, pos_tmp,
+                       vel_tmp, B.tag_tmp, L.bond_stride, L.ptag, L.pdir, L.prow, L.btmp);
+    hipLaunchKernelGGL(k_rows_back, dim3(blocks), dim3(256), 0, L.stream, B.rows, pos_tmp, vel_tmp, B.tag_tmp, pos, vel,
+                       tag, L.bond_stride, L.prow, L.btmp, L.ptag, L.pdir);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
