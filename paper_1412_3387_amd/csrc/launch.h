@@ -134,6 +134,8 @@ void launch_half_step(const LaunchCtx &L, double4 *pos, double4 *vel, const void
 // partials (w per tile) of its systems, then advance xi and eta.
 void launch_nvt_update(const LaunchCtx &L, int w);
 void launch_disp_check(const LaunchCtx &L, const double4 *pos, int32_t *flag, int32_t *sflag);
+// The flags cleared, then the displacement check (word: a counter kept at 0).
+void launch_disp_flags(const LaunchCtx &L, const double4 *pos, int32_t *flag, int32_t *sflag, uint32_t *word);
 size_t force_lds_bytes(int pair, int halo_cap, int nlist_cap);
 int force_row_over_read();
 int force_halo_entry_bytes(int pair);

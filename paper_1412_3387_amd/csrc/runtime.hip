@@ -452,7 +452,7 @@ size_t mark(hoomd_ctx *c)
 }
 
 // Device flags: 0 and 1 rebuild flags of the two buffer parities, 2 the flag
-// of explicit builds, 3 unused, 4 build counter, 5 step counter of replayed steps, 6
+// of explicit builds, 3 the word of their displacement check, 4 build counter, 5 step counter of replayed steps, 6
 // tiles passed from the framed build to the general one, 7 tiles the force
 // pass takes first.
 int32_t *flag_ptr(hoomd_ctx *c, int k) { return ws_ptr<int32_t>(c, c->lay.flags) + k; }
@@ -775,8 +775,7 @@ int build_nlist(hoomd_ctx *c, int32_t force_rebuild)
         }
         launch_set_flags(c->L, flag, sflag, 1);
     } else {
-        launch_set_flags(c->L, flag, sflag, 0);
-        launch_disp_check(c->L, pos, flag, sflag);
+        launch_disp_flags(c->L, pos, flag, sflag, reinterpret_cast<uint32_t *>(flag_ptr(c, 3)));
     }
     queue_rebuild(c, pos, c->arr.tag, 2, 0);
     c->built = true;
