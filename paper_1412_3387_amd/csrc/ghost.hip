@@ -164,9 +164,10 @@ __global__ __launch_bounds__(kGhostBlock) void k_ghost_mask(GhostArgs g, int32_t
     }
 }
 
-__global__ void k_ghost_totals(const int32_t *__restrict__ scanned, const int32_t *__restrict__ total,
-                               int nblocks, int32_t *__restrict__ counts, int32_t *__restrict__ offsets,
-                               int64_t send_cap, int64_t list_cap, Status *st)
+__device__ __forceinline__ void ghost_totals(const int32_t *__restrict__ scanned, const int32_t *__restrict__ total,
+                                             int nblocks, int32_t *__restrict__ counts,
+                                             int32_t *__restrict__ offsets, int64_t send_cap, int64_t list_cap,
+                                             Status *st)
 {
     const int d = threadIdx.x;
     if (d < 26) {
@@ -180,9 +181,16 @@ __global__ void k_ghost_totals(const int32_t *__restrict__ scanned, const int32_
 }
 
 __global__ __launch_bounds__(kGhostBlock) void k_ghost_scatter(GhostArgs g, const int32_t *__restrict__ scanned,
-                                                              int nblocks)
+                                                              int nblocks, int64_t list_cap)
 {
     __shared__ int32_t wc[kGhostBlock / 64][26];
+    // this block's first place in each direction, read side by side (one read
+    // per direction in the loop below, each waited for, made a selection over
+    // 4,000 rows 15 us)
+    __shared__ int32_t first[26];
+    if (threadIdx.x < 26) first[threadIdx.x] = scanned[(int64_t)threadIdx.x * nblocks + blockIdx.x];
+    if (blockIdx.x == 0)
+        ghost_totals(scanned, g.total, nblocks, g.counts, g.offsets, g.send_cap, list_cap, g.status);
     const int r = blockIdx.x * kGhostBlock + threadIdx.x;
     const uint32_t m = r < g.n_local ? g.mask[r] : 0u;
     wave_dir_counts(m, wc);
@@ -193,7 +201,7 @@ __global__ __launch_bounds__(kGhostBlock) void k_ghost_scatter(GhostArgs g, cons
         const bool sel = (m >> d) & 1u;
         const uint64_t b = __ballot(sel);
         if (!sel) continue;
-        int64_t p = scanned[(int64_t)d * nblocks + blockIdx.x] + __popcll(b & lt);
+        int64_t p = first[d] + __popcll(b & lt);
         for (int v = 0; v < w; ++v) p += wc[v][d];
         if (g.list && p < g.list_cap) g.list[p] = r;
         if (p < g.send_cap) pack_record(g, p, g.row0 + r, dir_of_index(d));
@@ -313,9 +321,7 @@ int queue_ghost_select(hipStream_t stream, const GhostBuffers &B, const GhostArg
     launch_scan(stream, B.blk_counts, B.blk_counts, 26 * (int64_t)nb, g.total, B.blk_sums);
     // without a stored list (list == nullptr) only the send buffer bounds the total
     const int64_t list_cap = g.list ? g.list_cap : INT64_MAX;
-    hipLaunchKernelGGL(k_ghost_totals, dim3(1), dim3(64), 0, stream, B.blk_counts, g.total, nb, g.counts,
-                       g.offsets, g.send_cap, list_cap, g.status);
-    hipLaunchKernelGGL(k_ghost_scatter, dim3(nb), dim3(kGhostBlock), 0, stream, g, B.blk_counts, nb);
+    hipLaunchKernelGGL(k_ghost_scatter, dim3(nb), dim3(kGhostBlock), 0, stream, g, B.blk_counts, nb, list_cap);
     return hipGetLastError() == hipSuccess ? 0 : 1;
 }
 
@@ -329,9 +335,7 @@ int queue_migrate(hipStream_t stream, const GhostBuffers &B, const GhostArgs &g,
     hipLaunchKernelGGL(k_migrate_mask, dim3(nb), dim3(kGhostBlock), 0, stream, g, B.blk_counts, nb, B.stay);
     launch_scan(stream, B.blk_counts, B.blk_counts, 26 * (int64_t)nb, g.total, B.blk_sums);
     const int64_t list_cap = g.list ? g.list_cap : INT64_MAX;
-    hipLaunchKernelGGL(k_ghost_totals, dim3(1), dim3(64), 0, stream, B.blk_counts, g.total, nb, g.counts,
-                       g.offsets, g.send_cap, list_cap, g.status);
-    hipLaunchKernelGGL(k_ghost_scatter, dim3(nb), dim3(kGhostBlock), 0, stream, g, B.blk_counts, nb);
+    hipLaunchKernelGGL(k_ghost_scatter, dim3(nb), dim3(kGhostBlock), 0, stream, g, B.blk_counts, nb, list_cap);
     // staying rows: their new places (the scan's total is the count that
     // stays), then the compacted copy into the scratch arrays
     if (g.n_local > 0) {
