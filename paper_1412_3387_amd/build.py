@@ -17,7 +17,7 @@ CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libhoomd_mi355x.so")
 SOURCES = ["nlist.hip", "nlist_lines.hip", "forces.hip", "sort.hip", "ghost.hip", "bonds.hip", "runtime.hip"]
-HEADERS = ["device.h", "launch.h", "nlist_dev.h", "sort.h", "ghost.h"]
+HEADERS = ["device.h", "launch.h", "nlist_dev.h", "nlist_general.h", "sort.h", "ghost.h"]
 ARCH = "gfx950"
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -27,6 +27,7 @@
 #include <algorithm>
 
 #include "nlist_dev.h"
+#include "nlist_general.h"
 
 namespace md {
 
@@ -486,6 +487,8 @@ __device__ __forceinline__ int4 next_header(const int4 *hdr, int tile)
 
 // NT threads per workgroup: NT / 64 waves share a tile, a wave scans a row at
 // a time.
+constexpr int kLineBytes = (int)((sizeof(LineShared) + 15) / 16 * 16);
+
 template <bool EXCL, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_build_lines(
     const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
@@ -496,6 +499,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     int32_t *__restrict__ halo, int32_t *__restrict__ halo_n, int halo_cap, LinePlan plan,
     int halo_lds, int32_t *__restrict__ rare_list, int32_t *__restrict__ rare_n, int32_t *__restrict__ tile_ctr,
     int32_t *__restrict__ cell_count, int64_t n_cells,
+    double4 *__restrict__ xbuild, double4 *__restrict__ tref, const int32_t *__restrict__ slow_list,
+    const int32_t *__restrict__ slow_n,
     const int32_t *__restrict__ flag, const int32_t *__restrict__ sflag, int32_t *build_count, Status *st)
 {
     if (*flag == 0) return;
@@ -503,8 +508,21 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // for the next build
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += (int64_t)gridDim.x * blockDim.x)
         cell_count[c] = 0;
-    __shared__ LineShared sh;
-    extern __shared__ uint16_t srows[];  // [kTile][rstride]: staged slot of each hit
+    extern __shared__ float4 lds_lines[];
+    LineShared &sh = *reinterpret_cast<LineShared *>(lds_lines);
+    // [kTile][rstride]: staged slot of each hit
+    uint16_t *const srows = reinterpret_cast<uint16_t *>(reinterpret_cast<char *>(lds_lines) + kLineBytes);
+    // The tiles that the plan passed on, first, where their time hides (as a
+    // launch of their own 54 us of most builds of 1,000,000 particles, and an
+    // empty launch of every other step); staged and in the order of chunks as
+    // in workgroups of 512 always.
+    if constexpr (NT == kBuildThreads) {
+        for (int it = blockIdx.x; it < *slow_n; it += gridDim.x)
+            general_tile<EXCL, NT, kChunk>(*reinterpret_cast<GeneralShared<kChunk> *>(lds_lines), slow_list[it], sys,
+                                           tprefix, n_sys, pos, tag, ptag, cell_size, cell_idx, nullptr, cell_cap,
+                                           nlist, nn, cap, halo, halo_n, halo_cap, xbuild, tref, halo_lds, rare_list,
+                                           rare_n, st);
+    }
     const int tid = threadIdx.x;
     const int lane = lane_id();
     const int wv = tid >> 6;
@@ -933,7 +951,10 @@ size_t line_plan_bytes(int64_t tiles)
            r(sizeof(float) * t * kTile * kRuns);
 }
 
-static int line_dyn(int cap) { return kTile * nlist_row_stride(cap) * 2; }
+static int line_dyn(int cap)
+{
+    return std::max(kLineBytes + kTile * nlist_row_stride(cap) * 2, (int)sizeof(GeneralShared<kChunk>));
+}
 
 hipError_t prepare_lines(int cap)
 {
@@ -971,7 +992,8 @@ void launch_build_lines(const LaunchCtx &L, const double4 *pos, const int32_t *t
                            L.tiles_local, pos, tag, L.ptag, L.cell_size, L.cell_idx, L.cell_xf, L.cell_cap,
                            cell_xf_stride(L.cell_cap), L.nlist, L.nn, L.nlist_cap, nlist_row_stride(L.nlist_cap),
                            L.halo, L.halo_n, L.halo_cap, plan, L.halo_lds, L.rare_list, L.rare_n, L.tile_ctr,
-                           L.cell_count, L.n_cells, L.flag, L.sflag, L.build_count, L.status);
+                           L.cell_count, L.n_cells, L.xbuild, L.tref, L.slow_list, L.slow_n, L.flag, L.sflag, L.build_count,
+                           L.status);
     };
     if (L.has_bonds) {
         if (block == 256) go(k_build_lines<true, 256>, 256);
