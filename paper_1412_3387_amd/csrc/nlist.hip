@@ -277,7 +277,8 @@ struct FastShared {
 };
 
 // Exclusions of a tile of bonded rows: the rows' partner tags in an open-
-// addressed table, and per wave the staged places found for them.
+// addressed table, and per wave the first staged places found for them (n
+// counts all).
 template <int NT>
 struct ExShared {
     int32_t tag[kExSlots];
@@ -1004,8 +1005,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
             const int sq = sh.selfq[wv][lane];
             if (sq != 0xFFFF) drop(sq);
             if constexpr (EXCL) {
-                const int en = ex.n[wv][lane] < 2 * kMaxBondCap ? ex.n[wv][lane] : 2 * kMaxBondCap;
-                for (int b = 0; b < en; ++b) drop(ex.q[wv][lane][b]);
+                const int en = ex.n[wv][lane];
+                const bool more_ex = en > 2 * kMaxBondCap;
+                for (int b = 0; b < en && !more_ex; ++b) drop(ex.q[wv][lane][b]);
+                if (__builtin_expect(__ballot(more_ex) != 0ull, 0)) {
+                    // more copies of a row's partners than places are kept
+                    // (ghosts that reach a small frame from several sides):
+                    // every member's tag against the row's partners
+                    const int32_t *pr = ptag + (int64_t)(rbase + (more_ex ? lane : 0)) * bond_stride;
+#pragma unroll 1
+                    for (int q = 0; q < n; ++q) {
+                        const int32_t tj = tag[sh.cj[base + q]];
+                        bool match = false;
+                        for (int b = 0; b < bond_stride; ++b) match = match || (pr[b] >= 0 && pr[b] == tj);
+                        if (more_ex && match) drop(q);
+                    }
+                }
             }
             int c = 0;
 #pragma unroll
