@@ -229,6 +229,7 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
 // to a device list and built in general.
 
 constexpr int kFastThreads = 256;    // threads per workgroup by default (4 waves)
+constexpr int kFastThreadsMax = 512;
 constexpr int kBoxDense = 160;       // cells of a frame box looked at without marking the stencils first
 constexpr int kSegMin = 256;         // segments of a tile's plan there is always room for
 
@@ -247,6 +248,11 @@ struct PlanTile {
 };                                       // (as many as the context has room for)
 constexpr int kPlanHead = 80 + 16 * kTile;
 static_assert(offsetof(PlanTile, seg) == kPlanHead, "one packed block");
+
+// Rounds of segments that k_build_fast reads ahead of those it needs, whether
+// a plan has them or not: the plans are padded by as many.
+constexpr int kRounds = 5;
+constexpr int64_t kPlanOverRead = (int64_t)sizeof(float4) * kRounds * (kFastThreadsMax / kSeg);
 
 // Bytes of a plan block with room for seg_cap segments.
 __host__ __device__ inline int64_t plan_stride(int seg_cap) { return kPlanHead + (int64_t)sizeof(float4) * seg_cap; }
@@ -702,9 +708,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         cell_count[c] = 0;
     using Sh = FastShared<NT, LPR>;
     constexpr int kWaves = Sh::kWaves, kC = Sh::kC, kCw = Sh::kCw, kWords = Sh::kWords, kA = build_astride(kC);
-    constexpr int kRounds = 5;                     // staging reads of a lane in flight
     constexpr int kSegWave = kWave / kSeg;         // segments a wave stages at once
     static_assert(kWords * kWaves * 4 <= kWave, "one-wave scan of the marks");
+    static_assert(NT <= kFastThreadsMax, "pad of the plans");
     // LDS: this structure and the exclusions', then the staged positions in
     // whose place (all distances taken) the rows' halo indices [kTile][rstride]
     // are put together
@@ -757,7 +763,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     int t_next = x_next < tend ? tile_of(x_next) : t_cur;
 
     // a tile's plan: the header's first words, and this lane's segments of
-    // kRounds rounds from r0 on (read whether they are there or not)
+    // kRounds rounds from r0 on (read whether they are there or not, up to
+    // kPlanOverRead past the last; as many staging reads are in flight)
     float4 head[3], sg[kRounds];
     auto plan_of = [&](int t) { return reinterpret_cast<const PlanTile *>(plan + t * plan_stride); };
     auto read_segments = [&](int t, int r0) {
@@ -1195,7 +1202,8 @@ size_t flagged_list_bytes(int n_sys) { return flagged_bytes(n_sys); }
 
 size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows)
 {
-    return line_rows ? line_plan_bytes(tiles) : (size_t)(tiles > 0 ? tiles : 1) * (size_t)plan_stride(seg_cap);
+    return line_rows ? line_plan_bytes(tiles)
+                     : (size_t)(tiles > 0 ? tiles : 1) * (size_t)plan_stride(seg_cap) + (size_t)kPlanOverRead;
 }
 
 int cell_xf_slots(int cell_cap) { return cell_xf_stride(cell_cap); }
