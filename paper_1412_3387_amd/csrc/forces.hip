@@ -49,12 +49,16 @@ template <> __device__ __forceinline__ float pair_sqrt<float>(float x)
 }
 
 // A per-system constant in scalar registers from here on (else the compiler
-// reads it anew, and waits for it, for every pair).
+// reads it anew, and waits for it, for every pair).  The lane read is the
+// compiler's own instruction, so that it places the wait states that a scalar
+// register written by a vector instruction needs, whatever uses it.  The empty
+// statements hide that the value is the same in every lane (the read would be
+// dropped) and where it comes from.
 __device__ __forceinline__ uint32_t pinned(uint32_t x)
 {
-    uint32_t b;
-    // (wait states between a vector write, the lane read and the scalar's use)
-    asm volatile("s_nop 1\n\tv_readfirstlane_b32 %0, %1\n\ts_nop 1" : "=s"(b) : "v"(x));
+    asm volatile("" : "+v"(x));
+    uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+    asm volatile("" : "+s"(b));
     return b;
 }
 __device__ __forceinline__ float pinned(float x) { return __uint_as_float(pinned(__float_as_uint(x))); }
