@@ -279,7 +279,8 @@ struct FastShared {
     uint16_t cnt[kWaves][kTile];         // hits of each row in each wave's members
     uint16_t selfq[kWaves][kTile];       // the row's own staged place, 0xFFFF: not this wave's
     int32_t left[kWaves];                // the wave has members left for another pass
-    int32_t grab[2];                     // tile indices taken from the die's counter
+    int32_t grab[3];                     // tile indices taken from the die's counter: the next of
+                                         // the loop, the first two
 };
 
 // Exclusions of a tile of bonded rows: the rows' partner tags in an open-
@@ -751,13 +752,15 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
         return flagged_tile(F, nf, tprefix, n_sys, x, s);
     };
     int grabbed = 0;
+    // (words of their own: no barrier lies between their reads here and the
+    // first write of the loop's)
     if (tid == kWave) {
-        sh.grab[0] = take_tile(ctr);
         sh.grab[1] = take_tile(ctr);
+        sh.grab[2] = take_tile(ctr);
     }
     lds_barrier();
-    int x_next = dfirst + uni(sh.grab[1]);
-    int t_cur = dfirst + uni(sh.grab[0]);
+    int x_next = dfirst + uni(sh.grab[2]);
+    int t_cur = dfirst + uni(sh.grab[1]);
     if (t_cur >= tend) return;
     t_cur = tile_of(t_cur);
     int t_next = x_next < tend ? tile_of(x_next) : t_cur;
