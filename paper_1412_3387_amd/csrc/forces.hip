@@ -100,7 +100,6 @@ __host__ __device__ constexpr int halo_entry_bytes(int pot) { return pot == PAIR
 // Rows may be read this many entries past their end (two passes of the
 // widest split): the neighbour list is padded by as many tile columns.
 constexpr int kRowOverRead = 2 * 4 * 16;
-constexpr size_t kWideLds = 40 * 1024;  // LDS of a workgroup where all are resident, at most (four per CU)
 constexpr int kAhead = 512;      // workgroups ahead of the others for the tiles that take longest
 
 // One tile of the fused step.  A tile with per-pair images, or a halo larger

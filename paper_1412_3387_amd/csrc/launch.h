@@ -139,6 +139,7 @@ void launch_disp_flags(const LaunchCtx &L, const double4 *pos, int32_t *flag, in
 size_t force_lds_bytes(int pair, int halo_cap, int nlist_cap);
 int force_row_over_read();
 int force_halo_entry_bytes(int pair);
+constexpr size_t kWideLds = 40 * 1024;  // halo stage of a workgroup of the force pass, at most (four per CU)
 int nlist_chunk();  // chunk (64 or 32) of the framed build (default)
 int nlist_block(bool line_rows);  // threads per workgroup of the framed build (default)
 bool nlist_shape_ok(int chunk, int block);  // a shape launch_nlist runs

@@ -147,12 +147,13 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
         // halo_lds entries in LDS (sized for four or more workgroups per CU)
         // and reads any further entries from global memory.
         const int entry = force_halo_entry_bytes(p[s].pair);
-        const int lds_budget = std::max(32768 / entry / 64 * 64, 64);
         const double vol = boxes[s].L[0] * boxes[s].L[1] * boxes[s].L[2];
         const double rho = (double)std::max<int64_t>(boxes[s].n_cap, 1) / vol;
-        const double side = std::cbrt(64.0 / rho);
         const double rl = pair_cut(p[s]) + p[s].r_buff;
-        const double est = rho * std::pow(side + 2.0 * rl, 3.0);
+        auto halo_of = [&](double density) {
+            return density * std::pow(std::cbrt(64.0 / density) + 2.0 * rl, 3.0);
+        };
+        const double est = halo_of(rho);
         const int64_t rows_up = (boxes[s].n_cap + 63) / 64 * 64;
         int hc = p[s].halo_cap;
         if (hc <= 0) {
@@ -160,12 +161,33 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
             hc = (int)std::min<int64_t>(hc, rows_up);
         }
         hc = std::min(std::max(hc, 64), 65535);
-        int hl = p[s].sort_period > 0 ? (int)std::ceil(1.25 * est / 64.0) * 64 : lds_budget;
+        // The same for the shape that a tile has: the curve halves every axis
+        // of the box in turn, so the tiles are as flat or long as the box.
+        double halo = rho;
+        for (int a = 0; a < 3; ++a) halo *= boxes[s].L[a] * std::cbrt(64.0 / (rho * vol)) + 2.0 * rl;
+        // Entries beyond the stage cost far more than workgroups per CU do:
+        // once the mean halo outgrows 32 KB the stage takes the 40 KB that
+        // leave four (256,000 LJ particles with r_cut 4.0, forces 172 us with
+        // 32 KB, 103 with 40; 3.5: 76 and 75; a liquid of 180 x 180 x 18.5
+        // with r_list 3.4: 265 and 182).
+        const int full = (int)kWideLds / entry, part = 32768 / entry / 64 * 64;
+        const int lds_budget = std::max(halo > part ? full : part, 64);
+        int hl = p[s].sort_period > 0 ? (int)std::ceil(1.25 * halo / 64.0) * 64 : part;
         // where the mean halo fits, stay within the share of seven
         // 256-thread workgroups in a CU's 160 KB of LDS: seven resident tiles
         // per CU outrun six, though a few more tiles have halos beyond it
         const int share7 = std::max(163840 / 7 / entry / 64 * 64, 64);
-        if (p[s].sort_period > 0 && est <= share7) hl = std::min(hl, share7);
+        if (p[s].sort_period > 0 && halo <= share7) hl = std::min(hl, share7);
+        // A row and a halo capacity that both have room for more than the mean
+        // density asks for are those of a liquid that fills part of its box:
+        // the stage then holds the halos of the density that they have room
+        // for, up to the same share (a droplet of 256,000 LJ particles in 27
+        // times its volume: forces 99 us, now 53).
+        if (p[s].sort_period > 0 && p[s].halo_cap > 0) {
+            const double room = (p[s].nlist_cap - 24) / 1.35 / (4.0 / 3.0 * M_PI * rl * rl * rl);
+            const double of_room = std::min(room > rho ? halo_of(room) : 0.0, (hc - 64) / 2.5);
+            hl = std::max(hl, std::min((int)std::ceil(1.25 * of_room / 64.0) * 64, share7));
+        }
         hl = std::min(std::max(hl, 64), std::min(lds_budget, hc));
         Lo.halo_cap = std::max(Lo.halo_cap, hc);
         Lo.halo_lds = std::max(Lo.halo_lds, hl);
