@@ -122,10 +122,8 @@ typedef struct {
                               latches HOOMD_E_DANGEROUS_BUILD: a particle may
                               have passed r_buff/2 before it was seen
                               (Sec. 4.2, Sec. 6.1)                          */
-    int32_t tpp_nlist;     /* neighbour-list build: 64 or 32, the members of a
-                              tile's cells staged at once (1,536 or 768; the
-                              same for mixed-precision DPD either way), 0 =
-                              64 (anything else is HOOMD_E_ARG)            */
+    int32_t tpp_nlist;     /* neighbour-list build: 64 or 32 (the same build),
+                              0 = 64 (anything else is HOOMD_E_ARG)         */
     int32_t tpp_force;     /* lanes per particle, forces: 1, 2, 4, 8 or 16
                               (0 = chosen from the system size; hoomd_autotune
                               times the candidates) (Sec. 5.1, 5.2)         */

@@ -115,7 +115,7 @@ void launch_bin(const LaunchCtx &L, const double4 *pos, int nvt_w = 0);
 // The list of rebuilt systems alone (the binning launch writes it too).
 void launch_flagged(const LaunchCtx &L);
 void launch_cell_sort(const LaunchCtx &L, const double4 *pos);
-void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int w, int block);
+void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int block);
 void launch_force(const LaunchCtx &L, const ForceLaunch &F, int w, int block);
 void launch_thermo_reduce(const LaunchCtx &L, int w, int log_row, double timestep);
 void launch_set_flag(const LaunchCtx &L, int32_t *flag, int32_t value);
@@ -140,9 +140,9 @@ size_t force_lds_bytes(int pair, int halo_cap, int nlist_cap);
 int force_row_over_read();
 int force_halo_entry_bytes(int pair);
 constexpr size_t kWideLds = 40 * 1024;  // halo stage of a workgroup of the force pass, at most (four per CU)
-int nlist_chunk();  // chunk (64 or 32) of the framed build (default)
+int nlist_chunk();  // tpp_nlist by default (64 and 32 are one build)
 int nlist_block(bool line_rows);  // threads per workgroup of the framed build (default)
-bool nlist_shape_ok(int chunk, int block);  // a shape launch_nlist runs
+bool nlist_shape_ok(int chunk, int block);  // tpp_nlist and block_nlist that are taken
 int build_seg_cap(double cell_mean);  // segments of a tile's plan, from the mean members of a cell
 size_t flagged_list_bytes(int n_sys);
 size_t build_plan_bytes(int64_t tiles, int seg_cap, bool line_rows);

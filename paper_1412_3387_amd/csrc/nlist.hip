@@ -258,18 +258,20 @@ constexpr int64_t kPlanOverRead = (int64_t)sizeof(float4) * kRounds * (kFastThre
 __host__ __device__ inline int64_t plan_stride(int seg_cap) { return kPlanHead + (int64_t)sizeof(float4) * seg_cap; }
 
 // Members staged at once, each wave's in its own part: eight of a wave's
-// blocks of 16 fill a mask word of 32 bits per row and result group.  LPR 64
-// holds the kept members of most tiles of a liquid in one pass (an LJ liquid
+// blocks of 16 fill a mask word of 32 bits per row and result group.  1,536
+// hold the kept members of most tiles of a liquid in one pass (an LJ liquid
 // at 0.8442 keeps 1,140 on average), whose rows are put together in the LDS
-// of the staged positions, and leaves room for four workgroups of 256 threads
-// per CU; with LPR 32 most tiles take two passes.  (The passes decide the
+// of the staged positions, and leave room for four workgroups of 256 threads
+// per CU.  (With 768 most tiles take two passes: 256 / 512 threads, us, 1,116
+// / 2,074 against 902 / 1,384 for 2,000,000 LJ rows, 85 / 93 against 72 / 62
+// for 32,000, and no faster in any context measured.  The passes decide the
 // order of a row's entries, so they are the same with and without bonds.)
-constexpr int build_chunk(int lpr) { return 24 * lpr; }
+constexpr int kBuildChunk = 1536;
 constexpr int kExSlots = 512;        // slots of a tile's partner-tag table (64 rows x 4 partners)
 
-template <int NT, int LPR>
+template <int NT>
 struct FastShared {
-    static constexpr int kC = build_chunk(LPR);
+    static constexpr int kC = kBuildChunk;
     static constexpr int kWaves = NT / kWave;
     static constexpr int kCw = kC / kWaves;              // members of a wave
     static constexpr int kWords = (kCw / 16 + 7) / 8;
@@ -300,8 +302,8 @@ struct ExShared {
 constexpr int build_astride(int kc) { return kc + 16 + (64 - kc % 64) % 64; }
 template <int NT>
 constexpr int kExShared = (int)((sizeof(ExShared<NT>) + 15) / 16 * 16);
-template <int NT, int LPR>
-constexpr int kFastShared = (int)((sizeof(FastShared<NT, LPR>) + 15) / 16 * 16);
+template <int NT>
+constexpr int kFastShared = (int)((sizeof(FastShared<NT>) + 15) / 16 * 16);
 
 
 // The plan of one tile per wave (workgroups of one wave: no block barriers
@@ -675,7 +677,7 @@ static_assert(kExSlots == 1 << 9, "ex_slot");
 
 // NT threads per workgroup: its waves share a tile, each with members of its
 // own, which it reads, packs and takes the distances of without waiting for
-// the others; up to 16 LPR / kWaves of them at a time.  The waves meet three
+// the others; up to 1,536 / kWaves of them at a time.  The waves meet three
 // times per tile: when the hits are known (halo numbering needs all of them),
 // when the rows are together in LDS, and when they have been read out.
 //
@@ -689,7 +691,7 @@ static_assert(kExSlots == 1 << 9, "ex_slot");
 // four tiles per CU; eight waves a tile, two per CU, took 0.5 ms more with
 // the same code, because the fixed work is done twice as often and two tiles
 // hide less of the reads' latency.
-template <bool EXCL, int NT, int LPR>
+template <bool EXCL, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_build_fast(
     const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
     const double4 *__restrict__ pos, const int32_t *__restrict__ tag, const int32_t *__restrict__ ptag,
@@ -707,7 +709,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     // for the next build
     for (int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; c < n_cells; c += (int64_t)gridDim.x * blockDim.x)
         cell_count[c] = 0;
-    using Sh = FastShared<NT, LPR>;
+    using Sh = FastShared<NT>;
     constexpr int kWaves = Sh::kWaves, kC = Sh::kC, kCw = Sh::kCw, kWords = Sh::kWords, kA = build_astride(kC);
     constexpr int kSegWave = kWave / kSeg;         // segments a wave stages at once
     static_assert(kWords * kWaves * 4 <= kWave, "one-wave scan of the marks");
@@ -718,9 +720,9 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_
     extern __shared__ float4 lds_all[];
     Sh &sh = *reinterpret_cast<Sh *>(lds_all);
     using Ex = ExShared<NT>;
-    Ex &ex = *reinterpret_cast<Ex *>(reinterpret_cast<char *>(lds_all) + kFastShared<NT, LPR>);
+    Ex &ex = *reinterpret_cast<Ex *>(reinterpret_cast<char *>(lds_all) + kFastShared<NT>);
     float *const lds_a =
-        reinterpret_cast<float *>(reinterpret_cast<char *>(lds_all) + kFastShared<NT, LPR> + (EXCL ? kExShared<NT> : 0));
+        reinterpret_cast<float *>(reinterpret_cast<char *>(lds_all) + kFastShared<NT> + (EXCL ? kExShared<NT> : 0));
     uint16_t *const srows = reinterpret_cast<uint16_t *>(lds_a);
     int tid = threadIdx.x;
     const int wv = uni(tid >> 6);
@@ -1213,60 +1215,45 @@ int cell_xf_slots(int cell_cap) { return cell_xf_stride(cell_cap); }
 
 // LDS of the framed launch: the shared structures, the staged positions (in
 // their place the rows), or a tile of the general build.
-template <bool EXCL, int NT, int LPR>
+template <bool EXCL, int NT>
 static int fast_dyn(int cap)
 {
     const int rows = kTile * nlist_row_stride(cap) * 2;
-    const int framed = kFastShared<NT, LPR> + (EXCL ? kExShared<NT> : 0) +
-                       std::max(rows, 4 * build_astride(build_chunk(LPR)) * (int)sizeof(float));
+    const int framed = kFastShared<NT> + (EXCL ? kExShared<NT> : 0) +
+                       std::max(rows, 4 * build_astride(kBuildChunk) * (int)sizeof(float));
     return std::max(framed, (int)sizeof(GeneralShared<0>));
 }
 
-template <bool EXCL, int NT, int LPR>
+template <bool EXCL, int NT>
 static hipError_t fast_attr(int cap)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_build_fast<EXCL, NT, LPR>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, fast_dyn<EXCL, NT, LPR>(cap));
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(&k_build_fast<EXCL, NT>),
+                               hipFuncAttributeMaxDynamicSharedMemorySize, fast_dyn<EXCL, NT>(cap));
 }
 
 hipError_t prepare_nlist(int cap)
 {
-    const hipError_t es[8] = {fast_attr<false, 512, 64>(cap), fast_attr<false, 256, 64>(cap),
-                              fast_attr<false, 512, 32>(cap), fast_attr<false, 256, 32>(cap),
-                              fast_attr<true, 512, 64>(cap),  fast_attr<true, 256, 64>(cap),
-                              fast_attr<true, 512, 32>(cap),  fast_attr<true, 256, 32>(cap)};
+    const hipError_t es[4] = {fast_attr<false, 512>(cap), fast_attr<false, 256>(cap), fast_attr<true, 512>(cap),
+                              fast_attr<true, 256>(cap)};
     for (hipError_t e : es)
         if (e != hipSuccess) return e;
     return prepare_lines(cap);
 }
 
-template <bool EXCL, int NT, int LPR>
+template <bool EXCL, int NT>
 static void fast_inst(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int blocks, int rs)
 {
-    const int dyn = fast_dyn<EXCL, NT, LPR>(L.nlist_cap);
-    hipLaunchKernelGGL((k_build_fast<EXCL, NT, LPR>), dim3(blocks), dim3(NT), dyn, L.stream, L.sys, L.tprefix_local,
+    const int dyn = fast_dyn<EXCL, NT>(L.nlist_cap);
+    hipLaunchKernelGGL((k_build_fast<EXCL, NT>), dim3(blocks), dim3(NT), dyn, L.stream, L.sys, L.tprefix_local,
                        L.n_sys, L.tiles_local, pos, tag, L.ptag, L.bond_stride, L.cell_xf, L.nlist, L.nn, L.nlist_cap, rs, L.halo,
                        L.halo_n, L.halo_cap, L.plan, plan_stride(L.seg_cap), L.halo_lds, L.rare_list, L.rare_n,
                        L.tile_ctr, L.cell_count, L.n_cells, L.cell_size, L.cell_idx, L.cell_cap, L.xbuild, L.tref, L.slow_list,
                        L.slow_n, L.flag, L.flagged, L.build_count, L.status);
 }
 
-template <bool EXCL>
-static void fast_shape(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int blocks, int rs,
-                       int w, int block)
-{
-    if (w == 32) {
-        if (block == 256) fast_inst<EXCL, 256, 32>(L, pos, tag, blocks, rs);
-        else fast_inst<EXCL, 512, 32>(L, pos, tag, blocks, rs);
-    } else {
-        if (block == 256) fast_inst<EXCL, 256, 64>(L, pos, tag, blocks, rs);
-        else fast_inst<EXCL, 512, 64>(L, pos, tag, blocks, rs);
-    }
-}
-
-// w: chunk of the framed build (64 or 32); block: its threads per
-// workgroup (512 or 256).  The general build's shape is fixed.
-void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int w, int block)
+// block: threads per workgroup of the framed build (512 or 256).  The
+// general build's shape is fixed.
+void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, int block)
 {
     if (L.tiles_local == 0) {
         // no framed scan to clear the cell counts
@@ -1277,8 +1264,13 @@ void launch_nlist(const LaunchCtx &L, const double4 *pos, const int32_t *tag, in
     const int blocks = capped(L.tiles_local);
     const int rs = nlist_row_stride(L.nlist_cap);
     if (!L.line_rows) {
-        if (L.has_bonds) fast_shape<true>(L, pos, tag, blocks, rs, w, block);
-        else fast_shape<false>(L, pos, tag, blocks, rs, w, block);
+        if (L.has_bonds) {
+            if (block == 256) fast_inst<true, 256>(L, pos, tag, blocks, rs);
+            else fast_inst<true, 512>(L, pos, tag, blocks, rs);
+        } else {
+            if (block == 256) fast_inst<false, 256>(L, pos, tag, blocks, rs);
+            else fast_inst<false, 512>(L, pos, tag, blocks, rs);
+        }
         return;
     }
     launch_build_lines(L, pos, tag, block);

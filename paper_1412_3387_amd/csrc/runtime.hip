@@ -104,8 +104,8 @@ bool valid(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
                     (p[u].dt != q.dt || p[u].nvt_T0 != q.nvt_T0 || p[u].nvt_tau != q.nvt_tau))
                     return false;
         }
-        // launch shapes: the framed build takes a chunk (64 or 32) and 512 or
-        // 256 threads per workgroup (one shape for all systems); the force
+        // launch shapes: the framed build takes 64 or 32 (one build either way)
+        // and 512 or 256 threads per workgroup (one shape for all systems); the force
         // pass runs 64 rows x tpp_force lanes per workgroup
         if (q.tpp_nlist != 0 && !nlist_shape_ok(q.tpp_nlist, nlist_block(false))) return false;
         if (q.block_nlist != 0 && !nlist_shape_ok(nlist_chunk(), q.block_nlist)) return false;
@@ -499,7 +499,7 @@ void queue_rebuild(hoomd_ctx *c, const double4 *pos, const int32_t *tag, int slo
     c->L.since_inc = since_inc;
     launch_bin(c->L, pos, nvt_w);
     launch_cell_sort(c->L, pos);
-    launch_nlist(c->L, pos, tag, c->tpp_nlist, c->block_nlist);
+    launch_nlist(c->L, pos, tag, c->block_nlist);
 }
 
 ForceLaunch base_force(hoomd_ctx *c)
@@ -546,7 +546,7 @@ constexpr int kLongPairs = 8;
 int ensure_step_graph(hoomd_ctx *c, int p, int kind, double4 *const *P, double4 *const *V, bool dpd)
 {
     hipGraphExec_t &ge = c->graph_exec[p][kind];
-    const int sig = c->tpp_force | (c->tpp_nlist << 8) | (c->block_nlist << 16);
+    const int sig = c->tpp_force | (c->block_nlist << 16);
     if (ge && c->graph_sig[p][kind] == sig) return HOOMD_OK;
     if (ge) {
         (void)hipGraphExecDestroy(ge);
@@ -1465,7 +1465,7 @@ int tune_now(hoomd_ctx *c, bool use_cache)
         float best = 1e30f;
         int bk = 0;
         for (int k = 0; k < 4; ++k) {
-            const int w = kBuildShapes[k][0], b = kBuildShapes[k][1];
+            const int b = kBuildShapes[k][1];
             const float t = median5(c,
                                     [&] {
                                         launch_set_flag(c->L, flag_ptr(c, 7), 0);
@@ -1475,7 +1475,7 @@ int tune_now(hoomd_ctx *c, bool use_cache)
                                         c->L.flag = flag;
                                         c->L.sflag = sflag;
                                         launch_flagged(c->L);
-                                        launch_nlist(c->L, pos, c->arr.tag, w, b);
+                                        launch_nlist(c->L, pos, c->arr.tag, b);
                                     },
                                     e0, e1);
             c->build_ms[k] = t;
