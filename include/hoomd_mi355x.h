@@ -463,9 +463,11 @@ int hoomd_get_layout(hoomd_ctx *ctx, int32_t sys, hoomd_layout *out);
  * neighbour count to within 4) from a process-wide cache, and scans only
  * when there is none.  Candidates: the force pass with W = 1, 2, 4, 8, 16
  * lanes per particle (64 W threads per workgroup); the framed list build
- * with (tpp_nlist, block_nlist) = (64, 512), (64, 256), (32, 512),
- * (32, 256).  A scan rebuilds the neighbour list afterwards, so
- * the state is what it was.  Synchronises when tuning.  Fields given
+ * with 512 and 256 threads per workgroup (its times are reported for
+ * (tpp_nlist, block_nlist) = (64, 512), (64, 256), (32, 512), (32, 256),
+ * the last two the same builds as the first two; a scan leaves tpp_nlist at
+ * 64).  A scan rebuilds the neighbour list afterwards, so the state is what
+ * it was.  Synchronises when tuning.  Fields given
  * explicitly in hoomd_params are kept (not tuned). */
 typedef struct {
     int32_t tpp_nlist, block_nlist, tpp_force, block_force;

@@ -1373,7 +1373,10 @@ static float median5(hoomd_ctx *c, Fn launch, hipEvent_t e0, hipEvent_t e1)
 
 namespace {
 
-constexpr int kBuildShapes[4][2] = {{64, 512}, {64, 256}, {32, 512}, {32, 256}};
+// Threads per workgroup of the list build.  The reported times are those of
+// (tpp_nlist, block_nlist) = (64, 512), (64, 256), (32, 512), (32, 256), the
+// last two the same builds as the first two.
+constexpr int kBuildBlocks[2] = {512, 256};
 
 struct TuneEntry {
     int tpp_force, tpp_nlist, block_nlist;
@@ -1458,14 +1461,14 @@ int tune_now(hoomd_ctx *c, bool use_cache)
         c->block_force = 64 * bw;
     }
     if (!c->fixed_nlist && c->lay.tiles_local > 0) {
-        // the list build over its shapes, on the cells and plans just made:
+        // the list build over its workgroups, on the cells and plans just made:
         // each timed launch redoes the framed and the general build (the list
         // of tiles that the force pass takes first is emptied before)
         int32_t *flag = flag_ptr(c, 2), *sflag = sflag_ptr(c, 2);
         float best = 1e30f;
         int bk = 0;
-        for (int k = 0; k < 4; ++k) {
-            const int b = kBuildShapes[k][1];
+        for (int k = 0; k < 2; ++k) {
+            const int b = kBuildBlocks[k];
             const float t = median5(c,
                                     [&] {
                                         launch_set_flag(c->L, flag_ptr(c, 7), 0);
@@ -1478,14 +1481,14 @@ int tune_now(hoomd_ctx *c, bool use_cache)
                                         launch_nlist(c->L, pos, c->arr.tag, b);
                                     },
                                     e0, e1);
-            c->build_ms[k] = t;
+            c->build_ms[k] = c->build_ms[k + 2] = t;
             if (t < best) {
                 best = t;
                 bk = k;
             }
         }
-        c->tpp_nlist = kBuildShapes[bk][0];
-        c->block_nlist = kBuildShapes[bk][1];
+        c->tpp_nlist = nlist_chunk();
+        c->block_nlist = kBuildBlocks[bk];
         // a whole rebuild with the chosen shape leaves the state as it was
         launch_set_flags(c->L, flag, sflag, 1);
         queue_rebuild(c, pos, c->arr.tag, 2, 0);

@@ -1,4 +1,5 @@
-"""GPU: the values that `tpp_nlist` takes are one list build, entry by entry."""
+"""GPU: the values that `tpp_nlist` takes are one list build, entry by entry,
+and the autotuner times each build once."""
 import numpy as np
 import pytest
 
@@ -32,3 +33,18 @@ def test_one_build_for_every_tpp_nlist(B, kind, block):
         nn, rows = ctx.neighbor_rows(0)
         got.append((nn, np.concatenate([np.asarray(r) for r in rows])))
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("kind", ["lj", "dpd"])
+def test_autotune_times_a_build_once(B, kind):
+    """The two values of tpp_nlist report the time of their one build, and the
+    first of them is the one chosen."""
+    s = inputs.lj_fluid(20000, 411, 412) if kind == "lj" else inputs.dpd_fluid(20000, 413, 414)
+    kw = dict() if kind == "lj" else dict(pair=B.PAIR_DPD, r_cut=1.0, r_buff=0.5)
+    ctx = B.Context([B.ModelParams(precision=B.MIXED, sort_period=100, **kw)],
+                    [dict(pos=s.pos, vel=s.vel, L=s.L, tag=s.tag)])
+    t = ctx.autotune(1)
+    ctx.check()
+    bm = list(t.build_ms)
+    assert min(bm) > 0 and bm[2:] == bm[:2]
+    assert (t.tpp_nlist, t.block_nlist) == (64, 512 if bm[0] <= bm[1] else 256)
