@@ -168,10 +168,13 @@ Layout make_layout(const hoomd_params *p, int32_t n_sys, const hoomd_box *boxes)
         // Entries beyond the stage cost far more than workgroups per CU do:
         // once the mean halo outgrows 32 KB the stage takes the 40 KB that
         // leave four (256,000 LJ particles with r_cut 4.0, forces 172 us with
-        // 32 KB, 103 with 40; 3.5: 76 and 75; a liquid of 180 x 180 x 18.5
-        // with r_list 3.4: 265 and 182).
+        // 32 KB, 103 with 40; a liquid of 180 x 180 x 18.5 with r_list 3.4:
+        // 265 and 182).  The mean overrates compact tiles, whose halos have
+        // round corners: up to a tenth above 32 KB few tiles reach beyond
+        // them (r_cut 3.5, 9 % above: 76 and 75; 1,000,000 DPD particles,
+        // at the line, lose 3.5 % of a step with 40).
         const int full = (int)kWideLds / entry, part = 32768 / entry / 64 * 64;
-        const int lds_budget = std::max(halo > part ? full : part, 64);
+        const int lds_budget = std::max(halo > 1.1 * part ? full : part, 64);
         int hl = p[s].sort_period > 0 ? (int)std::ceil(1.25 * halo / 64.0) * 64 : part;
         // where the mean halo fits, stay within the share of seven
         // 256-thread workgroups in a CU's 160 KB of LDS: seven resident tiles
