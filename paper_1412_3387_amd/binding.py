@@ -484,8 +484,9 @@ class Context:
         return int(self._ws_view(lay.general_tiles, 1).cpu().item())
 
     def rare_tiles(self) -> int:
-        """Tiles of the last build that the force pass handles in its second
-        launch (per-pair images or a halo beyond its LDS stage)."""
+        """Tiles of the last build with per-pair images or a halo beyond the
+        force pass's LDS stage (they take its slower pair loop, and go first in
+        its launch)."""
         lay = self.layout(0)
         return int(self._ws_view(lay.rare_tiles, 1).cpu().item())
 

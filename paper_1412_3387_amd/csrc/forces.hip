@@ -37,7 +37,7 @@ template <> __device__ __forceinline__ double tsqrt<double>(double x) { return _
 // sqrt of a positive finite x, the correctly rounded result as
 // __builtin_sqrtf has it: the root estimate (within 1 ulp) is moved by one ulp
 // where the sign of a residual says so; the residuals are exact enough while x
-// is far above the underflow threshold.
+// is far above the underflow threshold (the rounding test known as Tuckerman's).
 template <typename T> __device__ __forceinline__ T pair_sqrt(T x) { return tsqrt<T>(x); }
 template <> __device__ __forceinline__ float pair_sqrt<float>(float x)
 {

@@ -60,7 +60,6 @@ struct LaunchCtx {
     int32_t *slow_list;            // tiles the framed build passes on to the general one
     char *plan;                    // per-tile plans of the framed build (build_plan_bytes)
     int seg_cap;                   // segments a plan has room for
-    bool sorted;                   // rows are put in Morton order (sort_period > 0)
     bool line_rows;                // the line-ordered build (mixed-precision DPD)
     int32_t *slow_n;               // their number (cleared by the binning launch)
     int32_t *rare_list;            // tiles the force pass takes first (per-pair images, halos beyond its stage)

@@ -6,23 +6,25 @@
 // claim their slots with one integer atomic per distinct cell.  A per-cell
 // pass then sorts the members of each cell by x coordinate, ties by row
 // index (rank sort inside one wave), so the list is deterministic although
-// the slots were claimed in arbitrary order, and a line of x-adjacent cells
-// is ordered by x.  It also resets the counters for the next build.
+// the slots were claimed in arbitrary order, and writes each member's FP32
+// position from the cell's corner beside it.  The list build clears the
+// counters for the next binning.
 //
-// Neighbour list: one workgroup per tile of 64 consecutive rows (Morton
-// ordered rows make a tile one or a few compact clusters).  The workgroup
-//   1. collects the stencil cells of all its rows and sorts out the
-//      distinct ones (a bitmap or a sort in LDS), so any tile shape works,
-//   2. lets W lanes per particle stride over the members of the particle's
-//      own 27 stencil cells and test |x_j - x_i|^2 < r_list^2 in FP64
-//      (minimum image written as the stencil's image shift, which for every
-//      pair inside r_list is bitwise the shift the exact quotient gives),
-//      compacting hits into the row with a 64-bit ballot,
-//   3. marks every member that some row uses, numbers the marked members in
-//      the order of their cells -- the tile's halo -- and rewrites the rows
-//      as 16-bit halo indices.
-// That is the general build; tiles that fit one unwrapped frame take the
-// framed build further below.
+// Neighbour list, a tile of 64 consecutive rows (Morton ordered rows make a
+// tile one or a few compact clusters) at a time:
+//   * Most tiles fit one frame, unwrapped across periodic faces, and are built
+//     in k_build_fast on the matrix cores (further down), from a plan of the
+//     tile's cells.
+//   * The others go through the general build (nlist_general.h): it sorts out
+//     the distinct stencil cells of all rows (a bitmap or a sort in LDS), so
+//     any tile shape works, and each row's lanes test the members of the row's
+//     own 27 stencil cells.  Here they read the FP32 copies, and the FP64 test
+//     on the stored positions (nearest image) decides beside r_list; beside
+//     the line-ordered build of mixed-precision DPD (nlist_lines.hip) members
+//     are staged and tested in FP64.
+//   * Either way the list is exactly { j : |x_j - x_i|^2 < r_list^2 in FP64 }.
+//     Every member that some row uses is numbered -- the tile's halo -- and
+//     the rows hold 16-bit halo indices.
 // The force pass then loads each halo position once per tile into LDS
 // instead of once per neighbour from L2.
 //
@@ -204,9 +206,9 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
 // taken on the matrix cores:
 //   * The tile's cells are placed in one frame: cell coordinates relative to
 //     the first row's cell, unwrapped across periodic faces, positions
-//     relative to the centre of the rows' bounding box.  The stencil cells of
-//     all rows are marked in a bitmap over the frame's box; those farther
-//     than r_list from the bounding box are dropped.
+//     relative to the centre of the rows' bounding box.  Cells of the frame's
+//     box within r_list of the bounding box of some 16 rows are taken; where
+//     the box is large, only those that some row's stencil meets (a bitmap).
 //   * Members are staged as FP32 positions in the frame: the cell list keeps
 //     each member's position from its cell's corner in FP32, and staging adds
 //     the corner's frame position (one coalesced read per member, a segment
@@ -225,8 +227,8 @@ __global__ __launch_bounds__(kBuildThreads) void k_build_tile(
 //     is the tile's halo, and every row's hits are expanded into halo indices
 //     in LDS and written out coalesced.
 // Tiles that do not fit (a frame wider than a periodic box, fewer than three
-// cells on a periodic axis, too many distinct cells or members) are appended
-// to a device list and built in general.
+// cells on a periodic axis, more segments than a plan holds) are appended to a
+// device list and built in general, first in the same launch.
 
 constexpr int kFastThreads = 256;    // threads per workgroup by default (4 waves)
 constexpr int kFastThreadsMax = 512;

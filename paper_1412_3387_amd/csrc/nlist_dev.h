@@ -261,15 +261,6 @@ __device__ __forceinline__ double uni(double v)
     return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
 }
 
-// The value that lane l (the same in every lane) holds.
-__device__ __forceinline__ double lane_value(double v, int l)
-{
-    const int64_t b = __double_as_longlong(v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-    return __longlong_as_double((int64_t)(((uint64_t)hi << 32) | lo));
-}
-
 __device__ __forceinline__ int wave_max_full(int v)
 {
     v = max(v, dpp_mov<0xB1>(v));

@@ -39,7 +39,7 @@ struct GeneralShared {
     int8_t sm[kTile][kStencil];           // image code (mx+1) + 3 (my+1) + 9 (mz+1)
     int32_t scan[kBuildThreads / kWave];
     int32_t ext[6];                       // min / max cell offset from the first row
-    int32_t info[4];                      // (unused), per-pair image flag, longest row
+    int32_t info[2];                      // per-pair image flag, longest row
     int32_t st[3][3];                     // the stencil's offsets
 };
 static_assert(kSlotMax < 65536, "slots of a tile in 16 bits");
@@ -129,7 +129,7 @@ __device__ __forceinline__ void general_tile(
         sh.ext[tid] = INT32_MAX;
         sh.ext[3 + tid] = INT32_MIN;
     }
-    if (tid == 0) sh.info[2] = 0;
+    if (tid == 0) sh.info[1] = 0;
     if (tid < 9) sh.st[tid / 3][tid % 3] = S.st[tid / 3][tid % 3];
     const int nst[3] = {S.nst[0], S.nst[1], S.nst[2]};
     const int nbits = marks ? ((int)ncell + 31) / 32 : 0;
@@ -237,7 +237,7 @@ __device__ __forceinline__ void general_tile(
         const int per[3] = {px, py, pz};
         for (int a = 0; a < 3; ++a)
             if (per[a] && (double)(sh.ext[3 + a] - sh.ext[a] + 3) * (Ls[a] / bins[a]) >= 0.5 * Ls[a]) pp = 1;
-        sh.info[1] = pp;
+        sh.info[0] = pp;
     }
     __syncthreads();
     // member counts of the distinct cells and their prefix
@@ -486,7 +486,7 @@ __device__ __forceinline__ void general_tile(
             }
         }
     }
-    if (active && sl == 0) atomicMax(&sh.info[2], ntot < cap ? ntot : cap);
+    if (active && sl == 0) atomicMax(&sh.info[1], ntot < cap ? ntot : cap);
     __syncthreads();
     // ---- 4. halo numbering and row rewrite -------------------------------------
     const int nwords = (nslot + 31) / 32;
@@ -540,9 +540,9 @@ __device__ __forceinline__ void general_tile(
     }
     if (tid == 0) {
         tref[tile] = x0;
-        halo_n[tile] = (int32_t)((uint32_t)nhalo | ((uint32_t)sh.info[2] << 16) | (sh.info[1] ? 0x80000000u : 0u));
+        halo_n[tile] = (int32_t)((uint32_t)nhalo | ((uint32_t)sh.info[1] << 16) | (sh.info[0] ? 0x80000000u : 0u));
         // per-pair images or a halo beyond the force pass's LDS staging
-        if (sh.info[1] || nhalo > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
+        if (sh.info[0] || nhalo > halo_lds) rare_list[atomicAdd(rare_n, 1)] = tile;
     }
     __threadfence_block();
     __syncthreads();

@@ -145,7 +145,7 @@ struct LineShared {
     int32_t grab[2];                     // tile indices taken from the die's counter
 };
 
-// Per-tile plan of the line-ordered build, written by k_cells_and_plan and read
+// Per-tile plan of the line-ordered build, written by k_cells_and_lines and read
 // by k_build_lines: a header {distinct cells (-1: passed on), slots, per-pair
 // image flag, 0}, then per distinct cell {cell, first slot} and its corner
 // in the frame, per row its frame position, and per row line its slot range

@@ -417,7 +417,7 @@ namespace {
 template <typename T> T *ws_ptr(hoomd_ctx *c, size_t off) { return reinterpret_cast<T *>(c->ws + off); }
 
 // Tiles that hold local rows, over all systems (the force pass's choice of
-// one launch or two depends on it).
+// its LDS stage depends on it).
 void count_busy_tiles(hoomd_ctx *c)
 {
     int64_t t = 0;
@@ -676,7 +676,6 @@ int hoomd_init(hoomd_ctx **out, const hoomd_params *params, int32_t n_sys, const
     L.plan = ws_ptr<char>(c, lay.plan);
     L.seg_cap = lay.seg_cap;
     L.line_rows = lay.line_rows;
-    L.sorted = params[0].sort_period > 0;
     L.rare_n = flag_ptr(c, 7);
     L.tile_ctr = ws_ptr<int32_t>(c, lay.tile_ctr);
     L.status = ws_ptr<Status>(c, lay.status);
