@@ -683,16 +683,18 @@ static_assert(kExSlots == 1 << 9, "ex_slot");
 // times per tile: when the hits are known (halo numbering needs all of them),
 // when the rows are together in LDS, and when they have been read out.
 //
-// Vector instructions bound it: about 10,000 per tile for an LJ liquid (1,140
+// Vector instructions bound it: about 9,400 per tile for an LJ liquid (1,140
 // members kept, 628 of them in the halo), a fifth of them the 75 blocks of
 // matrix results (30 each beside four matrix instructions), the others
 // staging (45 per 64 places), the expansion of the masks and the fixed work
-// of each wave; the matrix units are a quarter busy.  Built and sorted LJ
-// liquid of 2,000,000 rows: 1.02 ms (scan of x-cut lines, a wave per row:
-// 1.70 ms; 17,900 instructions per tile).  Four waves a tile and 36 KB leave
-// four tiles per CU; eight waves a tile, two per CU, took 0.5 ms more with
-// the same code, because the fixed work is done twice as often and two tiles
-// hide less of the reads' latency.
+// of each wave; the matrix units are 13 % busy, the vector units 57 %.  LJ
+// liquid of 2,000,000 rows: 0.86 ms on the sorted start, 1.02 to 1.07 in a melt
+// (scan of x-cut lines, a wave per row: 1.70 ms; 17,900 instructions per
+// tile).  Four waves a tile and 36 KB leave four tiles per CU; eight waves a
+// tile, two per CU, took 0.5 ms more with the same code, because the fixed
+// work is done twice as often and two tiles hide less of the reads' latency
+// (where a tile's latency counts eight can win, 56 against 76 us for 4,000 LJ
+// rows: the autotuner times both).
 template <bool EXCL, int NT>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void k_build_fast(
     const SysDev *__restrict__ sys, const int32_t *__restrict__ tprefix, int n_sys, int tiles,
